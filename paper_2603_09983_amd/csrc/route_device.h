@@ -147,7 +147,13 @@ __device__ void block_histogram(const int32_t *idx, int A, int E, int32_t *hist,
 // Histogram (optional), slot lookup, ascending miss list, per-slot assignment lists and the
 // list of active slots, by one workgroup.  idx / slot_table may point to LDS copies.
 //   hist == nullptr: no histogram.   slot_table == nullptr: slot_idx is an input (lists only).
-// LDS: hist_s[E], cnt_s[C], off_s[C+1], scan_s[32], sidx_s[min(A, kLdsCopy)].
+// LDS: hist_s[E], cnt_s[kRouteWaves][C], off_s[C+1], scan_s[48], sidx_s[min(A, kLdsCopy)].
+//
+// A stable counting sort in blocks of one assignment per thread.  Inside a wavefront the lanes of one slot find
+// each other from one ballot per bit of the slot id, so an assignment's rank among them is a population count;
+// the wavefronts' counts per slot go through LDS, and the slots' offsets are one prefix sum.  Bound by the chain
+// of LDS trips and barriers of one workgroup: 7.1 us at 1536 assignments on 48 slots, 95 us when every assignment
+// counted the earlier ones of its slot one by one.
 template <typename IdxPtr, typename TabPtr>
 __device__ void block_post(IdxPtr idx, TabPtr slot_table, int A, int E, int C, int32_t *hist,
                            int32_t *slot_idx, int32_t *miss_list, int32_t *miss_count, int32_t *slot_count,
@@ -155,22 +161,24 @@ __device__ void block_post(IdxPtr idx, TabPtr slot_table, int A, int E, int C, i
                            unsigned *n_active, lds_i32 *hist_s, lds_i32 *cnt_s, lds_i32 *off_s, lds_i32 *scan_s,
                            lds_i32 *sidx_s)
 {
+    static_assert(kMaxC <= kRouteThreads && kMaxC <= 1 << 10, "one thread per slot; ten bits of slot id");
     const int tid = threadIdx.x, lane = tid & (kWave - 1), w = tid / kWave;
-    const int nw = blockDim.x / kWave;
+    const int nw = kRouteWaves;
+    const unsigned long long below = (1ull << lane) - 1ull;
     if (hist)
-        for (int e = tid; e < E; e += blockDim.x) hist_s[e] = 0;
-    for (int c = tid; c < C; c += blockDim.x) cnt_s[c] = 0;
+        for (int e = tid; e < E; e += kRouteThreads) hist_s[e] = 0;
+    for (int i = tid; i < nw * C; i += kRouteThreads) cnt_s[i] = 0;
+    if (tid < C) off_s[tid] = 0;   // (assignments of each slot so far)
     __syncthreads();
-    // pass over the assignments: histogram, slot of each, slot counts, miss list
     int running = 0;
-    for (int base = 0; base < A; base += blockDim.x) {
-        int a = base + tid;
-        bool valid = a < A;
+    for (int base = 0; base < A; base += kRouteThreads) {
+        const int a = base + tid;
+        const bool valid = a < A;
         int c = -1;
         if (valid) {
             if (slot_table) {
-                int e = idx[a];
-                bool e_ok = (unsigned)e < (unsigned)E;
+                const int e = idx[a];
+                const bool e_ok = (unsigned)e < (unsigned)E;
                 if (hist && e_ok) __hip_atomic_fetch_add(&hist_s[e], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 c = e_ok ? slot_table[e] : -1;
             } else {
@@ -178,77 +186,111 @@ __device__ void block_post(IdxPtr idx, TabPtr slot_table, int A, int E, int C, i
             }
             if ((unsigned)c >= (unsigned)C) c = -1;
             if (slot_table) slot_idx[a] = c;
-            if (a < kLdsCopy) sidx_s[a] = c;
-            if (c >= 0) __hip_atomic_fetch_add(&cnt_s[c], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        bool miss = valid && c < 0;
-        unsigned long long bal = __ballot(miss);
-        int before = __popcll(bal & ((1ull << lane) - 1ull));
-        if (A > kWave) {
-            // more than one wavefront holds assignments: offsets across wavefronts through LDS
-            if (lane == 0) scan_s[w] = __popcll(bal);
-            __syncthreads();
-            int wave_base = 0, total = 0;
-            for (int i = 0; i < nw; ++i) {
-                int s = scan_s[i];
-                if (i < w) wave_base += s;
-                total += s;
+        const bool miss = valid && c < 0;
+        const unsigned long long bal = __ballot(miss);
+        // the lanes of this wavefront that name the same slot
+        unsigned long long same = __ballot(c >= 0);
+        for (int bit = 0; (C - 1) >> bit > 0; ++bit) {
+            const unsigned long long on = __ballot((c >> bit) & 1);
+            same &= ((c >> bit) & 1) ? on : ~on;
+        }
+        int r = __popcll(same & below);
+        if (c >= 0 && r == 0) cnt_s[w * C + c] = __popcll(same);
+        if (lane == 0) scan_s[w] = __popcll(bal);
+        __syncthreads();
+        // (only the wavefronts that hold an assignment have anything to add)
+        const int left = A - base, nwv = left < kRouteThreads ? (left + kWave - 1) / kWave : nw;
+        int wave_base = 0, total = 0;
+        for (int i = 0; i < nwv; ++i) {
+            const int s = scan_s[i];
+            if (i < w) wave_base += s;
+            total += s;
+        }
+        if (miss && miss_list) miss_list[running + wave_base + __popcll(bal & below)] = a;
+        running += total;
+        if (c >= 0) {
+            r += off_s[c];
+            for (int i = 0; i < w; ++i) r += cnt_s[i * C + c];
+        }
+        // rank and slot wait for the offsets: in LDS, or behind it in the words that they end up in
+        if (valid) {
+            if (a < kLdsCopy) sidx_s[a] = c >= 0 ? r << 10 | c : -1;
+            else pos[a] = c >= 0 ? r : -1;
+        }
+        __syncthreads();
+        if (tid < C) {
+            int n = 0;
+            for (int i = 0; i < nwv; ++i) {
+                n += cnt_s[i * C + tid];
+                cnt_s[i * C + tid] = 0;
             }
-            if (miss && miss_list) miss_list[running + wave_base + before] = a;
-            running += total;
-            __syncthreads();
-        } else {
-            if (miss && miss_list) miss_list[before] = a;
-            if (w == 0 && lane == 0) scan_s[0] = __popcll(bal);
+            off_s[tid] += n;
         }
+        __syncthreads();
     }
-    __syncthreads();
-    if (A <= kWave) running = scan_s[0];
     if (tid == 0 && miss_count) *miss_count = running;
     if (hist)
-        for (int e = tid; e < E; e += blockDim.x) hist[e] = hist_s[e];
-    // offsets and active list: thread c looks at the slots before it
-    for (int c = tid; c <= C; c += blockDim.x) {
-        int o = 0, na = 0;
-#pragma unroll 8
-        for (int c2 = 0; c2 < c; ++c2) {
-            int v = cnt_s[c2];
-            o += v;
-            na += v > 0 ? 1 : 0;
+        for (int e = tid; e < E; e += kRouteThreads) hist[e] = hist_s[e];
+    // offsets and active list: prefix sums of the counts and of the flag (count > 0) over the slots
+    const int cntv = tid < C ? off_s[tid] : 0;
+    int inc_o = cntv;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int v = __shfl_up(inc_o, d, kWave);
+        if (lane >= d) inc_o += v;
+    }
+    const unsigned long long act = __ballot(cntv > 0);
+    if (lane == kWave - 1) {
+        scan_s[16 + w] = inc_o;
+        scan_s[32 + w] = __popcll(act);
+    }
+    __syncthreads();
+    int base_o = 0, base_a = 0, tot_o = 0, tot_a = 0;
+    for (int i = 0; i < (C + kWave - 1) / kWave; ++i) {
+        const int vo = scan_s[16 + i], va = scan_s[32 + i];
+        if (i < w) {
+            base_o += vo;
+            base_a += va;
         }
-        off_s[c] = o;
-        slot_offset[c] = o;
-        if (c < C) {
-            int v = cnt_s[c];
-            slot_count[c] = v;
-            if (v > 0) active_slots[na] = c;
-        } else {
-            *n_active = (unsigned)na;
-        }
+        tot_o += vo;
+        tot_a += va;
+    }
+    if (tid < C) {
+        const int off = base_o + inc_o - cntv;
+        off_s[tid] = off;
+        slot_offset[tid] = off;
+        slot_count[tid] = cntv;
+        if (cntv > 0) active_slots[base_a + __popcll(act & below)] = tid;
+    }
+    if (tid == 0) {
+        slot_offset[C] = tot_o;
+        *n_active = (unsigned)tot_a;
     }
     __syncthreads();
     // lists: assignment a goes to position off[slot] + (number of earlier assignments of that slot),
     // so the list of a slot holds its assignments in ascending flat id
-    for (int a = tid; a < A; a += blockDim.x) {
-        int s = (a < kLdsCopy) ? sidx_s[a] : slot_idx[a];
-        if ((unsigned)s >= (unsigned)C) {
+    for (int a = tid; a < A; a += kRouteThreads) {
+        int c, r;
+        if (a < kLdsCopy) {
+            const int v = sidx_s[a];
+            c = v < 0 ? -1 : v & 1023;
+            r = v >> 10;
+        } else {
+            r = pos[a];   // (written by this thread)
+            c = r < 0 ? -1 : slot_idx[a];
+        }
+        if (c < 0) {
             pos[a] = -1;
             continue;
         }
-        int r = 0;
-#pragma unroll 8
-        for (int a2 = 0; a2 < a; ++a2) {
-            int s2 = (a2 < kLdsCopy) ? sidx_s[a2] : slot_idx[a2];
-            if ((unsigned)s2 >= (unsigned)C) s2 = -1;
-            r += s2 == s ? 1 : 0;
-        }
-        int p = off_s[s] + r;
+        const int p = off_s[c] + r;
         perm[p] = a;
         pos[a] = p;
     }
 }
 
-// dynamic LDS: hist_s[E] tab_s[E] cnt_s[4C] off_s[C+1] scan_s[48] sidx_s[cap] idx_s[cap] lg_s[waves*E]
+// dynamic LDS: hist_s[E] tab_s[E] cnt_s[waves*C] off_s[C+1] scan_s[48] sidx_s[cap] idx_s[cap] lg_s[waves*E]
 struct PostLds {
     lds_i32 *hist_s, *tab_s, *cnt_s, *off_s, *scan_s, *sidx_s, *idx_s;
     lds_f32 *lg_s;
@@ -262,18 +304,18 @@ __device__ inline PostLds carve_lds(int *dyn_, int E, int C, int A)
     p.hist_s = dyn;
     p.tab_s = p.hist_s + E;
     p.cnt_s = p.tab_s + E;
-    p.off_s = p.cnt_s + 4 * C;   // (counters of the general builder, or up to four mask words per slot)
+    p.off_s = p.cnt_s + kRouteWaves * C;   // (counters of the general builder, or up to four mask words per slot)
     p.scan_s = p.off_s + C + 1;
     p.sidx_s = p.scan_s + 48;
     p.idx_s = p.sidx_s + cap;
-    p.lg_s = (lds_f32 *)(dyn + ((2 * E + 5 * C + 49 + 2 * cap + 3) & ~3));
+    p.lg_s = (lds_f32 *)(dyn + ((2 * E + (kRouteWaves + 1) * C + 49 + 2 * cap + 3) & ~3));
     return p;
 }
 
 inline size_t post_lds_bytes(int E, int C, int A, bool with_topk)
 {
     const int cap = A < kLdsCopy ? A : kLdsCopy;
-    size_t n = (size_t)2 * E + 4 * C + (C + 1) + 48 + 2 * cap;
+    size_t n = (size_t)2 * E + (size_t)kRouteWaves * C + (C + 1) + 48 + 2 * cap;
     if (with_topk) n += (size_t)kRouteWaves * lg_stride(E) + 4;
     return n * sizeof(int);
 }
