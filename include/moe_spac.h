@@ -25,10 +25,11 @@
  *     was launched.  No exceptions, no abort, nothing printed.
  *   - Supported sizes: 1 <= k <= min(E, 64); E <= 512; T*E <= 65536;
  *     C <= 1024; H, F and F_shared multiples of 8 (rows of 16 bytes); bf16
- *     tensors and `out` 16-byte aligned.  Batches of up to 32 tokens with
- *     H, F and F_shared multiples of 64 run in the weight-streaming kernels
- *     at any H; every other shape runs in a kernel that keeps a token tile's
- *     hidden rows in LDS, which limits it to H <= 4992 (MOE_ERR_SHAPE beyond).
+ *     tensors and `out` 16-byte aligned.  Batches of up to 32 tokens run
+ *     in the weight-streaming kernels, with H, F and F_shared multiples of 64
+ *     at any H; every other shape is limited to H <= 4992 (MOE_ERR_SHAPE
+ *     beyond): larger batches may run in a kernel that keeps a token tile's
+ *     hidden rows in LDS.
  *   - Two calls that share a workspace must not overlap in time.  A
  *     workspace holds state between calls (a call counter and regions whose
  *     entries are stamped with it): initialise it with moe_workspace_init
@@ -85,7 +86,7 @@ typedef struct moe_shape {
 enum {
     MOE_LAUNCH_AUTO = 0,
     MOE_LAUNCH_THREE = 1,         /* routing | gate/up stream | down stream + final sum (+ a combine launch above 32 tokens) */
-    MOE_LAUNCH_TWO = 2,           /* routing steps at the head of the gate/up kernel: T <= 32, E <= 128 */
+    MOE_LAUNCH_TWO = 2,           /* routing steps at the head of the gate/up kernel: T <= 32, E <= 128, H, F, F_shared multiples of 64 */
     MOE_LAUNCH_ONE = 3,           /* routing, gate/up, down and final sum as one kernel: T <= 16, E <= 128, H, F multiples of 64 */
     MOE_LAUNCH_ROUTE_PLUS_ONE = 4 /* routing kernel, then gate/up, down and final sum as one kernel: T <= 16 */
 };

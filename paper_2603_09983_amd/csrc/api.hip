@@ -41,7 +41,7 @@ int check_ffn_shape(int T, int H, int F, int k, int C, int n_shared, int F_share
     if (T < 1 || H < 1 || F < 1 || k < 1 || C < 0 || C > kMaxC || T > 65535) return MOE_ERR_SHAPE;
     if (H % 8 != 0 || F % 8 != 0 || (n_shared > 0 && F_shared % 8 != 0)) return MOE_ERR_ALIGN;   // 16-byte rows
     // the kernel that takes what the streaming kernels do not keeps a token tile's hidden rows in LDS
-    if (!use_stream_kernels(T, k, C, H, F, n_shared, F_shared) && ffn_token_tiles(T, H) == 0) return MOE_ERR_SHAPE;
+    if (!use_stream64(T, k, C, H, F, n_shared, F_shared) && ffn_token_tiles(T, H) == 0) return MOE_ERR_SHAPE;
     return MOE_OK;
 }
 
@@ -366,7 +366,9 @@ int run_ffn(const void *hidden, const float *topk_w, const void *w_gate, const v
         e = launch_layer(l, routing, s);
         return e == hipSuccess ? MOE_OK : launch_failed(e);
     }
-    if (use_stream_kernels(T, k, C, H, F, n_shared, F_shared)) {
+    if (w.stream) {
+        // (batches beyond 32 tokens: single panels of whole 64s only)
+        auto panel = [&](int K) { return T > 32 ? stream_panel_width(K) : stream_panel(K); };
         StreamArgs g = {};
         g.w0 = (const uint16_t *)w_gate; g.w1 = (const uint16_t *)w_up;
         g.s0 = (const uint16_t *)sh_gate; g.s1 = (const uint16_t *)sh_up;
@@ -377,7 +379,7 @@ int run_ffn(const void *hidden, const float *topk_w, const void *w_gate, const v
         g.n_active = (const unsigned *)(ws + w.ctrl) + kCtrlNActive;
         g.T = T; g.k = k; g.C = C;
         g.R = F; g.K = H; g.R_sh = F_shared; g.K_sh = H; g.n_shared = n_shared;
-        g.KP = g.KP_sh = stream_panel_width(H);
+        g.KP = g.KP_sh = panel(H);
         // (routing != null: the gate/up launch does the routing steps itself)
         e = routing ? launch_stream_routed(g, *routing, s) : launch_stream(g, true, nullptr, s);
         if (e != hipSuccess) return launch_failed(e);
@@ -387,7 +389,7 @@ int run_ffn(const void *hidden, const float *topk_w, const void *w_gate, const v
         d.bsrc = (const uint16_t *)(ws + w.act); d.bsrc_sh = (const uint16_t *)(ws + w.act_sh);
         d.out = ws + w.o; d.out_sh = ws + w.o_sh;
         d.R = H; d.K = F; d.R_sh = H; d.K_sh = F_shared;
-        d.KP = stream_panel_width(F); d.KP_sh = n_shared ? stream_panel_width(F_shared) : 0;
+        d.KP = panel(F); d.KP_sh = n_shared ? panel(F_shared) : 0;
         if (stream_can_join(d)) {
             // small batch: the down kernel also sums the per-assignment outputs into `out`
             JoinArgs j = {};
@@ -506,6 +508,8 @@ int run_layer(const moe_shape_t *sh, const void *hidden, const float *router_w, 
     if (form == MOE_LAUNCH_ONE && !(can_layer && can_route_inside)) return MOE_ERR_SHAPE;
     if (form == MOE_LAUNCH_ROUTE_PLUS_ONE && !can_layer) return MOE_ERR_SHAPE;
     if (form == MOE_LAUNCH_TWO && !can_route_inside) return MOE_ERR_SHAPE;
+    // (by name only for widths of whole 64s, as the other forms)
+    if (sh->launch_form == MOE_LAUNCH_TWO && !use_stream64(sh->T, sh->k, sh->C, sh->H, sh->F, n_sh, F_sh)) return MOE_ERR_SHAPE;
     if (form == MOE_LAUNCH_ONE || form == MOE_LAUNCH_TWO) {
         r.lists_pub = (unsigned long long *)(ws + w.lists_pub);
         return run_ffn(hidden, topk_w, w_gate, w_up, w_down, shared_gate, shared_up, shared_down, sh->T, sh->H,
@@ -576,7 +580,11 @@ extern "C" int moe_verify_layer_static(const moe_shape_t *sh, const void *hidden
     int rc = check_layer_args(sh, hidden, router_w, slot_table, w_gate, w_up, w_down, shared_gate, shared_up,
                               shared_down, topk_idx, topk_w, hist, slot_idx, miss_list, miss_count, out);
     if (rc) return rc;
-    const WsLayout w = ws_layout(sh->T, sh->E, sh->k, sh->C, sh->H, sh->F, sh->n_shared, sh->F_shared);
+    const int F_sh = sh->n_shared ? sh->F_shared : 0;
+    WsLayout w = ws_layout(sh->T, sh->E, sh->k, sh->C, sh->H, sh->F, sh->n_shared, sh->F_shared);
+    // (ragged widths: the general kernel needs less scratch memory for some shapes with many experts per token)
+    if (w.total > kScratchBytes && !use_stream64(sh->T, sh->k, sh->C, sh->H, sh->F, sh->n_shared, F_sh))
+        w = ws_layout(sh->T, sh->E, sh->k, sh->C, sh->H, sh->F, sh->n_shared, sh->F_shared, true);
     if (w.total > kScratchBytes) return MOE_ERR_SCRATCH;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);

@@ -1005,7 +1005,7 @@ size_t layer_lds_bytes(int T, int k, int E, int C, int H, int F, int n_shared, i
 bool use_layer_kernel(int T, int k, int E, int C, int H, int F, int n_shared, int F_shared)
 {
     if (T > 16 || C < 1 || C > kMaxC || H % 64 != 0 || F % 64 != 0 || (n_shared > 0 && F_shared % 64 != 0)) return false;
-    if (!use_stream_kernels(T, k, C, H, F, n_shared, F_shared)) return false;
+    if (!use_stream64(T, k, C, H, F, n_shared, F_shared)) return false;
     const LayerGeom g = layer_geom(H, F, n_shared, F_shared);
     if (g.npi > 4) return false;
     if ((size_t)T * 8 * (k + n_shared) * 4 > (size_t)g.tile_bytes) return false;   // the strip of the final sum sits in the tile buffer

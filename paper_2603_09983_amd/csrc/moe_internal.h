@@ -19,23 +19,26 @@ constexpr int kCtrlBytes = 256;
 // contraction lengths up to this many columns are parked in LDS whole (one panel per item)
 constexpr int kPanelMax = 2048;
 
-int stream_panel_width(int K);     // columns of a contraction parked in LDS at a time; 0 when K has no panel split
+// Columns of a contraction parked in LDS at a time.  stream_panel_width: equal panels of whole 64s (0 when K has no
+// such split); stream_panel: any K that is a multiple of 8, the last panel may begin inside the one before.
+int stream_panel_width(int K);
+int stream_panel(int K);
 
 // LDS of one workgroup of a streaming kernel: the tile (16 rows of a panel of KP columns, padded), the
 // partial results, the per-slot lists and the token list, the output buffer with its records.
 constexpr int kStreamRowPad = 16;   // bytes of padding per LDS tile row
 constexpr int kStreamOutCap = 16;   // items whose results wait in LDS between two batches of stores
+static inline size_t stream_tile_lds(int KP) { return (size_t)16 * ((2 * (size_t)KP + 127) / 128 * 128 + kStreamRowPad); }
 static inline size_t stream_lds_need(int KP, int T, int k, int C, bool gateup)
 {
     const size_t groups = T > 16 ? 2 : 1;
-    return (size_t)16 * (2 * (size_t)KP + kStreamRowPad) + groups * 16 * kWave * 16 +
+    return stream_tile_lds(KP) + groups * 16 * kWave * 16 +
            ((size_t)3 * C + (size_t)T * k) * 4 + (size_t)kStreamOutCap * (groups * (gateup ? 128 : 256) + 8) * 4;
 }
 
-// The streaming kernels (stream.hip) take every batch of up to 32 tokens, and larger batches when
-// every item is a single panel, as long as the lists fit their LDS; the rest (wide matrices with large
-// batches, ragged row lengths, very long lists) falls back to ffn.hip.
-static inline bool use_stream_kernels(int T, int k, int C, int H, int F, int n_shared, int F_shared)
+// Widths of whole 64s: the streaming kernels (stream.hip) take every batch of up to 32 tokens, and larger batches
+// when every item is a single panel, as long as the lists fit their LDS.
+static inline bool use_stream64(int T, int k, int C, int H, int F, int n_shared, int F_shared)
 {
     // (their 1 KB pieces must not straddle the middle of a 16-row tile: row bytes a multiple of 128)
     if (H % 64 != 0 || F % 64 != 0 || (n_shared > 0 && F_shared % 64 != 0)) return false;
@@ -44,6 +47,17 @@ static inline bool use_stream_kernels(int T, int k, int C, int H, int F, int n_s
     const int kp_s = n_shared > 0 ? stream_panel_width(F_shared) : 0;
     if (kp_h == 0 || kp_f == 0 || (n_shared > 0 && kp_s == 0)) return false;
     return stream_lds_need(kp_h, T, k, C, true) <= (size_t)kLdsBytes &&
+           stream_lds_need(kp_f > kp_s ? kp_f : kp_s, T, k, C, false) <= (size_t)kLdsBytes;
+}
+
+// ... and batches of up to 32 tokens of any width (multiples of 8) in the RAGGED instances.  The rest (wide or ragged
+// matrices with larger batches, very long lists) runs in ffn.hip.
+static inline bool use_stream_kernels(int T, int k, int C, int H, int F, int n_shared, int F_shared)
+{
+    if (use_stream64(T, k, C, H, F, n_shared, F_shared)) return true;
+    if (T > 32 || H < 8 || F < 8 || H % 8 != 0 || F % 8 != 0 || (n_shared > 0 && (F_shared < 8 || F_shared % 8 != 0))) return false;
+    const int kp_f = stream_panel(F), kp_s = n_shared > 0 ? stream_panel(F_shared) : 0;
+    return stream_lds_need(stream_panel(H), T, k, C, true) <= (size_t)kLdsBytes &&
            stream_lds_need(kp_f > kp_s ? kp_f : kp_s, T, k, C, false) <= (size_t)kLdsBytes;
 }
 
@@ -80,6 +94,7 @@ constexpr int kTagIdxEntries = 4096;   // (at most as many as the routing kernel
 // Byte offsets of the scratch arrays inside the caller's workspace.
 struct WsLayout {
     size_t ctrl, tagged, tagged_idx, perm, pos, slot_count, slot_offset, active, part, part_sh, act, act_sh, o, o_sh, total;
+    bool stream;        // the streaming kernels' regions (else: those of the general kernel)
     size_t lists_pub;   // stamped copies of the per-slot lists (gate/up kernel that does the routing itself), or 0
 };
 
@@ -108,9 +123,11 @@ constexpr int kKindLayer = 9;     // measurement aid: the one-launch layer kerne
 
 static inline int n_slices(int F) { return (F + kSliceF - 1) / kSliceF; }
 
-static inline WsLayout ws_layout(int T, int E, int k, int C, int H, int F, int n_shared, int F_shared)
+// general: lay out for the general FFN kernel also where the streaming kernels would take the shape
+static inline WsLayout ws_layout(int T, int E, int k, int C, int H, int F, int n_shared, int F_shared, bool general = false)
 {
     WsLayout w;
+    w.stream = !general && use_stream_kernels(T, k, C, H, F, n_shared, F_shared);
     size_t A = (size_t)T * k;
     size_t o = 0;
     w.lists_pub = 0;
@@ -122,7 +139,7 @@ static inline WsLayout ws_layout(int T, int E, int k, int C, int H, int F, int n
     w.slot_count = o;  o += align256((size_t)(C > 0 ? C : 1) * 4);
     w.slot_offset = o; o += align256((size_t)(C + 1) * 4);
     w.active = o;      o += align256((size_t)(C > 0 ? C : 1) * 4);
-    if (!use_stream_kernels(T, k, C, H, F, n_shared, F_shared)) {
+    if (!w.stream) {
         // large batches: per-slice partial sums of the fused FFN kernel
         w.part = o;    o += align256((size_t)n_slices(F) * A * H * 4);
         w.part_sh = o; o += align256((size_t)n_shared * n_slices(F_shared) * T * H * 4);
@@ -205,11 +222,11 @@ struct StreamArgs {
     int R, K, R_sh, K_sh, n_shared, C;
     int KP, KP_sh;             // panel widths (columns parked in LDS at a time)
     // Filled in by the launch functions: panels per routed / shared item, and floor(2^32 / d) for the divisors of
-    // the kernel's index arithmetic (grid size, items per routed / shared expert, k, k + n_shared).  A division by a
+    // the kernel's index arithmetic (grid size, items per routed / shared expert, panels per item, k, k + n_shared).  A division by a
     // value only known at run time is ~30 instructions, and in the prologue of a launch sixteen wavefronts execute
     // them one after the other on the compute unit's one scalar unit.
     int np, np_sh;
-    unsigned rcp_G, rcp_tiles, rcp_tiles_sh, rcp_k, rcp_S;
+    unsigned rcp_G, rcp_tiles, rcp_tiles_sh, rcp_np, rcp_k, rcp_S;
 };
 
 // n / d with rcp = floor(2^32 / d) (d = 1: 2^32 - 1): the estimate is never too large and at most one short.

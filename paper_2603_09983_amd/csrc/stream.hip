@@ -100,13 +100,19 @@ __device__ unsigned long long g_timeline[2][kTimelineGroups][kTimelineWords];
 //
 // WSPLIT (down kernel, shared experts whose items have another number of panels than the routed ones):
 // the item list is cut into runs of equal numbers of TILES instead of items.
-template <bool GATEUP, int NPI, int MODE, bool JOIN, bool WSPLIT, bool FUSED>
+//
+// RAGGED (batches of up to 32 tokens): contraction lengths and row counts that are multiples of 8 only.  A tile's
+// pieces are then counted per half (8 rows of rs bytes), the lanes of a half's last piece that lie beyond it re-read
+// its last 16 bytes; the last panel of a row starts early enough to be as wide as the others, and the columns that
+// the panel before had, or that no row has, are zero in both operands; the down kernel's last tile may have 8 rows.
+template <bool GATEUP, int NPI, int MODE, bool JOIN, bool WSPLIT, bool FUSED, bool RAGGED>
 __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_lds_bytes, const JoinArgs &jn,
                                             const RouteArgs &ra)
 {
     static_assert(!WSPLIT || !GATEUP, "gate/up items all have the panels of the hidden size");
     static_assert(!FUSED || (GATEUP && MODE <= 1 && !JOIN && !WSPLIT), "the routing steps ride on the gate/up kernels of up to 32 tokens");
     static_assert(!JOIN || (!GATEUP && MODE < 2), "the join rides on the down kernel of batches up to 32 tokens");
+    static_assert(!RAGGED || MODE < 2, "ragged widths of larger batches are another kernel's");
     constexpr int NG = MODE == 0 ? 1 : 2;   // token groups of 16 multiplied per pass
     constexpr bool MULTIPASS = MODE == 2;
     constexpr int RPI = GATEUP ? 8 : 16;    // output rows per item
@@ -136,7 +142,11 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     // The shared experts' items need nothing from the routing step, so each workgroup takes its
     // run of them first: their weights are in flight while the slot lists are still being read.
     const int G = gridDim.x, b = blockIdx.x;
-    const int tiles = a.R / RPI, tiles_sh = a.n_shared ? a.R_sh / RPI : 0;
+    const int tiles = RAGGED ? (a.R + RPI - 1) / RPI : a.R / RPI;
+    const int tiles_sh = !a.n_shared ? 0 : RAGGED ? (a.R_sh + RPI - 1) / RPI : a.R_sh / RPI;
+    // (bytes of a tile row in LDS, and its 32-wide column blocks, for a panel row of rs bytes)
+    auto lds_row = [](int rs) { return RAGGED ? ((rs + 127) & ~127) + kRowPad : rs + kRowPad; };
+    auto col_blocks = [](int rs) { return RAGGED ? (rs + 63) / 64 : rs / 64; };
     const int n_sh_items = a.n_shared * tiles_sh;
     const int sh_per = udiv_rcp(n_sh_items, G, a.rcp_G), sh_rem = n_sh_items - sh_per * G;
     // (FUSED: workgroup 0 also writes the step outputs and waits for every workgroup's word before it gives the
@@ -151,26 +161,36 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     int pK2 = 0, prs = 0, pnpan = 1, ppan = 0;            // row stride, panel row bytes, panels, panel
     int pp = 0, pe = 0, prt = 0;                          // item of the run, expert within class, row tile
     bool psh = false, pvalid = false;
+    int ppoff = 0, ppc = 0;                               // RAGGED: the panel's first byte in a row, pieces of a tile
     auto prod_set = [&](bool sh, int e, int rt) {
         psh = sh; pe = e; prt = rt; ppan = 0;
+        if (RAGGED) ppoff = 0;
         if (sh) {
             const int K = a.K_sh;
             const size_t eoff = ((size_t)e * a.R_sh + (size_t)rt * RPI) * K;
             pw0 = (const unsigned char *)(a.s0 + eoff);
             pw1 = GATEUP ? (const unsigned char *)(a.s1 + eoff) : pw0 + (size_t)16 * K;
+            if (RAGGED && !GATEUP && rt * 16 + 8 >= a.R_sh) pw1 = pw0;   // (the last tile has 8 rows)
             pK2 = 2 * K; prs = 2 * a.KP_sh; pnpan = a.np_sh;
         } else {
             const int K = a.K;
             const size_t eoff = ((size_t)active_s[e] * a.R + (size_t)rt * RPI) * K;
             pw0 = (const unsigned char *)(a.w0 + eoff);
             pw1 = GATEUP ? (const unsigned char *)(a.w1 + eoff) : pw0 + (size_t)16 * K;
+            if (RAGGED && !GATEUP && rt * 16 + 8 >= a.R) pw1 = pw0;
             pK2 = 2 * K; prs = 2 * a.KP; pnpan = a.np;
         }
+        if (RAGGED) ppc = (prs + 127) / 128 * 2;
     };
     auto prod_advance = [&]() {
         if (!pvalid) return;
-        if (ppan + 1 < pnpan) { ++ppan; return; }
+        if (ppan + 1 < pnpan) {
+            ++ppan;
+            if (RAGGED) ppoff = ppan + 1 == pnpan ? pK2 - prs : ppoff + prs;
+            return;
+        }
         ppan = 0;
+        if (RAGGED) ppoff = 0;
         ++pp;
         if (pp >= cnt) {            // end of the run: stay on a few cached kilobytes from now on
             pvalid = false;
@@ -185,6 +205,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
             ++prt;
             pw0 += (size_t)RPI * pK2;
             pw1 += (size_t)RPI * pK2;
+            if (RAGGED && !GATEUP && prt * 16 + 8 >= (psh ? a.R_sh : a.R)) pw1 = pw0;
         }
     };
 
@@ -239,7 +260,19 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     unsigned goff[2][PACKED ? 1 : NPI];   // PACKED: unused
     int loff[2][LEAN ? 1 : NPI];          // PACKED: row << 16 | column; LEAN: unused
     int st_rs[2] = {-1, -1}, st_K2[2] = {-1, -1};
+    // piece i of this wavefront in a tile of rs-byte rows: which half (uniform), and row << 16 | column of this lane
+    auto rgeom = [&](int i, int rs) {
+        const int ph = (rs + 127) / 128;   // pieces per half
+        int pc = i * kWaves + w;
+        pc = pc < 2 * ph ? pc : 2 * ph - 1;
+        const bool upper = pc >= ph;
+        int off = ((upper ? pc - ph : pc) << 10) + (lane << 4);
+        off = off < 8 * rs ? off : 8 * rs - 16;
+        const int row = (int)(((float)(off >> 4) + 0.5f) * (16.0f / (float)rs));
+        return (row + (upper ? 8 : 0)) << 16 | (off - row * rs);
+    };
     auto geom = [&](int i, int rs) {      // row << 16 | column of piece i in a tile of rs-byte rows
+        if (RAGGED) return rgeom(i, rs);
         const int np = rs / 64;
         int pc = i * kWaves + w;
         pc = pc < np ? pc : np - 1;
@@ -262,21 +295,26 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
                 int off = (pc << 10) + (lane << 4);
                 int row = (int)(((float)(off >> 4) + 0.5f) * inv_d);
                 int col = off - row * prs;
+                if (RAGGED) {
+                    const int rc = rgeom(i, prs);
+                    row = rc >> 16;
+                    col = rc & 0xffff;
+                }
                 if (PACKED) {
                     loff[s][LEAN ? 0 : i] = row << 16 | col;
                 } else {
                     goff[s][i] = (unsigned)((row & 7) * pK2 + col);
-                    loff[s][i] = row * (prs + kRowPad) + col;
+                    loff[s][i] = row * lds_row(prs) + col;
                 }
             }
         }
-        const unsigned poff = (unsigned)ppan * (unsigned)prs;
-        const int np = prs / 64;
+        const unsigned poff = RAGGED ? (unsigned)ppoff : (unsigned)ppan * (unsigned)prs;
+        const int np = RAGGED ? ppc : prs / 64;
 #pragma unroll
         for (int i = 0; i < NPI; ++i) {
             int pc = i * kWaves + w;
             pc = pc < np ? pc : np - 1;
-            const unsigned char *base = (pc << 10) < 8 * prs ? pw0 : pw1;   // uniform
+            const unsigned char *base = (RAGGED ? 2 * pc < np : (pc << 10) < 8 * prs) ? pw0 : pw1;   // uniform
             const int rc = LEAN ? geom(i, prs) : loff[s][LEAN ? 0 : i];
             const unsigned go = PACKED ? (unsigned)(((rc >> 16) & 7) * pK2 + (rc & 0xffff)) : goff[s][PACKED ? 0 : i];
             st[s][i] = ld_stream(base + (poff + go));
@@ -287,7 +325,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
 #pragma unroll
         for (int i = 0; i < NPI; ++i) {
             const int rc = LEAN ? geom(i, st_rs[s]) : loff[s][LEAN ? 0 : i];
-            const int lo = PACKED ? (rc >> 16) * (st_rs[s] + kRowPad) + (rc & 0xffff) : rc;
+            const int lo = PACKED ? (rc >> 16) * lds_row(st_rs[s]) + (rc & 0xffff) : rc;
             *(u32x4 *)(tile_s + lo) = st[s][i];
         }
     };
@@ -299,7 +337,9 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     // token tok0 + 16*gr + n sits on column n of group gr.  Drains every load in flight (rare path), unless
     // told to leave the wait to the caller.
     auto load_bx = [&](int tok0, bool wait = true) {
-        const int nkb = c_rs / 64;
+        const int nkb = col_blocks(c_rs);
+        const int cstart = RAGGED && cpan > 0 && cpan + 1 == cnpan ? cK - c_rs / 2 : cpan * (c_rs / 2);   // the panel's first column
+        const int clo = cpan * (c_rs / 2) - cstart;   // RAGGED: columns of the panel that the panel before had
         const uint16_t *bbase = a.bsrc;
         if (!GATEUP && csh) bbase = a.bsrc_sh;
 #pragma unroll
@@ -307,12 +347,15 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
             const int tk = tok0 + 16 * gr + n;
             int boff = -1;
             if (tk < (ALLTOK ? a.T : cm))
-                boff = (cbrow0 >= 0 ? cbrow0 + tk : perm_s[corow0 + tk]) * cK + cpan * (c_rs / 2);
+                boff = (cbrow0 >= 0 ? cbrow0 + tk : perm_s[corow0 + tk]) * cK + cstart;
 #pragma unroll
             for (int j = 0; j < kPieces; ++j) {
                 int kb = w + kWaves * j;
                 bx[gr][j] = (u32x4){0u, 0u, 0u, 0u};
-                if (kb < nkb && boff >= 0) bx[gr][j] = *(const u32x4 *)(bbase + (unsigned)(boff + kb * 32 + g * 8));
+                const int col = kb * 32 + g * 8;
+                const bool in = RAGGED ? (unsigned)(col - clo) < (unsigned)(c_rs / 2 - clo) : kb < nkb;
+                if (RAGGED ? (int)in & (int)(boff >= 0) : in && boff >= 0)
+                    bx[gr][j] = *(const u32x4 *)(bbase + (unsigned)(boff + col));
             }
         }
         if (wait) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
@@ -479,17 +522,18 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         cnt = per + (rk < rem ? 1 : 0);
         r_start = rk * per + (rk < rem ? rk : rem) - s_start;
     } else {
-        // Workgroup x starts at routed item max(0, x * total tiles / G - tiles of the shared items
-        // before x) / panels per routed item: that never decreases with x, is 0 for x = 0 and the
-        // number of routed items for x = G.
+        // Workgroup x starts at routed item max(0, (its equal share of the tiles before it) - tiles of the shared
+        // items before x) / panels per routed item: that never decreases with x, is 0 for x = 0 and the
+        // number of routed items for x = G.  (In 32 bits with reciprocals from the host: four 64-bit divisions took
+        // about 1 us of a launch.  A layer whose weights fit the device has far fewer than 2^31 tiles.)
         const int np_r = a.np, np_sh = a.np_sh;
         const int n_routed = n_act * tiles;
-        const long long total = (long long)n_sh_items * np_sh + (long long)n_routed * np_r;
+        const int total = n_sh_items * np_sh + n_routed * np_r;
+        const int per = udiv_rcp(total, G, a.rcp_G), rem = total - per * G;
         auto routed_before = [&](int x) {
-            const long long sh = (long long)(x * sh_per + (x < sh_rem ? x : sh_rem)) * np_sh;
-            const long long rt = (long long)x * total / G - sh;
-            const long long r = rt > 0 ? rt / np_r : 0;
-            return (int)(r < n_routed ? r : n_routed);
+            const int rt = x * per + (x < rem ? x : rem) - (x * sh_per + (x < sh_rem ? x : sh_rem)) * np_sh;
+            const int r = rt > 0 ? udiv_rcp(rt, np_r, a.rcp_np) : 0;
+            return r < n_routed ? r : n_routed;
         };
         r_start = routed_before(b);
         cnt = s_cnt + routed_before(b + 1) - r_start;
@@ -578,12 +622,35 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     int orec = 0, flushed = 0;   // output records written to / flushed from the LDS output buffer
 
     auto multiply = [&]() {
-        const int nkb = c_rs / 64;
+        const int nkb = c_rs / 64, row_bytes = lds_row(c_rs);
+        if (RAGGED) {
+            // All column blocks, without a branch: what lies in a column without a weight (the next row, the results
+            // of other tiles; an infinity for all we know) becomes zero, like the B operand there.
+            const int clo = cpan > 0 && cpan + 1 == cnpan ? cnpan * (c_rs / 2) - cK : 0;
+            const unsigned width = (unsigned)(c_rs / 2 - clo);
+            const unsigned char *arow = tile_s + n * row_bytes + g * 16 + w * 64;
+            const int col0 = w * 32 + g * 8 - clo;
+            constexpr int AHEAD = NPI < 4 ? NPI : 2;   // (reads in flight: what the registers allow)
+            u32x4 av[NPI];
+#pragma unroll
+            for (int j = 0; j < AHEAD; ++j) av[j] = *(const u32x4 *)(arow + j * (kWaves * 64));
+#pragma unroll
+            for (int j = 0; j < NPI; ++j) {
+                const bool in = (unsigned)(col0 + j * (kWaves * 32)) < width;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) av[j][q] = in ? av[j][q] : 0u;
+#pragma unroll
+                for (int gr = 0; gr < NG; ++gr) acc[gr] = mfma(av[j], bx[gr][j], acc[gr]);
+                if (j + AHEAD < NPI) av[j + AHEAD] = *(const u32x4 *)(arow + (j + AHEAD) * (kWaves * 64));
+                __builtin_amdgcn_sched_barrier(0x6);   // (keep the reads of later blocks behind: vector and scalar arithmetic may cross)
+            }
+            return;
+        }
 #pragma unroll
         for (int j = 0; j < kPieces; ++j) {
             int kb = w + kWaves * j;
             if (kb < nkb) {
-                u32x4 av = *(const u32x4 *)(tile_s + n * (c_rs + kRowPad) + kb * 64 + g * 16);
+                u32x4 av = *(const u32x4 *)(tile_s + n * row_bytes + kb * 64 + g * 16);
 #pragma unroll
                 for (int gr = 0; gr < NG; ++gr) acc[gr] = mfma(av, bx[gr][j], acc[gr]);
             }
@@ -601,7 +668,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
             for (int i = lane; i < NG * kOutPerItem; i += kWave) {
                 const int gr = i / kOutPerItem, q = i - gr * kOutPerItem;
                 const int tok = d[4] + 16 * gr + ((q >> 2) & 15), row = 4 * (q >> 6) + (q & 3);
-                if (tok < d[3]) {
+                if (tok < d[3] && (!RAGGED || GATEUP || d[2] / OB + row < a.R)) {
                     int src = i;
                     if (ALLTOK && !d[0]) {   // entry `tok` of the expert's list: its token's column
                         const int t = perm_s[d[1] + tok];
@@ -746,20 +813,20 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
 #endif
 }
 
-template <bool GATEUP, int NPI, int MODE, bool JOIN, bool WSPLIT = false>
+template <bool GATEUP, int NPI, int MODE, bool JOIN, bool WSPLIT = false, bool RAGGED = false>
 __global__ __launch_bounds__(kThreads) void stream_kernel(StreamArgs a, int tile_lds_bytes, JoinArgs jn)
 {
     const RouteArgs none = {};
-    stream_body<GATEUP, NPI, MODE, JOIN, WSPLIT, false>(a, tile_lds_bytes, jn, none);
+    stream_body<GATEUP, NPI, MODE, JOIN, WSPLIT, false, RAGGED>(a, tile_lds_bytes, jn, none);
 }
 
 // The small-batch gate/up kernel with steps 1-3 of the layer in front of it (one launch less per layer, and the
 // shared experts' weights stream while the routing runs).
-template <int NPI, int MODE>
+template <int NPI, int MODE, bool RAGGED = false>
 __global__ __launch_bounds__(kThreads) void routed_stream_kernel(StreamArgs a, int tile_lds_bytes, RouteArgs ra)
 {
     const JoinArgs none = {};
-    stream_body<true, NPI, MODE, false, false, true>(a, tile_lds_bytes, none, ra);
+    stream_body<true, NPI, MODE, false, false, true, RAGGED>(a, tile_lds_bytes, none, ra);
 }
 
 // out[t,:] (+)= sum_j w[t,j] * o[pos[t,j],:] + sum_i o_sh[i,t,:], in a fixed order
@@ -807,10 +874,20 @@ int stream_panel_width(int K)
 {
     // equal panels, each a multiple of 64 columns (128 bytes: a tile's 1 KB pieces must not straddle the middle of
     // the tile, as for whole rows) and at most kPanelMax columns wide
-    if (K < 64) return 0;
+    if (K < 64 || K % 64 != 0) return 0;
     for (int np = (K + kPanelMax - 1) / kPanelMax; np <= K / 64; ++np)
         if (K % np == 0 && (K / np) % 64 == 0) return K / np;
     return 0;
+}
+
+int stream_panel(int K)
+{
+    // A step of the kernels costs about the same whatever its panel's width, so a K whose only equal split is into
+    // many narrow panels (K = 64 times a prime: 64 columns each) is split like a ragged one.
+    const int equal = stream_panel_width(K);
+    const int np = (K + kPanelMax - 1) / kPanelMax;
+    if (equal > 0 && K / equal <= np + np / 2 + 1) return equal;
+    return ((K + np - 1) / np + 7) / 8 * 8;
 }
 
 bool stream_can_join(const StreamArgs &d)
@@ -819,7 +896,7 @@ bool stream_can_join(const StreamArgs &d)
     // and read back at 128 tokens, H = 2048).  Measured per layer against the separate launch, with the
     // entries of a strip requested eight per thread at a time: no difference at 33 and 64 tokens, 4.6 us
     // more at 128 (and that batched form cost the small batches 0.4-1 us).  The strip's entries fit the tile buffer.
-    const size_t tile = (size_t)16 * (2 * (d.KP > d.KP_sh ? d.KP : d.KP_sh) + kRowPad);
+    const size_t tile = stream_tile_lds(d.KP > d.KP_sh ? d.KP : d.KP_sh);
     return d.T <= 32 && d.R % 8 == 0 && (size_t)d.T * 8 * (d.k + d.n_shared) * 4 <= tile;
 }
 
@@ -828,13 +905,23 @@ namespace {
 void fill_derived(StreamArgs &x, bool gateup, int grid)
 {
     const int rpi = gateup ? 8 : 16;
-    x.np = x.KP > 0 ? x.K / x.KP : 1;
-    x.np_sh = x.n_shared > 0 && x.KP_sh > 0 ? x.K_sh / x.KP_sh : 1;
+    x.np = x.KP > 0 ? (x.K + x.KP - 1) / x.KP : 1;
+    x.np_sh = x.n_shared > 0 && x.KP_sh > 0 ? (x.K_sh + x.KP_sh - 1) / x.KP_sh : 1;
     x.rcp_G = rcp32((unsigned)grid);
-    x.rcp_tiles = rcp32((unsigned)(x.R / rpi));
-    x.rcp_tiles_sh = rcp32((unsigned)(x.n_shared > 0 ? x.R_sh / rpi : 1));
+    x.rcp_tiles = rcp32((unsigned)((x.R + rpi - 1) / rpi));
+    x.rcp_tiles_sh = rcp32((unsigned)(x.n_shared > 0 ? (x.R_sh + rpi - 1) / rpi : 1));
+    x.rcp_np = rcp32((unsigned)x.np);
     x.rcp_k = rcp32((unsigned)x.k);
     x.rcp_S = rcp32((unsigned)(x.k + x.n_shared));
+}
+// Does the launch need the RAGGED instances?  (On widths that both can take those measured 2 to 12 % slower per layer,
+// from the masks and the longer index arithmetic: 64 experts T = 9 70.6 against 66.9 us, T = 17 127.8 against 125.1,
+// H = 4096 with F = 14336 400 against 358 us.  So widths of whole 64s keep instances of their own.)
+bool stream_ragged(const StreamArgs &x, bool gateup)
+{
+    auto odd = [](int K, int KP) { return K % 64 != 0 || KP % 64 != 0 || K % KP != 0; };
+    return odd(x.K, x.KP) || (x.n_shared > 0 && odd(x.K_sh, x.KP_sh)) ||
+           (!gateup && (x.R % 16 != 0 || (x.n_shared > 0 && x.R_sh % 16 != 0)));
 }
 }  // namespace
 
@@ -842,10 +929,10 @@ hipError_t launch_stream(const StreamArgs &a, bool gateup, const JoinArgs *join,
 {
     if (join && (gateup || !stream_can_join(a))) return hipErrorInvalidValue;
     const int kp_max = a.KP > a.KP_sh ? a.KP : a.KP_sh;
-    const size_t tile = (size_t)16 * (2 * kp_max + kRowPad);
+    const size_t tile = stream_tile_lds(kp_max);
     const size_t lds = stream_lds_need(kp_max, a.T, a.k, a.C, gateup);
     if (lds > (size_t)kLdsBytes) return hipErrorInvalidValue;
-    const int npi = (kp_max / 32 + kWaves - 1) / kWaves;   // 1..4 pieces per wavefront and tile
+    const int npi = ((kp_max + 63) / 64 * 2 + kWaves - 1) / kWaves;   // 1..4 pieces per wavefront and tile
     const int mode = a.T > 32 ? 2 : a.T > 16 ? 1 : 0;
 #define MOE_STREAM_FN(GU, N)                                                                     \
     {(const void *)stream_kernel<GU, N, 0, false>, (const void *)stream_kernel<GU, N, 1, false>, \
@@ -871,6 +958,18 @@ hipError_t launch_stream(const StreamArgs &a, bool gateup, const JoinArgs *join,
     const bool wsplit = !gateup && a.n_shared > 0 && a.KP_sh > 0 && a.K_sh / a.KP_sh != a.K / a.KP;
     const void *fn = join ? join_fns[npi - 1][mode] : fns[gateup ? 1 : 0][npi - 1][mode];
     if (wsplit) fn = join ? wsplit_join_fns[npi - 1][mode] : wsplit_fns[npi - 1][mode];
+    if (stream_ragged(a, gateup)) {
+        // (runs of equal numbers of tiles for every down kernel: fewer instances)
+        if (a.T > 32) return hipErrorInvalidValue;
+#define MOE_RAGGED_FN(GU, N, J) \
+    {(const void *)stream_kernel<GU, N, 0, J, !GU, true>, (const void *)stream_kernel<GU, N, 1, J, !GU, true>}
+#define MOE_RAGGED_FNS(GU, J) {MOE_RAGGED_FN(GU, 1, J), MOE_RAGGED_FN(GU, 2, J), MOE_RAGGED_FN(GU, 3, J), MOE_RAGGED_FN(GU, 4, J)}
+        static const void *const ragged_fns[3][4][2] = {MOE_RAGGED_FNS(true, false), MOE_RAGGED_FNS(false, false),
+                                                        MOE_RAGGED_FNS(false, true)};
+#undef MOE_RAGGED_FN
+#undef MOE_RAGGED_FNS
+        fn = ragged_fns[gateup ? 0 : join ? 2 : 1][npi - 1][mode];
+    }
     hipError_t e = allow_full_lds(fn);
     if (e != hipSuccess) return e;
     const int grid = device_cus(&e);
@@ -890,18 +989,23 @@ hipError_t launch_stream_routed(const StreamArgs &a, const RouteArgs &r, hipStre
 {
     if (!r.lists_pub || a.T > 32) return hipErrorInvalidValue;
     const int kp_max = a.KP > a.KP_sh ? a.KP : a.KP_sh;
-    const size_t tile = (size_t)16 * (2 * kp_max + kRowPad);
+    const size_t tile = stream_tile_lds(kp_max);
     size_t lds = stream_lds_need(kp_max, a.T, a.k, a.C, true);
     const size_t lds_route = post_lds_bytes(r.E, r.C, r.T * r.k, true);
     lds = lds > lds_route ? lds : lds_route;
     if (lds > (size_t)kLdsBytes) return hipErrorInvalidValue;
-    const int npi = (kp_max / 32 + kWaves - 1) / kWaves;
+    const int npi = ((kp_max + 63) / 64 * 2 + kWaves - 1) / kWaves;
     static const void *const fns[2][4] = {
         {(const void *)routed_stream_kernel<1, 0>, (const void *)routed_stream_kernel<2, 0>,
          (const void *)routed_stream_kernel<3, 0>, (const void *)routed_stream_kernel<4, 0>},
         {(const void *)routed_stream_kernel<1, 1>, (const void *)routed_stream_kernel<2, 1>,
          (const void *)routed_stream_kernel<3, 1>, (const void *)routed_stream_kernel<4, 1>}};
-    const void *fn = fns[a.T > 16 ? 1 : 0][npi - 1];
+    static const void *const ragged_fns[2][4] = {
+        {(const void *)routed_stream_kernel<1, 0, true>, (const void *)routed_stream_kernel<2, 0, true>,
+         (const void *)routed_stream_kernel<3, 0, true>, (const void *)routed_stream_kernel<4, 0, true>},
+        {(const void *)routed_stream_kernel<1, 1, true>, (const void *)routed_stream_kernel<2, 1, true>,
+         (const void *)routed_stream_kernel<3, 1, true>, (const void *)routed_stream_kernel<4, 1, true>}};
+    const void *fn = (stream_ragged(a, true) ? ragged_fns : fns)[a.T > 16 ? 1 : 0][npi - 1];
     hipError_t e = allow_full_lds(fn);
     if (e != hipSuccess) return e;
     const int grid = device_cus(&e);
