@@ -323,7 +323,7 @@ extern "C" int moe_slot_resolve(const int32_t *topk_idx, const int32_t *slot_tab
                                   (int32_t *)(ws + w.slot_count), (int32_t *)(ws + w.slot_offset),
                                   (int32_t *)(ws + w.perm), (int32_t *)(ws + w.pos),
                                   (int32_t *)(ws + w.active), (unsigned *)(ws + w.ctrl) + kCtrlNActive,
-                                  (hipStream_t)stream);
+                                  (unsigned *)(ws + w.ctrl) + kCtrlMaxTokens, (hipStream_t)stream);
     return e == hipSuccess ? MOE_OK : launch_failed(e);
 }
 
@@ -336,7 +336,8 @@ namespace {
 int run_ffn(const void *hidden, const float *topk_w, const void *w_gate, const void *w_up, const void *w_down,
             const void *sh_gate, const void *sh_up, const void *sh_down, int T, int H, int F, int k, int C,
             int n_shared, int F_shared, const WsLayout &w, char *ws, void *out, int out_bf16, int accumulate,
-            hipStream_t s, const RouteArgs *routing = nullptr, bool one_launch = false, int32_t *miss_count = nullptr)
+            hipStream_t s, bool wide, const RouteArgs *routing = nullptr, bool one_launch = false,
+            int32_t *miss_count = nullptr)
 {
     // (the caller's routing / list kernel has given this call its number in the control block)
     int32_t *slot_count = (int32_t *)(ws + w.slot_count), *slot_offset = (int32_t *)(ws + w.slot_offset);
@@ -377,11 +378,12 @@ int run_ffn(const void *hidden, const float *topk_w, const void *w_gate, const v
         g.slot_count = slot_count; g.slot_offset = slot_offset; g.perm = perm;
         g.active_slots = (const int32_t *)(ws + w.active);
         g.n_active = (const unsigned *)(ws + w.ctrl) + kCtrlNActive;
+        g.max_tokens = (const unsigned *)(ws + w.ctrl) + kCtrlMaxTokens;
         g.T = T; g.k = k; g.C = C;
         g.R = F; g.K = H; g.R_sh = F_shared; g.K_sh = H; g.n_shared = n_shared;
         g.KP = g.KP_sh = panel(H);
         // (routing != null: the gate/up launch does the routing steps itself)
-        e = routing ? launch_stream_routed(g, *routing, s) : launch_stream(g, true, nullptr, s);
+        e = routing ? launch_stream_routed(g, *routing, s) : wide ? launch_wide(g, true, s) : launch_stream(g, true, nullptr, s);
         if (e != hipSuccess) return launch_failed(e);
         StreamArgs d = g;
         d.w0 = (const uint16_t *)w_down; d.w1 = nullptr;
@@ -390,7 +392,7 @@ int run_ffn(const void *hidden, const float *topk_w, const void *w_gate, const v
         d.out = ws + w.o; d.out_sh = ws + w.o_sh;
         d.R = H; d.K = F; d.R_sh = H; d.K_sh = F_shared;
         d.KP = panel(F); d.KP_sh = n_shared ? panel(F_shared) : 0;
-        if (stream_can_join(d)) {
+        if (!wide && stream_can_join(d)) {
             // small batch: the down kernel also sums the per-assignment outputs into `out`
             JoinArgs j = {};
             j.topk_w = topk_w; j.pos = pos; j.out = out;
@@ -401,7 +403,7 @@ int run_ffn(const void *hidden, const float *topk_w, const void *w_gate, const v
             e = launch_stream(d, false, &j, s);
             return e == hipSuccess ? MOE_OK : launch_failed(e);
         }
-        e = launch_stream(d, false, nullptr, s);
+        e = wide ? launch_wide(d, false, s) : launch_stream(d, false, nullptr, s);
         if (e != hipSuccess) return launch_failed(e);
         e = launch_combine_rows(c, (const float *)(ws + w.o), (const float *)(ws + w.o_sh), s);
         return e == hipSuccess ? MOE_OK : launch_failed(e);
@@ -442,10 +444,11 @@ extern "C" int moe_grouped_ffn(const void *hidden, const float *topk_w, const in
                                            (int32_t *)(ws + w.slot_offset), (int32_t *)(ws + w.perm),
                                            (int32_t *)(ws + w.pos), (int32_t *)(ws + w.active),
                                            (unsigned *)(ws + w.ctrl) + kCtrlNActive,
+                                           (unsigned *)(ws + w.ctrl) + kCtrlMaxTokens,
                                            (unsigned *)(ws + w.ctrl) + kCtrlEpoch, s);
     if (e != hipSuccess) return launch_failed(e);
     return run_ffn(hidden, topk_w, w_gate, w_up, w_down, nullptr, nullptr, nullptr, T, H, F, k, C, 0, 0, w, ws,
-                   out, out_bf16, accumulate, s);
+                   out, out_bf16, accumulate, s, w.wide);
 }
 
 namespace {
@@ -496,6 +499,7 @@ int run_layer(const moe_shape_t *sh, const void *hidden, const float *router_w, 
     r.slot_count = (int32_t *)(ws + w.slot_count); r.slot_offset = (int32_t *)(ws + w.slot_offset);
     r.perm = (int32_t *)(ws + w.perm); r.pos = (int32_t *)(ws + w.pos);
     r.active_slots = (int32_t *)(ws + w.active); r.n_active = (unsigned *)(ws + w.ctrl) + kCtrlNActive;
+    r.max_tokens = (unsigned *)(ws + w.ctrl) + kCtrlMaxTokens;
     // The launch forms (moe_shape_t::launch_form): three launches (routing kernel, gate/up stream, down stream with
     // the final sum), two (routing steps at the head of the gate/up kernel), one (routing, gate/up, down and the
     // final sum in one kernel: batches of up to 16 tokens), or the routing kernel followed by the one-launch FFN.
@@ -504,7 +508,9 @@ int run_layer(const moe_shape_t *sh, const void *hidden, const float *router_w, 
     const bool can_route_inside = w.lists_pub != 0;
     int form = sh->launch_form;
     // (the library's choice: routing inside the gate/up launch where the shape allows, one launch less per layer)
-    if (form == MOE_LAUNCH_AUTO) form = can_route_inside ? MOE_LAUNCH_TWO : MOE_LAUNCH_THREE;
+    // (the kernels of larger batches start behind the routing kernel; up to 32 tokens a named form is the streaming kernels')
+    const bool wide = w.wide && (sh->T > 32 || form == MOE_LAUNCH_AUTO);
+    if (form == MOE_LAUNCH_AUTO) form = can_route_inside && !wide ? MOE_LAUNCH_TWO : MOE_LAUNCH_THREE;
     if (form == MOE_LAUNCH_ONE && !(can_layer && can_route_inside)) return MOE_ERR_SHAPE;
     if (form == MOE_LAUNCH_ROUTE_PLUS_ONE && !can_layer) return MOE_ERR_SHAPE;
     if (form == MOE_LAUNCH_TWO && !can_route_inside) return MOE_ERR_SHAPE;
@@ -513,13 +519,13 @@ int run_layer(const moe_shape_t *sh, const void *hidden, const float *router_w, 
     if (form == MOE_LAUNCH_ONE || form == MOE_LAUNCH_TWO) {
         r.lists_pub = (unsigned long long *)(ws + w.lists_pub);
         return run_ffn(hidden, topk_w, w_gate, w_up, w_down, shared_gate, shared_up, shared_down, sh->T, sh->H,
-                       sh->F, sh->k, sh->C, n_sh, F_sh, w, ws, out, out_bf16, accumulate, s, &r,
+                       sh->F, sh->k, sh->C, n_sh, F_sh, w, ws, out, out_bf16, accumulate, s, false, &r,
                        form == MOE_LAUNCH_ONE, miss_count);
     }
     hipError_t e = launch_route(r, s);
     if (e != hipSuccess) return launch_failed(e);
     return run_ffn(hidden, topk_w, w_gate, w_up, w_down, shared_gate, shared_up, shared_down, sh->T, sh->H,
-                   sh->F, sh->k, sh->C, n_sh, F_sh, w, ws, out, out_bf16, accumulate, s, nullptr,
+                   sh->F, sh->k, sh->C, n_sh, F_sh, w, ws, out, out_bf16, accumulate, s, wide, nullptr,
                    form == MOE_LAUNCH_ROUTE_PLUS_ONE, miss_count);
 }
 
@@ -581,11 +587,13 @@ extern "C" int moe_verify_layer_static(const moe_shape_t *sh, const void *hidden
                               shared_down, topk_idx, topk_w, hist, slot_idx, miss_list, miss_count, out);
     if (rc) return rc;
     const int F_sh = sh->n_shared ? sh->F_shared : 0;
+    // Which shapes fit is decided by one layout each: widths of whole 64s by their own kernels' (panels that fit, see
+    // use_stream64), every other shape by the general kernel's, which also runs it if its faster kernels need more.
+    const bool by_general = !use_stream64(sh->T, sh->k, sh->C, sh->H, sh->F, sh->n_shared, F_sh);
+    const WsLayout fit = ws_layout(sh->T, sh->E, sh->k, sh->C, sh->H, sh->F, sh->n_shared, sh->F_shared, by_general);
+    if (fit.total > kScratchBytes) return MOE_ERR_SCRATCH;
     WsLayout w = ws_layout(sh->T, sh->E, sh->k, sh->C, sh->H, sh->F, sh->n_shared, sh->F_shared);
-    // (ragged widths: the general kernel needs less scratch memory for some shapes with many experts per token)
-    if (w.total > kScratchBytes && !use_stream64(sh->T, sh->k, sh->C, sh->H, sh->F, sh->n_shared, F_sh))
-        w = ws_layout(sh->T, sh->E, sh->k, sh->C, sh->H, sh->F, sh->n_shared, sh->F_shared, true);
-    if (w.total > kScratchBytes) return MOE_ERR_SCRATCH;
+    if (w.total > kScratchBytes) w = fit;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return launch_failed(e);

@@ -50,8 +50,7 @@ static inline bool use_stream64(int T, int k, int C, int H, int F, int n_shared,
            stream_lds_need(kp_f > kp_s ? kp_f : kp_s, T, k, C, false) <= (size_t)kLdsBytes;
 }
 
-// ... and batches of up to 32 tokens of any width (multiples of 8) in the RAGGED instances.  The rest (wide or ragged
-// matrices with larger batches, very long lists) runs in ffn.hip.
+// ... and batches of up to 32 tokens of any width (multiples of 8) in the RAGGED instances.
 static inline bool use_stream_kernels(int T, int k, int C, int H, int F, int n_shared, int F_shared)
 {
     if (use_stream64(T, k, C, H, F, n_shared, F_shared)) return true;
@@ -59,6 +58,29 @@ static inline bool use_stream_kernels(int T, int k, int C, int H, int F, int n_s
     const int kp_f = stream_panel(F), kp_s = n_shared > 0 ? stream_panel(F_shared) : 0;
     return stream_lds_need(stream_panel(H), T, k, C, true) <= (size_t)kLdsBytes &&
            stream_lds_need(kp_f > kp_s ? kp_f : kp_s, T, k, C, false) <= (size_t)kLdsBytes;
+}
+
+// Larger batches (wide.hip), any width that is a multiple of 8.
+size_t wide_lds_bytes(int T, int k, int C, int n_shared);
+constexpr int kWideTokCap = 6144;   // list entries whose tokens are kept in LDS
+static inline bool use_either_kernel(int T, int k, int C, int H, int F, int n_shared, int F_shared)
+{
+    return T > 32 && n_shared == 0 && (size_t)T * k <= (size_t)kWideTokCap && use_stream64(T, k, C, H, F, n_shared, F_shared) &&
+           wide_lds_bytes(T, k, C, 0) <= (size_t)kLdsBytes;
+}
+static inline bool use_wide_kernels(int T, int k, int C, int H, int F, int n_shared, int F_shared)
+{
+    if (T <= 16 || T > 65535 || H < 8 || F < 8 || H % 8 != 0 || F % 8 != 0 || n_shared > kMaxC ||
+        (n_shared > 0 && (F_shared < 8 || F_shared % 8 != 0)) || wide_lds_bytes(T, k, C, n_shared) > (size_t)kLdsBytes)
+        return false;
+    // Two token groups and rows of several panels: the streaming kernels reload the B operand for every tile (8 experts
+    // of 4096 x 14336: 17 tokens 576 us, 32 tokens 749 us; here 445 and 446).
+    if (T <= 32) return H > kPanelMax || F > kPanelMax;
+    // Single panels: the streaming kernels as long as no expert has more than 32 tokens (64 experts of 2048 x 1408,
+    // 128 tokens: 156 us against 170; 200 tokens 246 against 192; 64 tokens with Zipf-skewed routing 370 against 140).
+    // The kernel decides when it has the counts (either_kernel), except that shared experts always have all T tokens
+    // and that it takes lists of up to kWideTokCap entries.
+    return !use_either_kernel(T, k, C, H, F, n_shared, F_shared);
 }
 
 static inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -94,7 +116,8 @@ constexpr int kTagIdxEntries = 4096;   // (at most as many as the routing kernel
 // Byte offsets of the scratch arrays inside the caller's workspace.
 struct WsLayout {
     size_t ctrl, tagged, tagged_idx, perm, pos, slot_count, slot_offset, active, part, part_sh, act, act_sh, o, o_sh, total;
-    bool stream;        // the streaming kernels' regions (else: those of the general kernel)
+    bool stream;        // the streaming kernels' regions (else: those of the general kernel) ...
+    bool wide;          // ... for the kernels of more than 32 tokens
     size_t lists_pub;   // stamped copies of the per-slot lists (gate/up kernel that does the routing itself), or 0
 };
 
@@ -107,6 +130,7 @@ constexpr int kCtrlEpoch = 3;     // routing calls completed on this workspace (
 constexpr int kCtrlSpin = 4;      // polls before a wait gives up (0 = the built-in bound)
 constexpr int kCtrlSkew = 5;      // added to the call number that producers stamp their entries with (0)
 constexpr int kCtrlLayout = 6;    // hash of the layout the workspace has been used with since it was initialised (0: none yet)
+constexpr int kCtrlMaxTokens = 7; // most tokens that any slot received (written for batches of more than 32 tokens)
 constexpr unsigned kErrWait = 1u, kErrLayout = 2u;   // bits of the error word
 
 // The first kernel of a call: the workspace serves one layout between two initialisations (a region that held
@@ -123,11 +147,13 @@ constexpr int kKindLayer = 9;     // measurement aid: the one-launch layer kerne
 
 static inline int n_slices(int F) { return (F + kSliceF - 1) / kSliceF; }
 
-// general: lay out for the general FFN kernel also where the streaming kernels would take the shape
+// general: lay out for the general FFN kernel also where the other kernels would take the shape
 static inline WsLayout ws_layout(int T, int E, int k, int C, int H, int F, int n_shared, int F_shared, bool general = false)
 {
     WsLayout w;
-    w.stream = !general && use_stream_kernels(T, k, C, H, F, n_shared, F_shared);
+    w.wide = !general && use_wide_kernels(T, k, C, H, F, n_shared, F_shared);
+    w.stream = !general && (w.wide || (T > 32 ? use_either_kernel(T, k, C, H, F, n_shared, F_shared)
+                                              : use_stream_kernels(T, k, C, H, F, n_shared, F_shared)));
     size_t A = (size_t)T * k;
     size_t o = 0;
     w.lists_pub = 0;
@@ -148,11 +174,14 @@ static inline WsLayout ws_layout(int T, int E, int k, int C, int H, int F, int n
         // activations and per-assignment outputs of the streaming kernels
         w.part = w.part_sh = o;
         // (4 bytes per element: the one-launch kernel stores (call number, two bf16 values) entries)
-        w.act = o;     o += align256(A * F * 4);
-        w.act_sh = o;  o += align256((size_t)n_shared * T * F_shared * 4);
+        const bool compact = T > 32 && w.wide && !use_stream64(T, k, C, H, F, n_shared, F_shared);
+        const size_t act_b = compact ? 2 : 4;
+        w.act = o;     o += align256(A * F * act_b);
+        w.act_sh = o;  o += align256((size_t)n_shared * T * F_shared * act_b);
         // (8 bytes per element: small batches store (call number, value) entries, see JoinArgs)
-        w.o = o;       o += align256(A * H * 8);
-        w.o_sh = o;    o += align256((size_t)n_shared * T * H * 8);
+        const size_t o_b = compact ? 4 : 8;
+        w.o = o;       o += align256(A * H * o_b);
+        w.o_sh = o;    o += align256((size_t)n_shared * T * H * o_b);
         if (use_fused_route(T, k, E, C, H, F, n_shared, F_shared)) {
             w.lists_pub = o;
             // (..., one stamped word per workgroup of the launch, and the gate weights, stamped, kListReplicas copies)
@@ -202,6 +231,7 @@ struct RouteArgs {
     int32_t *pos;              // [T*k]
     int32_t *active_slots;     // [C] slots with at least one token, ascending
     unsigned *n_active;        // [1]
+    unsigned *max_tokens;      // [1] most tokens of any slot (batches of more than 32)
     unsigned *error_flag;      // control word set when a bounded wait inside a kernel ran out
     unsigned long long *tagged_logits;   // [T*E] (tag << 32 | value bits)
     unsigned long long *tagged_idx;      // [T*k] (tag << 32 | expert id), batches above 16 tokens
@@ -218,6 +248,7 @@ struct StreamArgs {
     void *out, *out_sh;        // gate/up: act, act_sh (bf16); down: o [A,H], o_sh [n_shared,T,H] (fp32)
     const int32_t *slot_count, *slot_offset, *perm, *active_slots;
     const unsigned *n_active;
+    const unsigned *max_tokens;   // most tokens of any slot (read for batches of more than 32)
     int T, k;
     int R, K, R_sh, K_sh, n_shared, C;
     int KP, KP_sh;             // panel widths (columns parked in LDS at a time)
@@ -293,18 +324,22 @@ hipError_t launch_histogram(const int32_t *topk_idx, int A, int E, int32_t *hist
 hipError_t launch_resolve(const int32_t *topk_idx, const int32_t *slot_table, int A, int E, int C,
                           int32_t *slot_idx, int32_t *miss_list, int32_t *miss_count, int32_t *slot_count,
                           int32_t *slot_offset, int32_t *perm, int32_t *pos, int32_t *active_slots,
-                          unsigned *n_active, hipStream_t s);
+                          unsigned *n_active, unsigned *max_tokens, hipStream_t s);
 // (epoch: control word stepped by one, so that the FFN kernels of this call have a number of their own)
 // (layout: hash of the workspace layout of this call, checked against the one the workspace has served so far)
 hipError_t launch_lists_from_slots(unsigned layout, const int32_t *slot_idx, int A, int C, int32_t *slot_count,
                                    int32_t *slot_offset, int32_t *perm, int32_t *pos, int32_t *active_slots,
-                                   unsigned *n_active, unsigned *epoch, hipStream_t s);
+                                   unsigned *n_active, unsigned *max_tokens, unsigned *epoch, hipStream_t s);
 // join != null (down kernel only, stream_can_join() true): outputs leave as stamped 64-bit entries
 // and the kernel ends with the weighted sum into `out`; no combine launch is needed then
 hipError_t launch_stream(const StreamArgs &a, bool gateup, const JoinArgs *join, hipStream_t s);
 // gate/up kernel that first does the routing steps described by `r` (use_fused_route() true, r.lists_pub set)
 hipError_t launch_stream_routed(const StreamArgs &a, const RouteArgs &r, hipStream_t s);
 bool stream_can_join(const StreamArgs &d);
+// the same two steps for batches of more than 32 tokens (use_wide_kernels() true); no final sum inside
+hipError_t launch_wide(const StreamArgs &a, bool gateup, hipStream_t s);
+// 64 weight rows to an item, or 32 where those would be less than two for every workgroup (if every slot is used)
+bool wide_tall(const StreamArgs &a, bool gateup);
 hipError_t launch_combine_rows(const CombineArgs &a, const float *o, const float *o_sh, hipStream_t s);
 // one-launch form (batches of up to 16 tokens): use_layer_kernel() must hold; route != null: the kernel does
 // the routing steps itself (use_fused_route() true, route->lists_pub set)

@@ -158,7 +158,7 @@ template <typename IdxPtr, typename TabPtr>
 __device__ void block_post(IdxPtr idx, TabPtr slot_table, int A, int E, int C, int32_t *hist,
                            int32_t *slot_idx, int32_t *miss_list, int32_t *miss_count, int32_t *slot_count,
                            int32_t *slot_offset, int32_t *perm, int32_t *pos, int32_t *active_slots,
-                           unsigned *n_active, lds_i32 *hist_s, lds_i32 *cnt_s, lds_i32 *off_s, lds_i32 *scan_s,
+                           unsigned *n_active, unsigned *max_tokens, lds_i32 *hist_s, lds_i32 *cnt_s, lds_i32 *off_s, lds_i32 *scan_s,
                            lds_i32 *sidx_s)
 {
     static_assert(kMaxC <= kRouteThreads && kMaxC <= 1 << 10, "one thread per slot; ten bits of slot id");
@@ -241,7 +241,9 @@ __device__ void block_post(IdxPtr idx, TabPtr slot_table, int A, int E, int C, i
         if (lane >= d) inc_o += v;
     }
     const unsigned long long act = __ballot(cntv > 0);
+    const unsigned most = wave_max_u32((unsigned)cntv);
     if (lane == kWave - 1) {
+        scan_s[w] = (int)most;   // (the misses' counts are no longer needed)
         scan_s[16 + w] = inc_o;
         scan_s[32 + w] = __popcll(act);
     }
@@ -266,6 +268,9 @@ __device__ void block_post(IdxPtr idx, TabPtr slot_table, int A, int E, int C, i
     if (tid == 0) {
         slot_offset[C] = tot_o;
         *n_active = (unsigned)tot_a;
+        int m = 0;
+        for (int i = 0; i < (C + kWave - 1) / kWave; ++i) m = scan_s[i] > m ? scan_s[i] : m;
+        *max_tokens = (unsigned)m;
     }
     __syncthreads();
     // lists: assignment a goes to position off[slot] + (number of earlier assignments of that slot),
@@ -378,9 +383,11 @@ __device__ __forceinline__ SmallLists block_post_small(lds_i32 *idx_s, lds_i32 *
     const int inc_a = __popcll(__ballot(cntv > 0) & upto);
     int inc_o = 0;
     for (int bit = 0; (1 << bit) <= T; ++bit) inc_o += __popcll(__ballot((cntv >> bit) & 1) & upto) << bit;
+    const bool want_most = to_memory && T > 32;   // (uniform)
+    const unsigned most = want_most ? wave_max_u32((unsigned)cntv) : 0u;
     if (lane == kWave - 1) {
         scan_s[16 + w] = inc_o;
-        scan_s[32 + w] = inc_a;
+        scan_s[32 + w] = inc_a | (int)most << 16;
     }
     // (only the wavefronts that hold an assignment or a slot have anything to add)
     const int nwv = ((A > C ? A : C) + kWave - 1) / kWave;
@@ -398,9 +405,10 @@ __device__ __forceinline__ SmallLists block_post_small(lds_i32 *idx_s, lds_i32 *
         }
     }
     __syncthreads();
-    int base_o = 0, base_a = 0, tot_o = 0, tot_a = 0;
+    int base_o = 0, base_a = 0, tot_o = 0, tot_a = 0, tot_m = 0;
     for (int i = 0; i < nwv; ++i) {
-        const int vo = scan_s[16 + i], va = scan_s[32 + i];
+        const int vo = scan_s[16 + i], vm = scan_s[32 + i], va = vm & 0xffff;
+        tot_m = vm >> 16 > tot_m ? vm >> 16 : tot_m;
         if (i < w) {
             base_o += vo;
             base_a += va;
@@ -429,6 +437,7 @@ __device__ __forceinline__ SmallLists block_post_small(lds_i32 *idx_s, lds_i32 *
         if (to_memory) {
             r.slot_offset[C] = tot_o;
             *r.n_active = (unsigned)tot_a;
+            if (want_most) *r.max_tokens = (unsigned)tot_m;
         }
         publish(0, tot_a);
     }

@@ -27,6 +27,7 @@
 // whole one, since its requests wait in the same queues behind everybody's whole tiles.)
 #include "moe_internal.h"
 #include "route_device.h"
+#include "wide_device.h"
 
 namespace moe {
 
@@ -76,8 +77,7 @@ __device__ inline uint32_t f32_to_bf16_rne(float f)
 // the younger tile in flight.  The state of the two walks over the run (the tile to load next,
 // the tile being consumed) lives in plain scalars and is stepped, not recomputed.
 // MODE 0: batches up to 16 tokens (one group of 16 token columns per pass); MODE 1: up to 32 tokens
-// (two groups); MODE 2: larger batches: two groups per pass, and experts with more than 32 tokens
-// take further passes over the parked tile.
+// (two groups); MODE 2: larger batches in which no expert has more than 32 tokens (two groups).
 //
 // JOIN (down kernel, batches of up to 32 tokens): the weighted sum back into token order (Sec. 2.2 last
 // line; the join of App. D when `accumulate` is set) rides at the end of the down kernel instead
@@ -105,7 +105,9 @@ __device__ unsigned long long g_timeline[2][kTimelineGroups][kTimelineWords];
 // pieces are then counted per half (8 rows of rs bytes), the lanes of a half's last piece that lie beyond it re-read
 // its last 16 bytes; the last panel of a row starts early enough to be as wide as the others, and the columns that
 // the panel before had, or that no row has, are zero in both operands; the down kernel's last tile may have 8 rows.
-template <bool GATEUP, int NPI, int MODE, bool JOIN, bool WSPLIT, bool FUSED, bool RAGGED>
+//
+// WIDE_RB (MODE 2): row blocks of the larger-batch kernel that takes over when an expert has more than 32 tokens.
+template <bool GATEUP, int NPI, int MODE, bool JOIN, bool WSPLIT, bool FUSED, bool RAGGED, int WIDE_RB = 0>
 __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_lds_bytes, const JoinArgs &jn,
                                             const RouteArgs &ra)
 {
@@ -114,7 +116,6 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     static_assert(!JOIN || (!GATEUP && MODE < 2), "the join rides on the down kernel of batches up to 32 tokens");
     static_assert(!RAGGED || MODE < 2, "ragged widths of larger batches are another kernel's");
     constexpr int NG = MODE == 0 ? 1 : 2;   // token groups of 16 multiplied per pass
-    constexpr bool MULTIPASS = MODE == 2;
     constexpr int RPI = GATEUP ? 8 : 16;    // output rows per item
     constexpr int OB = GATEUP ? 2 : 4;      // bytes per output element
     constexpr int kOutPerItem = RPI * 16;   // results of one item (rows x token columns)
@@ -129,7 +130,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     int *ctl_s = (int *)(lds + tile_lds_bytes + NG * kWaves * kWave * 16);
     int *count_s = ctl_s, *offset_s = ctl_s + a.C, *active_s = ctl_s + 2 * a.C, *perm_s = ctl_s + 3 * a.C;
     float *out_s = (float *)(perm_s + a.T * a.k);                     // [kOutCap][NG][kOutPerItem] results waiting to be stored
-    int *odesc_s = (int *)(out_s + kOutCap * NG * kOutPerItem);       // [kOutCap][8]: shared?, row of token 0, column bytes, m, first token
+    int *odesc_s = (int *)(out_s + kOutCap * NG * kOutPerItem);       // [kOutCap][8]: shared?, row of token 0, column bytes, m
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
 #ifdef MOE_STREAM_TRACE
@@ -331,12 +332,11 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     };
 
     u32x4 bx[NG][kPieces];
-    int bx_key = -1, bx_panel = -1;   // expert (and panel) whose FIRST token pass the registers hold
+    int bx_key = -1, bx_panel = -1;   // expert (and panel) whose operand the registers hold
 
-    // B operand of this wavefront's column blocks for the token pass starting at token tok0:
-    // token tok0 + 16*gr + n sits on column n of group gr.  Drains every load in flight (rare path), unless
+    // B operand of this wavefront's column blocks: token 16*gr + n sits on column n of group gr.  Drains every load in flight (rare path), unless
     // told to leave the wait to the caller.
-    auto load_bx = [&](int tok0, bool wait = true) {
+    auto load_bx = [&](bool wait = true) {
         const int nkb = col_blocks(c_rs);
         const int cstart = RAGGED && cpan > 0 && cpan + 1 == cnpan ? cK - c_rs / 2 : cpan * (c_rs / 2);   // the panel's first column
         const int clo = cpan * (c_rs / 2) - cstart;   // RAGGED: columns of the panel that the panel before had
@@ -344,7 +344,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         if (!GATEUP && csh) bbase = a.bsrc_sh;
 #pragma unroll
         for (int gr = 0; gr < NG; ++gr) {
-            const int tk = tok0 + 16 * gr + n;
+            const int tk = 16 * gr + n;
             int boff = -1;
             if (tk < (ALLTOK ? a.T : cm))
                 boff = (cbrow0 >= 0 ? cbrow0 + tk : perm_s[corow0 + tk]) * cK + cstart;
@@ -372,7 +372,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         cons_set(true, e, s_start - e * tiles_sh);
         pvalid = true;
         issue(0);
-        load_bx(0, false);
+        load_bx(false);
         bx_key = ckey;
         bx_panel = cpan;
         bx_early = true;
@@ -512,6 +512,14 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         else if (JOIN)
             for (int i = tid; i < a.T * a.k; i += kThreads) perm_s[i] = jn.pos[i];
         n_act = (int)(*a.n_active);
+        if constexpr (MODE == 2) {
+            // (asked for here, with the lists: ahead of them it would be a trip to memory of its own)
+            if (*a.max_tokens > 32u) {
+                __syncthreads();
+                wide::wide_body<GATEUP, true, WIDE_RB>(a);
+                return;
+            }
+        }
         __syncthreads();
     }
 
@@ -667,7 +675,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
 #pragma unroll
             for (int i = lane; i < NG * kOutPerItem; i += kWave) {
                 const int gr = i / kOutPerItem, q = i - gr * kOutPerItem;
-                const int tok = d[4] + 16 * gr + ((q >> 2) & 15), row = 4 * (q >> 6) + (q & 3);
+                const int tok = 16 * gr + ((q >> 2) & 15), row = 4 * (q >> 6) + (q & 3);
                 if (tok < d[3] && (!RAGGED || GATEUP || d[2] / OB + row < a.R)) {
                     int src = i;
                     if (ALLTOK && !d[0]) {   // entry `tok` of the expert's list: its token's column
@@ -705,7 +713,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     // added in wavefront order.  Element q = lane*4 + j of the MFMA result layout is token (q/4)%16,
     // tile row 4*(q/64) + q%4; gate rows are tile rows 0..7 and the up row of the same activation
     // sits 128 elements further on.
-    auto reduce_to_record = [&](int tok0) {
+    auto reduce_to_record = [&]() {
         const int slot = orec % kOutCap;
         if (tid < NG * kOutPerItem) {
             const int gr = tid / kOutPerItem, q = tid - gr * kOutPerItem;
@@ -720,7 +728,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         }
         if (tid == 0) {
             int *d = odesc_s + slot * 8;
-            d[0] = csh ? 1 : 0; d[1] = corow0; d[2] = cocol; d[3] = cm; d[4] = tok0;
+            d[0] = csh ? 1 : 0; d[1] = corow0; d[2] = cocol; d[3] = cm;
         }
         ++orec;
     };
@@ -733,7 +741,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     // ahead in flight, multiply, and on the item's last panel reduce into the output buffer
     auto step = [&](int s) {
         if (bx_key != ckey || bx_panel != cpan) {
-            load_bx(0);
+            load_bx();
             bx_key = ckey;
             bx_panel = cpan;
         }
@@ -750,21 +758,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         if (last_panel) post_partials();
         __syncthreads();   // every wavefront is done with the tile in LDS (and its partial result is posted)
         if (last_panel) {
-            reduce_to_record(0);
-            // more tokens than one pass holds (only reached with a single panel per item): the tile
-            // stays parked while further passes reload the B operand
-            for (int tok0 = 16 * NG; MULTIPASS && tok0 < cm; tok0 += 16 * NG) {
-                if (orec - flushed == kOutCap) { __syncthreads(); flush(); }
-                load_bx(tok0);
-                bx_key = -1;
-#pragma unroll
-                for (int gr = 0; gr < NG; ++gr) acc[gr] = (f32x4){0.f, 0.f, 0.f, 0.f};
-                multiply();
-                __syncthreads();   // the previous pass has been reduced: red_s is free again
-                post_partials();
-                __syncthreads();
-                reduce_to_record(tok0);
-            }
+            reduce_to_record();
         }
         cons_advance();
         if (last_panel && orec - flushed == kOutCap) {
@@ -779,7 +773,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     // the second tile is requested would leave the memory system with one tile per workgroup for the
     // two to three microseconds of that round trip.
     if (!bx_early) {
-        load_bx(0, false);
+        load_bx(false);
         bx_key = ckey;
         bx_panel = cpan;
     }
@@ -818,6 +812,18 @@ __global__ __launch_bounds__(kThreads) void stream_kernel(StreamArgs a, int tile
 {
     const RouteArgs none = {};
     stream_body<GATEUP, NPI, MODE, JOIN, WSPLIT, false, RAGGED>(a, tile_lds_bytes, jn, none);
+}
+
+// Batches of more than 32 tokens with widths of whole 64s in single panels and no shared experts.  If no expert has more
+// than 32 tokens, its whole B operand fits the registers and the weight rows stream past it; otherwise the kernel of
+// larger batches (wide_device.h), which reads the weights once per 32 tokens.  (64 experts of 2048 x 1408: 128 tokens,
+// routed evenly, 156 against 170 us; 64 tokens, Zipf-skewed, with further passes over the parked tile 370 against 140.)
+template <bool GATEUP, int NPI, int RB>
+__global__ __launch_bounds__(kThreads) void either_kernel(StreamArgs a, int tile_lds_bytes)
+{
+    const JoinArgs no_join = {};
+    const RouteArgs no_route = {};
+    stream_body<GATEUP, NPI, 2, false, false, false, false, RB>(a, tile_lds_bytes, no_join, no_route);
 }
 
 // The small-batch gate/up kernel with steps 1-3 of the layer in front of it (one launch less per layer, and the
@@ -925,6 +931,29 @@ bool stream_ragged(const StreamArgs &x, bool gateup)
 }
 }  // namespace
 
+static hipError_t launch_either(const StreamArgs &a, bool gateup, int npi, int tile_lds_bytes, size_t lds, hipStream_t s)
+{
+    if (a.n_shared > 0 || (size_t)a.T * a.k > (size_t)kWideTokCap || stream_ragged(a, gateup) || a.K != a.KP) return hipErrorInvalidValue;
+#define MOE_EITHER_FN(GU, N) {(const void *)either_kernel<GU, N, 2>, (const void *)either_kernel<GU, N, 4>}
+    static const void *const fns[2][4][2] = {
+        {MOE_EITHER_FN(false, 1), MOE_EITHER_FN(false, 2), MOE_EITHER_FN(false, 3), MOE_EITHER_FN(false, 4)},
+        {MOE_EITHER_FN(true, 1), MOE_EITHER_FN(true, 2), MOE_EITHER_FN(true, 3), MOE_EITHER_FN(true, 4)}};
+#undef MOE_EITHER_FN
+    const void *fn = fns[gateup ? 1 : 0][npi - 1][wide_tall(a, gateup) ? 1 : 0];
+    const size_t lds_wide = wide_lds_bytes(a.T, a.k, a.C, 0);
+    lds = lds > lds_wide ? lds : lds_wide;
+    if (lds > (size_t)kLdsBytes) return hipErrorInvalidValue;
+    hipError_t e = allow_full_lds(fn);
+    if (e != hipSuccess) return e;
+    const int grid = device_cus(&e);
+    if (e != hipSuccess) return e;
+    StreamArgs args = a;
+    fill_derived(args, gateup, grid);
+    void *params[] = {&args, &tile_lds_bytes};
+    e = launch_timed(fn, dim3(grid), dim3(kThreads), params, lds, s, gateup ? 2 : 4);
+    return e != hipSuccess ? e : hipGetLastError();
+}
+
 hipError_t launch_stream(const StreamArgs &a, bool gateup, const JoinArgs *join, hipStream_t s)
 {
     if (join && (gateup || !stream_can_join(a))) return hipErrorInvalidValue;
@@ -933,25 +962,22 @@ hipError_t launch_stream(const StreamArgs &a, bool gateup, const JoinArgs *join,
     const size_t lds = stream_lds_need(kp_max, a.T, a.k, a.C, gateup);
     if (lds > (size_t)kLdsBytes) return hipErrorInvalidValue;
     const int npi = ((kp_max + 63) / 64 * 2 + kWaves - 1) / kWaves;   // 1..4 pieces per wavefront and tile
-    const int mode = a.T > 32 ? 2 : a.T > 16 ? 1 : 0;
-#define MOE_STREAM_FN(GU, N)                                                                     \
-    {(const void *)stream_kernel<GU, N, 0, false>, (const void *)stream_kernel<GU, N, 1, false>, \
-     (const void *)stream_kernel<GU, N, 2, false>}
+    if (a.T > 32) return launch_either(a, gateup, npi, (int)tile, lds, s);
+    const int mode = a.T > 16 ? 1 : 0;
+#define MOE_STREAM_FN(GU, N) {(const void *)stream_kernel<GU, N, 0, false>, (const void *)stream_kernel<GU, N, 1, false>}
 #define MOE_JOIN_FN(N) {(const void *)stream_kernel<false, N, 0, true>, (const void *)stream_kernel<false, N, 1, true>}
     static const void *const join_fns[4][2] = {MOE_JOIN_FN(1), MOE_JOIN_FN(2), MOE_JOIN_FN(3), MOE_JOIN_FN(4)};
 #undef MOE_JOIN_FN
     // down kernel, runs of equal numbers of tiles
-#define MOE_WSPLIT_FN(N)                                                                                       \
-    {(const void *)stream_kernel<false, N, 0, false, true>, (const void *)stream_kernel<false, N, 1, false, true>, \
-     (const void *)stream_kernel<false, N, 2, false, true>}
+#define MOE_WSPLIT_FN(N) {(const void *)stream_kernel<false, N, 0, false, true>, (const void *)stream_kernel<false, N, 1, false, true>}
 #define MOE_WSPLIT_JOIN_FN(N) \
     {(const void *)stream_kernel<false, N, 0, true, true>, (const void *)stream_kernel<false, N, 1, true, true>}
-    static const void *const wsplit_fns[4][3] = {MOE_WSPLIT_FN(1), MOE_WSPLIT_FN(2), MOE_WSPLIT_FN(3), MOE_WSPLIT_FN(4)};
+    static const void *const wsplit_fns[4][2] = {MOE_WSPLIT_FN(1), MOE_WSPLIT_FN(2), MOE_WSPLIT_FN(3), MOE_WSPLIT_FN(4)};
     static const void *const wsplit_join_fns[4][2] = {MOE_WSPLIT_JOIN_FN(1), MOE_WSPLIT_JOIN_FN(2), MOE_WSPLIT_JOIN_FN(3),
                                                       MOE_WSPLIT_JOIN_FN(4)};
 #undef MOE_WSPLIT_FN
 #undef MOE_WSPLIT_JOIN_FN
-    static const void *const fns[2][4][3] = {
+    static const void *const fns[2][4][2] = {
         {MOE_STREAM_FN(false, 1), MOE_STREAM_FN(false, 2), MOE_STREAM_FN(false, 3), MOE_STREAM_FN(false, 4)},
         {MOE_STREAM_FN(true, 1), MOE_STREAM_FN(true, 2), MOE_STREAM_FN(true, 3), MOE_STREAM_FN(true, 4)}};
 #undef MOE_STREAM_FN
@@ -960,7 +986,6 @@ hipError_t launch_stream(const StreamArgs &a, bool gateup, const JoinArgs *join,
     if (wsplit) fn = join ? wsplit_join_fns[npi - 1][mode] : wsplit_fns[npi - 1][mode];
     if (stream_ragged(a, gateup)) {
         // (runs of equal numbers of tiles for every down kernel: fewer instances)
-        if (a.T > 32) return hipErrorInvalidValue;
 #define MOE_RAGGED_FN(GU, N, J) \
     {(const void *)stream_kernel<GU, N, 0, J, !GU, true>, (const void *)stream_kernel<GU, N, 1, J, !GU, true>}
 #define MOE_RAGGED_FNS(GU, J) {MOE_RAGGED_FN(GU, 1, J), MOE_RAGGED_FN(GU, 2, J), MOE_RAGGED_FN(GU, 3, J), MOE_RAGGED_FN(GU, 4, J)}
