@@ -227,7 +227,7 @@ extern "C" int moe_workspace_bytes(const moe_shape_t *sh, size_t *bytes_out)
     if (sh->T < 1 || sh->H < 1 || sh->E < 1 || sh->k < 1 || sh->k > sh->E || sh->F < 1 || sh->C < 0 ||
         sh->n_shared < 0 || (sh->n_shared > 0 && sh->F_shared < 1))
         return MOE_ERR_SHAPE;
-    *bytes_out = ws_layout(sh->T, sh->E, sh->k, sh->C, sh->H, sh->F, sh->n_shared, sh->F_shared).total;
+    *bytes_out = ws_bytes(sh->T, sh->E, sh->k, sh->C, sh->H, sh->F, sh->n_shared, sh->F_shared);
     return MOE_OK;
 }
 
@@ -436,8 +436,8 @@ extern "C" int moe_grouped_ffn(const void *hidden, const float *topk_w, const in
         !aligned16(out) || !aligned16(workspace))
         return MOE_ERR_ALIGN;
     // the single-step call has no routing scratch: lay the workspace out with E = 0
-    WsLayout w = ws_layout(T, 0, k, C, H, F, 0, 0);
-    if (workspace_bytes < w.total) return MOE_ERR_WORKSPACE;
+    WsLayout w;
+    if (!ws_choose(T, 0, k, C, H, F, 0, 0, workspace_bytes, w)) return MOE_ERR_WORKSPACE;
     char *ws = (char *)workspace;
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = launch_lists_from_slots(layout_hash(w), slot_idx, T * k, C, (int32_t *)(ws + w.slot_count),
@@ -544,8 +544,8 @@ extern "C" int moe_verify_layer(const moe_shape_t *sh, const void *hidden, const
                               shared_down, topk_idx, topk_w, hist, slot_idx, miss_list, miss_count, out);
     if (rc) return rc;
     if (!aligned16(workspace)) return MOE_ERR_ALIGN;
-    WsLayout w = ws_layout(sh->T, sh->E, sh->k, sh->C, sh->H, sh->F, sh->n_shared, sh->F_shared);
-    if (workspace_bytes < w.total) return MOE_ERR_WORKSPACE;
+    WsLayout w;
+    if (!ws_choose(sh->T, sh->E, sh->k, sh->C, sh->H, sh->F, sh->n_shared, sh->F_shared, workspace_bytes, w)) return MOE_ERR_WORKSPACE;
     return run_layer(sh, hidden, router_w, router_bias, slot_table, w_gate, w_up, w_down, shared_gate, shared_up,
                      shared_down, topk_idx, topk_w, hist, slot_idx, miss_list, miss_count, out, out_bf16,
                      accumulate, w, (char *)workspace, (hipStream_t)stream);
@@ -586,14 +586,8 @@ extern "C" int moe_verify_layer_static(const moe_shape_t *sh, const void *hidden
     int rc = check_layer_args(sh, hidden, router_w, slot_table, w_gate, w_up, w_down, shared_gate, shared_up,
                               shared_down, topk_idx, topk_w, hist, slot_idx, miss_list, miss_count, out);
     if (rc) return rc;
-    const int F_sh = sh->n_shared ? sh->F_shared : 0;
-    // Which shapes fit is decided by one layout each: widths of whole 64s by their own kernels' (panels that fit, see
-    // use_stream64), every other shape by the general kernel's, which also runs it if its faster kernels need more.
-    const bool by_general = !use_stream64(sh->T, sh->k, sh->C, sh->H, sh->F, sh->n_shared, F_sh);
-    const WsLayout fit = ws_layout(sh->T, sh->E, sh->k, sh->C, sh->H, sh->F, sh->n_shared, sh->F_shared, by_general);
-    if (fit.total > kScratchBytes) return MOE_ERR_SCRATCH;
-    WsLayout w = ws_layout(sh->T, sh->E, sh->k, sh->C, sh->H, sh->F, sh->n_shared, sh->F_shared);
-    if (w.total > kScratchBytes) w = fit;
+    WsLayout w;
+    if (!ws_choose(sh->T, sh->E, sh->k, sh->C, sh->H, sh->F, sh->n_shared, sh->F_shared, kScratchBytes, w)) return MOE_ERR_SCRATCH;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return launch_failed(e);

@@ -192,6 +192,26 @@ static inline WsLayout ws_layout(int T, int E, int k, int C, int H, int F, int n
     return w;
 }
 
+// Which workspaces are large enough is decided by one layout for each shape: widths of whole 64s (use_stream64) by their
+// own kernels', every other shape by the general kernel's, which also runs the shape where its faster kernels would need
+// more than `have` bytes.  False: not large enough.
+static inline bool ws_choose(int T, int E, int k, int C, int H, int F, int n_shared, int F_shared, size_t have, WsLayout &w)
+{
+    const WsLayout fit = ws_layout(T, E, k, C, H, F, n_shared, F_shared, !use_stream64(T, k, C, H, F, n_shared, F_shared));
+    if (have < fit.total) return false;
+    w = ws_layout(T, E, k, C, H, F, n_shared, F_shared);
+    if (have < w.total) w = fit;
+    return true;
+}
+
+// ... and what to allocate: enough for the shape's faster kernels too.
+static inline size_t ws_bytes(int T, int E, int k, int C, int H, int F, int n_shared, int F_shared)
+{
+    const size_t fit = ws_layout(T, E, k, C, H, F, n_shared, F_shared, !use_stream64(T, k, C, H, F, n_shared, F_shared)).total;
+    const size_t own = ws_layout(T, E, k, C, H, F, n_shared, F_shared).total;
+    return own > fit ? own : fit;
+}
+
 // Non-zero hash of where the regions of a layout lie: two shapes with the same offsets keep the same kind of
 // entry in every place, and may share a workspace without a new initialisation.
 static inline unsigned layout_hash(const WsLayout &w)

@@ -59,3 +59,24 @@ def test_an_infinite_weight_stays_in_its_own_row(F):
     li.w_down[:, 50, F - 2056 if F > 2048 else 0] = 0x7F80
     out = G.run_layer(G.upload(li)).out.cpu()
     assert torch.equal(out[:, rest], ref[:, rest])
+
+
+def test_static_call_where_only_the_general_layout_fits():
+    """32 tokens x 64 experts each, F = 120: the streaming kernels' regions exceed the library's static array, the general
+    kernel's do not.  The call was always accepted and has to stay so."""
+    import gpu_util as G
+    T, H, F, E, k, C = 32, 1000, 120, 64, 64, 6
+    li = synth.make_layer(synth.small_recipe("static", 91, T=T, H=H, F=F, E=E, k=k, C=C, hidden="unit"), margin=0.0)
+    d = G.upload(li)
+    buf = B.LayerBuffers.allocate(d.shape)
+    print("[case] static, general layout", flush=True)
+    args = (d.hidden, d.router_w, d.router_bias, d.slot_table, d.w_gate, d.w_up, d.w_down, d.sh_gate, d.sh_up, d.sh_down,
+            buf.topk_idx, buf.topk_w, buf.hist, buf.slot_idx, buf.miss_list, buf.miss_count, buf.out, False, False)
+    B.moe_verify_layer_static(d.shape, *args)
+    torch.cuda.synchronize()
+    own, small = buf.out.clone(), torch.empty(10 << 20, dtype=torch.uint8, device="cuda")
+    B.moe_workspace_init(small)   # a workspace of the general layout's size does too
+    B.moe_verify_layer(d.shape, *args, small)
+    assert torch.equal(own, buf.out)
+    ref = G.run_layer(d).out
+    assert (own - ref).abs().max() <= G.RTOL_RMS * ref.square().mean().sqrt()
