@@ -105,6 +105,9 @@ def _ptr_store(t: torch.Tensor):
 
 def _stream(stream) -> int:
     if stream is None:
+        # (torch.cuda.current_stream() makes a Stream object, 2.8 us of a call that took 7.9; the handle alone takes 0.2)
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
