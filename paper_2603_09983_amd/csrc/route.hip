@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs a)
 
     const int32_t *idx = idx_in_lds ? (const int32_t *)L.idx_s : a.topk_idx;
     if (small) {
-        block_post_small<false>(L.idx_s, L.tab_s, T, a.k, E, a.C, a, L.hist_s, L.cnt_s, L.scan_s, L.off_s, tag);
+        block_post_small<false, true>(L.idx_s, L.tab_s, T, a.k, E, a.C, a, L.hist_s, L.cnt_s, L.scan_s, L.off_s, tag);
     } else if (a.slot_table) {
         // ids and slot table are read through LDS-typed pointers when they are in LDS (the usual case)
         if (idx_in_lds)

@@ -342,7 +342,8 @@ struct SmallLists {
 };
 
 // to_memory false: nothing is written to global memory (a workgroup that only wants the lists for itself).
-template <bool PUBLISH>
+// MOST: also r.max_tokens, the most tokens of any slot (a template argument: the small batches' serial path has no use for it).
+template <bool PUBLISH, bool MOST = false>
 __device__ __forceinline__ SmallLists block_post_small(lds_i32 *idx_s, lds_i32 *tab_s, int T, int kk, int E, int C, const RouteArgs &r,
                                  lds_i32 *hist_s, lds_i32 *mask_s, lds_i32 *scan_s, lds_i32 *off_s, unsigned tag,
                                  bool to_memory = true)
@@ -383,11 +384,10 @@ __device__ __forceinline__ SmallLists block_post_small(lds_i32 *idx_s, lds_i32 *
     const int inc_a = __popcll(__ballot(cntv > 0) & upto);
     int inc_o = 0;
     for (int bit = 0; (1 << bit) <= T; ++bit) inc_o += __popcll(__ballot((cntv >> bit) & 1) & upto) << bit;
-    const bool want_most = to_memory && T > 32;   // (uniform)
-    const unsigned most = want_most ? wave_max_u32((unsigned)cntv) : 0u;
+    const unsigned most = MOST ? wave_max_u32((unsigned)cntv) : 0u;
     if (lane == kWave - 1) {
         scan_s[16 + w] = inc_o;
-        scan_s[32 + w] = inc_a | (int)most << 16;
+        scan_s[32 + w] = MOST ? inc_a | (int)most << 16 : inc_a;
     }
     // (only the wavefronts that hold an assignment or a slot have anything to add)
     const int nwv = ((A > C ? A : C) + kWave - 1) / kWave;
@@ -407,8 +407,8 @@ __device__ __forceinline__ SmallLists block_post_small(lds_i32 *idx_s, lds_i32 *
     __syncthreads();
     int base_o = 0, base_a = 0, tot_o = 0, tot_a = 0, tot_m = 0;
     for (int i = 0; i < nwv; ++i) {
-        const int vo = scan_s[16 + i], vm = scan_s[32 + i], va = vm & 0xffff;
-        tot_m = vm >> 16 > tot_m ? vm >> 16 : tot_m;
+        const int vo = scan_s[16 + i], vm = scan_s[32 + i], va = MOST ? vm & 0xffff : vm;
+        if (MOST) tot_m = vm >> 16 > tot_m ? vm >> 16 : tot_m;
         if (i < w) {
             base_o += vo;
             base_a += va;
@@ -437,7 +437,7 @@ __device__ __forceinline__ SmallLists block_post_small(lds_i32 *idx_s, lds_i32 *
         if (to_memory) {
             r.slot_offset[C] = tot_o;
             *r.n_active = (unsigned)tot_a;
-            if (want_most) *r.max_tokens = (unsigned)tot_m;
+            if (MOST) *r.max_tokens = (unsigned)tot_m;
         }
         publish(0, tot_a);
     }
