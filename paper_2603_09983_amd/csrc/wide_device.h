@@ -11,8 +11,7 @@
 // its weights once per 32, the later times from the caches, as neighbouring items run at the same time).
 //
 // One workgroup of sixteen wavefronts per CU takes items b, b + G, .. and keeps three chunks in flight, across items
-// (3 x 64 KB of weights; with two the time between a chunk's arrival and the request that re-uses its registers is not
-// covered).  Wavefront w multiplies row block w % 4 with the column part w / 4 of the chunk; the four partial results
+// (3 x 64 KB of weights; two workgroups of eight wavefronts with two chunks of 32 KB each measured the same).  Wavefront w multiplies row block w % 4 with the column part w / 4 of the chunk; the four partial results
 // are added through LDS, in a fixed order, while the next chunk is parked.
 //
 // An item starts at a chunk of its own, (item / 8) mod chunks: with rows of 4 or 8 KB all rows' kilobytes of one chunk
