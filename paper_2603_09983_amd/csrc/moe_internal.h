@@ -74,8 +74,10 @@ static inline bool use_wide_kernels(int T, int k, int C, int H, int F, int n_sha
         (n_shared > 0 && (F_shared < 8 || F_shared % 8 != 0)) || wide_lds_bytes(T, k, C, n_shared) > (size_t)kLdsBytes)
         return false;
     // Two token groups and rows of several panels: the streaming kernels reload the B operand for every tile (8 experts
-    // of 4096 x 14336: 17 tokens 576 us, 32 tokens 749 us; here 445 and 446).
-    if (T <= 32) return H > kPanelMax || F > kPanelMax;
+    // of 4096 x 14336: 17 tokens 576 us, 32 tokens 749 us; here 445 and 446).  Two launches more have to pay, though: pools
+    // of 7 MB 23.7 against 25.8 us, 50 MB 33.6 against 34.0, 91 MB 44.2 against 39.5, 201 MB 64.1 against 58.8.
+    if (T <= 32)
+        return (H > kPanelMax || F > kPanelMax) && 6ll * H * ((long long)C * F + (long long)n_shared * F_shared) >= 64ll << 20;
     // Single panels: the streaming kernels as long as no expert has more than 32 tokens (64 experts of 2048 x 1408,
     // 128 tokens: 156 us against 170; 200 tokens 246 against 192; 64 tokens with Zipf-skewed routing 370 against 140).
     // The kernel decides when it has the counts (either_kernel), except that shared experts always have all T tokens
