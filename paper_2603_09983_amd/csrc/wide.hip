@@ -14,13 +14,13 @@ __global__ __launch_bounds__(wide::kThreads) void wide_kernel(StreamArgs a)
 
 }  // namespace
 
-static_assert((size_t)96 * wide::kRowLds + wide::kWaves * 2 * 1024 + (kMaxC + 1) * 16 + kWideTokCap * 2 <= (size_t)kLdsBytes,
+static_assert((size_t)wide::kItemLds + (kMaxC + 1) * 16 + kWideTokCap * 2 <= (size_t)kLdsBytes,
               "any number of slots without shared experts");
 
 size_t wide_lds_bytes(int T, int k, int C, int n_shared)
 {
     const size_t A = (size_t)T * k, n = (size_t)n_shared + C + 1;
-    return (size_t)64 * wide::kRowLds + wide::kTokLds + wide::kWaves * 2 * 1024 + n * 16 + (A <= (size_t)wide::kTokCap ? (A * 2 + 15) / 16 * 16 : 0);
+    return (size_t)wide::kItemLds + n * 16 + (A <= (size_t)wide::kTokCap ? (A * 2 + 15) / 16 * 16 : 0);
 }
 
 bool wide_tall(const StreamArgs &a, bool gateup)

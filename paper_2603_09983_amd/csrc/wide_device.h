@@ -11,18 +11,21 @@
 // its weights once per 32, the later times from the caches, as neighbouring items run at the same time).
 //
 // One workgroup of sixteen wavefronts per CU takes items b, b + G, .. and keeps three chunks in flight, across items
-// (3 x 64 KB of weights; two workgroups of eight wavefronts with two chunks of 32 KB each measured the same).  Wavefront w multiplies row block w % 4 with the column part w / 4 of the chunk; the four partial results
-// are added through LDS, in a fixed order, while the next chunk is parked.
+// (3 x 64 KB of weights).
 //
-// An item starts at a chunk of its own, (item / 8) mod chunks: with rows of 4 or 8 KB all rows' kilobytes of one chunk
-// lie in a quarter or an eighth of an L2's sixteen channels, and workgroups that start together would all be in the same
-// ones (items 8 apart run on the same L2).  Loads alone, 554 MB of gate/up weights with H = 2048: 100 us with all items
-// starting at chunk 0, 90 us so; 1.88 GB with H = 4096: 350 and 298 us.
+// The order of the sums is the streaming kernels': wavefront w multiplies columns 32 w .. 32 w + 31 of every chunk, the
+// chunks of a row in ascending order, and an item's sixteen partial results are added through LDS in wavefront order.  So a
+// token's outputs have the same bits whichever of the kernels runs (contractions of up to kPanelMax columns), whatever else
+// is in the batch and wherever the item lies in the list.  It costs an item's end two barriers and 128 KB of LDS traffic each
+// way (64 rows; with 32 rows the partial results have LDS of their own).
 //
-// Measured (kernels, gate/up + down): 64 tokens, 8 experts of 4096 x 14336: 321 + 163 us (5.9 and 5.7 TB/s), 1048 us in
-// the general kernel; 256 tokens, 48 experts of 2048 x 1408, a mean of 24 tokens each: 112 + 73 us, 247 + 128 us in the
-// streaming kernels, which reload the B operand and drain their loads for every pass over a tile.  At 128 tokens (a mean
-// of 12) those take 88 + 49 us against 99 + 58 here: the rules that choose are use_wide_kernels() and either_kernel.
+// Rows of several panels (K > kPanelMax) start at a chunk that follows from the row: with rows of 8 KB and more all rows'
+// kilobytes of one chunk lie in few of an L2's sixteen channels, and workgroups that start together would all be in the same
+// ones (8 experts of 4096 x 14336, 24 tokens: 530 us per layer with all items starting at chunk 0, 446 us so; H = 2048: no
+// difference).  What an XCD has at a time must differ in that chunk: an expert's tiles begin one XCD further on than those of
+// the expert before.  An expert with more than 32 tokens has its token blocks of a row tile eight items apart, so that they
+// read the same weights from one L2 at the same time (128 tokens on 8 experts of 4096 x 14336: 724 -> 700 us; 64 experts of
+// 2048 x 1408, Zipf-skewed, 128 tokens: 195.5 -> 189.4 us, both with neighbouring blocks before).
 //
 // Any width that is a multiple of 8: rows and tokens beyond the end repeat the last one and are not stored; columns
 // beyond the end of a row are zero in both operands.
@@ -43,6 +46,7 @@ constexpr int kStages = 3;                   // chunks in flight per workgroup
 constexpr int kChunkBytes = 1024;            // 512 columns
 constexpr int kRowLds = kChunkBytes + 16;    // (padding: sixteen rows' 16-byte words fall into sixteen bank groups)
 constexpr int kTokLds = kToks * kRowLds;
+constexpr int kItemLds = 64 * kRowLds + kWaves * 4 * 1024;   // tiles and partial results of an item of two row blocks; those of four share it
 constexpr int kTokCap = kWideTokCap;
 
 __device__ inline uint32_t f32_to_bf16_rne(float f)
@@ -56,6 +60,14 @@ __device__ inline f32x4 mfma(u32x4 a, u32x4 b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// The same value, but not one that the compiler may have worked with before: what an item's end derives from it is not kept
+// in registers (or scratch memory) all through the loop.
+__device__ __forceinline__ int here(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // TOK_LDS: the tokens of the list entries are in LDS (gate/up kernel, lists of up to kTokCap entries).  (A template
 // argument: a global load that the walk might do would make every later wait in the loop one for all loads.)
 // RB: blocks of 16 weight rows in an item (gate/up: the first half gate rows, the second half up rows).
@@ -63,64 +75,93 @@ template <bool GATEUP, bool TOK_LDS, int RB>
 __device__ __forceinline__ void wide_body(const StreamArgs &a)
 {
     constexpr int RPI = GATEUP ? 8 * RB : 16 * RB;   // output rows of an item
-    constexpr int KQ = kWaves / RB;                  // parts that the columns of a chunk are split into
-    constexpr int KB = kChunkBytes / 64 / KQ;        // 32-wide column blocks of a part
     constexpr int kTileLds = 16 * RB * kRowLds;
+    static_assert(kChunkBytes == kWaves * 64, "a wavefront multiplies one block of 32 columns of a chunk");
+    constexpr int kPart = kWaves * RB * 2 * 1024;          // partial results of an item
+    constexpr bool OWN = kTileLds + kTokLds + kPart <= kItemLds;   // ... in LDS of their own, or in the place of the tiles
+    static_assert(OWN || (kPart <= kItemLds && kTileLds + kTokLds <= kItemLds), "the item's LDS");
     extern __shared__ __align__(16) unsigned char lds[];
     unsigned char *const a_s = lds, *const b_s = lds + kTileLds;
-    float *const red_s = (float *)(lds + kTileLds + kTokLds);   // [wavefront][token group][256] partial results
-    const int A = a.T * a.k, n_cap = a.n_shared + a.C + 1;
-    int *const first_s = (int *)(red_s + kWaves * 2 * 256);   // [entry] its first item (entries: shared experts, active slots)
+    float *const part_s = (float *)(lds + (OWN ? kTileLds + kTokLds : 0));   // [token group][wavefront][row block][256] partial results
+    const int A = a.T * a.k, n_cap = a.C + 1;
+    int *const first_s = (int *)(lds + kItemLds);   // [active slot] its first item
     int *const m_s = first_s + n_cap, *const off_s = m_s + n_cap, *const slot_s = off_s + n_cap;
     uint16_t *const tok_s = (uint16_t *)(slot_s + n_cap);   // token of each list entry (A <= kTokCap)
 
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int n = lane & 15, g = lane >> 4;
     const int G = gridDim.x, b = blockIdx.x;
-    const int n_act = (int)*a.n_active, n_ent = a.n_shared + n_act;
+    const int n_act = (int)*a.n_active;
     const int tiles = (a.R + RPI - 1) / RPI, tiles_sh = a.n_shared ? (a.R_sh + RPI - 1) / RPI : 0;
+    const int nb_sh = (a.T + kToks - 1) / kToks, sh_items = a.n_shared * tiles_sh * nb_sh;   // (the shared experts' items come first)
 
     if (GATEUP && TOK_LDS)
         for (int i = tid; i < A; i += kThreads) tok_s[i] = (uint16_t)udiv_rcp(a.perm[i], a.k, a.rcp_k);
-    for (int e = tid; e < n_ent; e += kThreads) {
-        const int c = e < a.n_shared ? e : a.active_slots[e - a.n_shared];
+    for (int e = tid; e < n_act; e += kThreads) {
+        const int c = a.active_slots[e];
         slot_s[e] = c;
-        m_s[e] = e < a.n_shared ? a.T : a.slot_count[c];
-        off_s[e] = e < a.n_shared ? e * a.T : a.slot_offset[c];
+        m_s[e] = a.slot_count[c];
+        off_s[e] = a.slot_offset[c];
     }
     __syncthreads();
     if (w == 0) {
-        // items before each entry: row tiles x blocks of 32 tokens
-        int base = 0;
-        for (int e0 = 0; e0 < n_ent; e0 += kWave) {
+        // items before each active slot: row tiles x blocks of 32 tokens
+        int base = sh_items;
+        for (int e0 = 0; e0 < n_act; e0 += kWave) {
             const int e = e0 + lane;
-            const int own = e < n_ent ? (m_s[e] + kToks - 1) / kToks * (e < a.n_shared ? tiles_sh : tiles) : 0;
+            const int own = e < n_act ? (m_s[e] + kToks - 1) / kToks * tiles : 0;
             int inc = own;
 #pragma unroll
             for (int d = 1; d < kWave; d <<= 1) {
                 const int v = __shfl_up(inc, d, kWave);
                 if (lane >= d) inc += v;
             }
-            if (e < n_ent) first_s[e] = base + inc - own;
+            if (e < n_act) first_s[e] = base + inc - own;
             base += __builtin_amdgcn_readlane(inc, kWave - 1);
         }
-        if (lane == 0) first_s[n_ent] = base;
+        if (lane == 0) first_s[n_act] = base;
     }
     __syncthreads();
-    const int total = first_s[n_ent];
+    const int total = first_s[n_act];
     if (b >= total) return;
 
-    // Item i: its entry (expert), row tile and token block.  The blocks of a row tile are neighbours.
-    struct Item { int e, row0, tok0; };
+    // Item i: its expert, first row, first token, and the expert's tokens, first list entry (or act row) and place in
+    // the pool.  Which workgroup (so: which XCD, i mod 8) gets a row tile: the token blocks of a tile lie eight items apart, on
+    // one L2 at the same time; and an expert's tiles begin one XCD further on than those of the one before (see `prot`).
+    struct Item { bool sh; int row0, tok0, m, off, slot; };
     auto decode = [&](int i) {
-        int e = -1;
-        for (int e0 = 0; e0 < n_ent; e0 += kWave) e += __popcll(__ballot(e0 + lane < n_ent && first_s[e0 + lane] <= i));
-        e = __builtin_amdgcn_readfirstlane(e);
-        const int nb = (__builtin_amdgcn_readfirstlane(m_s[e]) + kToks - 1) / kToks;
-        const int rem = i - __builtin_amdgcn_readfirstlane(first_s[e]);
-        const int rt = nb == 1 ? rem : rem / nb;
-        return Item{e, rt * RPI, (rem - rt * nb) * kToks};
+        Item it;
+        int e, rem, nb, tl;
+        it.sh = i < sh_items;
+        if (it.sh) {
+            e = i / (tiles_sh * nb_sh);
+            rem = i - e * (tiles_sh * nb_sh);
+            nb = nb_sh; tl = tiles_sh;
+            it.m = a.T; it.off = e * a.T; it.slot = e;
+        } else {
+            e = -1;
+            const int lane = here(threadIdx.x) & (kWave - 1);
+            for (int e0 = 0; e0 < n_act; e0 += kWave) e += __popcll(__ballot(e0 + lane < n_act && first_s[e0 + lane] <= i));
+            e = __builtin_amdgcn_readfirstlane(e);
+            it.m = __builtin_amdgcn_readfirstlane(m_s[e]);
+            it.off = __builtin_amdgcn_readfirstlane(off_s[e]);
+            it.slot = __builtin_amdgcn_readfirstlane(slot_s[e]);
+            rem = i - __builtin_amdgcn_readfirstlane(first_s[e]);
+            nb = (it.m + kToks - 1) / kToks; tl = tiles;
+        }
+        int rt = rem, tb = 0;
+        if (nb > 1) {
+            const int q = rem / (8 * nb), r8 = rem - q * (8 * nb), gs = tl - 8 * q < 8 ? tl - 8 * q : 8;
+            tb = r8 / gs;
+            rt = 8 * q + r8 - tb * gs;
+        }
+        if (tl >= 8) {
+            rt += e & 7;
+            rt = rt < tl ? rt : rt - tl;
+        }
+        it.row0 = __builtin_amdgcn_readfirstlane(rt * RPI);
+        it.tok0 = __builtin_amdgcn_readfirstlane(tb * kToks);
+        return it;
     };
 
     // ---- the walk that loads: chunk pc of item pi is the next one to put in flight ----
@@ -128,16 +169,17 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
     int pi = b, pc = 0, pK2 = 0, pn = 0, prot = 0;   // (an item's chunks in turn from chunk prot on)
     auto prod_set = [&](int i) {
         const Item it = decode(i);
-        const bool sh = it.e < a.n_shared;
+        const bool sh = it.sh;
         const int K = sh ? a.K_sh : a.K, R = sh ? a.R_sh : a.R;
-        const int m = __builtin_amdgcn_readfirstlane(m_s[it.e]), off = __builtin_amdgcn_readfirstlane(off_s[it.e]);
-        const size_t eoff = (size_t)__builtin_amdgcn_readfirstlane(slot_s[it.e]) * R * K;
+        const int m = it.m, off = it.off;
+        const size_t eoff = (size_t)it.slot * R * K;
         const uint16_t *const w0 = (sh ? a.s0 : a.w0) + eoff, *const w1 = (sh ? a.s1 : a.w1) + eoff;
         const uint16_t *const src = !GATEUP && sh ? a.bsrc_sh : a.bsrc;
         pK2 = 2 * K;
         pn = (pK2 + kChunkBytes - 1) / kChunkBytes;
         pc = 0;
-        prot = (i >> 3) % pn;
+        const int u = it.row0 >> (GATEUP ? 5 : 6);
+        prot = K > kPanelMax ? (u + (u >> 3)) % pn : 0;
 #pragma unroll
         for (int j = 0; j < RB; ++j) {
             int r = it.row0 + 16 * (GATEUP ? j % (RB / 2) : j) + w;
@@ -161,7 +203,7 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
     int s_left[kStages];   // bytes of the row from the chunk's first column on
     auto issue = [&](int s) {
         const int pch = pc + prot < pn ? pc + prot : pc + prot - pn;
-        const int o0 = pch * kChunkBytes, left = pK2 - o0;
+        const int o0 = pch * kChunkBytes, left = pK2 - o0, lane = here(threadIdx.x) & (kWave - 1);
         s_left[s] = left;
         const unsigned o = (unsigned)(o0 + (lane * 16 < left ? lane * 16 : left - 16));   // (lanes beyond the row's end re-read its last word)
 #pragma unroll
@@ -178,6 +220,7 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
         }   // (past the last item: its last chunk again, which nobody multiplies)
     };
     auto park = [&](int s) {
+        const int lane = here(threadIdx.x) & (kWave - 1);
         if (s_left[s] < kChunkBytes) {
             const bool in = lane * 16 < s_left[s];
 #pragma unroll
@@ -195,50 +238,68 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
     };
 
     // ---- the walk that multiplies ----
-    const int rb = w % RB, kq = w / RB;
     int ci = b, cc = 0;
     Item it = decode(ci);
     int cm = 0, cn = 0;
     auto cons_set = [&]() {
-        cm = __builtin_amdgcn_readfirstlane(m_s[it.e]);
-        cn = (2 * (it.e < a.n_shared ? a.K_sh : a.K) + kChunkBytes - 1) / kChunkBytes;
+        cm = it.m;
+        cn = (2 * (it.sh ? a.K_sh : a.K) + kChunkBytes - 1) / kChunkBytes;
         cc = 0;
     };
-    f32x4 acc[2];
+    // Wavefront w multiplies columns 32 w .. 32 w + 31 of every chunk, all row blocks and token groups of the item.
+    f32x4 acc[RB][2];
     auto multiply = [&]() {
-        const unsigned char *const ar = a_s + (16 * rb + n) * kRowLds + kq * (64 * KB) + g * 16;
-        const unsigned char *const br = b_s + n * kRowLds + kq * (64 * KB) + g * 16;
-        u32x4 av[KB], bv[KB];
+        const int ln = here(threadIdx.x) & (kWave - 1), at = (ln & 15) * kRowLds + w * 64 + (ln >> 4) * 16;
+        const unsigned char *const ar = a_s + at, *const br = b_s + at;
+        const bool two = cm - it.tok0 > 16;
+        const u32x4 b0 = *(const u32x4 *)br;
+        u32x4 b1 = {0u, 0u, 0u, 0u};
+        if (two) b1 = *(const u32x4 *)(br + 16 * kRowLds);
 #pragma unroll
-        for (int j = 0; j < KB; ++j) {
-            av[j] = *(const u32x4 *)(ar + j * 64);
-            bv[j] = *(const u32x4 *)(br + j * 64);
-        }
+        for (int j0 = 0; j0 < RB; j0 += 2) {
+            u32x4 av[2];
 #pragma unroll
-        for (int j = 0; j < KB; ++j) acc[0] = mfma(av[j], bv[j], acc[0]);
-        if (cm - it.tok0 > 16) {
+            for (int j = 0; j < 2; ++j) av[j] = *(const u32x4 *)(ar + (j0 + j) * (16 * kRowLds));
 #pragma unroll
-            for (int j = 0; j < KB; ++j) bv[j] = *(const u32x4 *)(br + 16 * kRowLds + j * 64);
-#pragma unroll
-            for (int j = 0; j < KB; ++j) acc[1] = mfma(av[j], bv[j], acc[1]);
+            for (int j = 0; j < 2; ++j) {
+                acc[j0 + j][0] = mfma(av[j], b0, acc[j0 + j][0]);
+                acc[j0 + j][1] = mfma(av[j], b1, acc[j0 + j][1]);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // (no more reads ahead than the registers hold)
         }
     };
-    // The partial results of each element (wavefronts rb, rb + RB, ..), added in that order.
-    // Element (row r, token t) of a 16 x 16 result sits at ((r / 4) * 16 + t) * 4 + r % 4.
+    // Element (row r, token t) of a 16 x 16 partial result lies in word (r / 4) * 64 + ((t + r / 4 + 4 * block) % 16) * 4 + r % 4:
+    // what is read together, consecutive rows of one token, falls into banks of its own.
+    auto post_partials = [&]() {
+        const int gmax = cm - it.tok0 > 16 ? 2 : 1;
+        const int ln = here(threadIdx.x) & (kWave - 1), n = ln & 15, g = ln >> 4;   // (the MFMA result's token; rows 4 g .. 4 g + 3)
+#pragma unroll
+        for (int gr = 0; gr < 2; ++gr)
+            if (gr < gmax)
+#pragma unroll
+                for (int j = 0; j < RB; ++j)
+                    *(f32x4 *)(part_s + ((gr * kWaves + w) * RB + j) * 256 + g * 64 + ((n + g + 4 * j) & 15) * 4) = acc[j][gr];
+    };
+    // ... and its sixteen partial results, added in wavefront order.
     auto total_of = [&](int block, int gr, int r, int t) {
-        const float *p = red_s + (block * 2 + gr) * 256 + ((r >> 2) * 16 + t) * 4 + (r & 3);
-        float v[KQ];
+        const float *p = part_s + (gr * kWaves * RB + block) * 256 + (r >> 2) * 64 + ((t + (r >> 2) + 4 * block) & 15) * 4 + (r & 3);
+        float sum = 0.f;
 #pragma unroll
-        for (int i = 0; i < KQ; ++i) v[i] = p[i * (RB * 512)];
+        for (int i0 = 0; i0 < kWaves; i0 += 8) {
+            float v[8];
 #pragma unroll
-        for (int i = 1; i < KQ; ++i) v[0] += v[i];
-        return v[0];
+            for (int i = 0; i < 8; ++i) v[i] = p[(i0 + i) * (RB * 256)];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sum += v[i];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        return sum;
     };
-    // (every wavefront's partial results are there; the next ones are written behind another barrier)
     auto finish = [&]() {
-        const bool sh = it.e < a.n_shared;
+        const int tid = here(threadIdx.x);
+        const bool sh = it.sh;
         const int R = sh ? a.R_sh : a.R;
-        const size_t row0 = (size_t)__builtin_amdgcn_readfirstlane(off_s[it.e]) + it.tok0;
+        const size_t row0 = (size_t)it.off + it.tok0;
         if (GATEUP) {
             const int f = tid % RPI, t = tid / RPI;
             if (t < kToks && it.tok0 + t < cm && it.row0 + f < R) {
@@ -267,15 +328,20 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
         issue(s);
         prod_advance();
         __syncthreads();
-        if (cc == 0) acc[0] = acc[1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if (cc == 0)
+#pragma unroll
+            for (int j = 0; j < RB; ++j) acc[j][0] = acc[j][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
         multiply();
         const bool last = ++cc == cn;
-        if (last)
-#pragma unroll
-            for (int gr = 0; gr < 2; ++gr) *(f32x4 *)(red_s + (w * 2 + gr) * 256 + lane * 4) = acc[gr];
+        if (OWN && last) post_partials();
         __syncthreads();
         if (last) {
+            if (!OWN) {
+                post_partials();
+                __syncthreads();
+            }
             finish();
+            if (!OWN) __syncthreads();   // (OWN: the next ones are written behind the next step's first barrier)
             if (ci + G < total) {
                 ci += G;
                 it = decode(ci);
@@ -285,7 +351,7 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
     };
     // chunks of this workgroup's items (shared experts' items come first).  The first step is peeled off and the
     // loop goes in threes, so that the compiler's count of the loads in flight is exact: a park waits for its own chunk.
-    const int n_sh = first_s[a.n_shared] > b ? (first_s[a.n_shared] - b + G - 1) / G : 0, n_all = (total - b + G - 1) / G;
+    const int n_sh = sh_items > b ? (sh_items - b + G - 1) / G : 0, n_all = (total - b + G - 1) / G;
     const int chunks = n_sh * ((2 * a.K_sh + kChunkBytes - 1) / kChunkBytes) + (n_all - n_sh) * ((2 * a.K + kChunkBytes - 1) / kChunkBytes);
     step(0);
     int c = 1;
