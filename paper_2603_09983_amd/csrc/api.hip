@@ -323,7 +323,7 @@ extern "C" int moe_slot_resolve(const int32_t *topk_idx, const int32_t *slot_tab
                                   (int32_t *)(ws + w.slot_count), (int32_t *)(ws + w.slot_offset),
                                   (int32_t *)(ws + w.perm), (int32_t *)(ws + w.pos),
                                   (int32_t *)(ws + w.active), (unsigned *)(ws + w.ctrl) + kCtrlNActive,
-                                  (unsigned *)(ws + w.ctrl) + kCtrlMaxTokens, (hipStream_t)stream);
+                                  (unsigned *)(ws + w.ctrl) + kCtrlBlocks, (hipStream_t)stream);
     return e == hipSuccess ? MOE_OK : launch_failed(e);
 }
 
@@ -378,7 +378,7 @@ int run_ffn(const void *hidden, const float *topk_w, const void *w_gate, const v
         g.slot_count = slot_count; g.slot_offset = slot_offset; g.perm = perm;
         g.active_slots = (const int32_t *)(ws + w.active);
         g.n_active = (const unsigned *)(ws + w.ctrl) + kCtrlNActive;
-        g.max_tokens = (const unsigned *)(ws + w.ctrl) + kCtrlMaxTokens;
+        g.n_blocks = (const unsigned *)(ws + w.ctrl) + kCtrlBlocks;
         g.T = T; g.k = k; g.C = C;
         g.R = F; g.K = H; g.R_sh = F_shared; g.K_sh = H; g.n_shared = n_shared;
         g.KP = g.KP_sh = panel(H);
@@ -444,7 +444,7 @@ extern "C" int moe_grouped_ffn(const void *hidden, const float *topk_w, const in
                                            (int32_t *)(ws + w.slot_offset), (int32_t *)(ws + w.perm),
                                            (int32_t *)(ws + w.pos), (int32_t *)(ws + w.active),
                                            (unsigned *)(ws + w.ctrl) + kCtrlNActive,
-                                           (unsigned *)(ws + w.ctrl) + kCtrlMaxTokens,
+                                           (unsigned *)(ws + w.ctrl) + kCtrlBlocks,
                                            (unsigned *)(ws + w.ctrl) + kCtrlEpoch, s);
     if (e != hipSuccess) return launch_failed(e);
     return run_ffn(hidden, topk_w, w_gate, w_up, w_down, nullptr, nullptr, nullptr, T, H, F, k, C, 0, 0, w, ws,
@@ -499,7 +499,7 @@ int run_layer(const moe_shape_t *sh, const void *hidden, const float *router_w, 
     r.slot_count = (int32_t *)(ws + w.slot_count); r.slot_offset = (int32_t *)(ws + w.slot_offset);
     r.perm = (int32_t *)(ws + w.perm); r.pos = (int32_t *)(ws + w.pos);
     r.active_slots = (int32_t *)(ws + w.active); r.n_active = (unsigned *)(ws + w.ctrl) + kCtrlNActive;
-    r.max_tokens = (unsigned *)(ws + w.ctrl) + kCtrlMaxTokens;
+    r.n_blocks = (unsigned *)(ws + w.ctrl) + kCtrlBlocks;
     // The launch forms (moe_shape_t::launch_form): three launches (routing kernel, gate/up stream, down stream with
     // the final sum), two (routing steps at the head of the gate/up kernel), one (routing, gate/up, down and the
     // final sum in one kernel: batches of up to 16 tokens), or the routing kernel followed by the one-launch FFN.

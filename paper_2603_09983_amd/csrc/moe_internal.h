@@ -60,14 +60,24 @@ static inline bool use_stream_kernels(int T, int k, int C, int H, int F, int n_s
            stream_lds_need(kp_f > kp_s ? kp_f : kp_s, T, k, C, false) <= (size_t)kLdsBytes;
 }
 
+// entries of the item list beyond one for each slot when an expert's 32-token blocks are entries of their own
+__host__ __device__ static inline int stream_more_entries(int T, int k) { return T * k / 32; }
+
+// Batches of more than 32 tokens in the streaming kernels: single panels of whole 64s, lists of up to kLargeListCap entries
+// (beyond, with a mean of a hundred tokens an expert, the larger-batch kernels are the faster ones; launch_large has the figures).
+constexpr int kLargeListCap = 6144;
+static inline bool use_stream_large(int T, int k, int C, int H, int F, int n_shared, int F_shared)
+{
+    if (T <= 32 || (size_t)T * k > (size_t)kLargeListCap || !use_stream64(T, k, C, H, F, n_shared, F_shared)) return false;
+    const size_t more = (size_t)stream_more_entries(T, k) * 4;
+    const int kp_f = n_shared > 0 && F_shared > F ? F_shared : F;
+    return stream_lds_need(H, T, k, C, true) + more <= (size_t)kLdsBytes && stream_lds_need(kp_f, T, k, C, false) + more <= (size_t)kLdsBytes &&
+           (long long)n_shared * T <= 1 << 16;   // (32-bit offsets of a shared expert's activations)
+}
+
 // Larger batches (wide.hip), any width that is a multiple of 8.
 size_t wide_lds_bytes(int T, int k, int C, int n_shared);
 constexpr int kWideTokCap = 6144;   // list entries whose tokens are kept in LDS
-static inline bool use_either_kernel(int T, int k, int C, int H, int F, int n_shared, int F_shared)
-{
-    return T > 32 && n_shared == 0 && (size_t)T * k <= (size_t)kWideTokCap && use_stream64(T, k, C, H, F, n_shared, F_shared) &&
-           wide_lds_bytes(T, k, C, 0) <= (size_t)kLdsBytes;
-}
 static inline bool use_wide_kernels(int T, int k, int C, int H, int F, int n_shared, int F_shared)
 {
     if (T <= 16 || T > 65535 || H < 8 || F < 8 || H % 8 != 0 || F % 8 != 0 || n_shared > kMaxC ||
@@ -78,11 +88,7 @@ static inline bool use_wide_kernels(int T, int k, int C, int H, int F, int n_sha
     // of 7 MB 23.7 against 25.8 us, 50 MB 33.6 against 34.0, 91 MB 44.2 against 39.5, 201 MB 64.1 against 58.8.
     if (T <= 32)
         return (H > kPanelMax || F > kPanelMax) && 6ll * H * ((long long)C * F + (long long)n_shared * F_shared) >= 64ll << 20;
-    // Single panels: the streaming kernels as long as no expert has more than 32 tokens (64 experts of 2048 x 1408,
-    // 128 tokens: 156 us against 170; 200 tokens 246 against 192; 64 tokens with Zipf-skewed routing 370 against 140).
-    // The kernel decides when it has the counts (either_kernel), except that shared experts always have all T tokens
-    // and that it takes lists of up to kWideTokCap entries.
-    return !use_either_kernel(T, k, C, H, F, n_shared, F_shared);
+    return !use_stream_large(T, k, C, H, F, n_shared, F_shared);
 }
 
 static inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -132,7 +138,7 @@ constexpr int kCtrlEpoch = 3;     // routing calls completed on this workspace (
 constexpr int kCtrlSpin = 4;      // polls before a wait gives up (0 = the built-in bound)
 constexpr int kCtrlSkew = 5;      // added to the call number that producers stamp their entries with (0)
 constexpr int kCtrlLayout = 6;    // hash of the layout the workspace has been used with since it was initialised (0: none yet)
-constexpr int kCtrlMaxTokens = 7; // most tokens that any slot received (written for batches of more than 32 tokens)
+constexpr int kCtrlBlocks = 7;    // blocks of 32 tokens (the last one of a list may be short) that the slots' lists consist of
 constexpr unsigned kErrWait = 1u, kErrLayout = 2u;   // bits of the error word
 
 // The first kernel of a call: the workspace serves one layout between two initialisations (a region that held
@@ -154,7 +160,7 @@ static inline WsLayout ws_layout(int T, int E, int k, int C, int H, int F, int n
 {
     WsLayout w;
     w.wide = !general && use_wide_kernels(T, k, C, H, F, n_shared, F_shared);
-    w.stream = !general && (w.wide || (T > 32 ? use_either_kernel(T, k, C, H, F, n_shared, F_shared)
+    w.stream = !general && (w.wide || (T > 32 ? use_stream_large(T, k, C, H, F, n_shared, F_shared)
                                               : use_stream_kernels(T, k, C, H, F, n_shared, F_shared)));
     size_t A = (size_t)T * k;
     size_t o = 0;
@@ -253,7 +259,7 @@ struct RouteArgs {
     int32_t *pos;              // [T*k]
     int32_t *active_slots;     // [C] slots with at least one token, ascending
     unsigned *n_active;        // [1]
-    unsigned *max_tokens;      // [1] most tokens of any slot (batches of more than 32)
+    unsigned *n_blocks;        // [1] blocks of 32 tokens that the slots' lists consist of
     unsigned *error_flag;      // control word set when a bounded wait inside a kernel ran out
     unsigned long long *tagged_logits;   // [T*E] (tag << 32 | value bits)
     unsigned long long *tagged_idx;      // [T*k] (tag << 32 | expert id), batches above 16 tokens
@@ -270,16 +276,16 @@ struct StreamArgs {
     void *out, *out_sh;        // gate/up: act, act_sh (bf16); down: o [A,H], o_sh [n_shared,T,H] (fp32)
     const int32_t *slot_count, *slot_offset, *perm, *active_slots;
     const unsigned *n_active;
-    const unsigned *max_tokens;   // most tokens of any slot (read for batches of more than 32)
+    const unsigned *n_blocks;     // blocks of 32 tokens that the slots' lists consist of (read for batches of more than 32)
     int T, k;
     int R, K, R_sh, K_sh, n_shared, C;
     int KP, KP_sh;             // panel widths (columns parked in LDS at a time)
     // Filled in by the launch functions: panels per routed / shared item, and floor(2^32 / d) for the divisors of
-    // the kernel's index arithmetic (grid size, items per routed / shared expert, panels per item, k, k + n_shared).  A division by a
+    // the kernel's index arithmetic (grid size, items per routed / shared expert, panels per item, k, k + n_shared, blocks of 32 tokens).  A division by a
     // value only known at run time is ~30 instructions, and in the prologue of a launch sixteen wavefronts execute
     // them one after the other on the compute unit's one scalar unit.
     int np, np_sh;
-    unsigned rcp_G, rcp_tiles, rcp_tiles_sh, rcp_np, rcp_k, rcp_S;
+    unsigned rcp_G, rcp_tiles, rcp_tiles_sh, rcp_np, rcp_k, rcp_S, rcp_nb;
 };
 
 // n / d with rcp = floor(2^32 / d) (d = 1: 2^32 - 1): the estimate is never too large and at most one short.
@@ -346,12 +352,12 @@ hipError_t launch_histogram(const int32_t *topk_idx, int A, int E, int32_t *hist
 hipError_t launch_resolve(const int32_t *topk_idx, const int32_t *slot_table, int A, int E, int C,
                           int32_t *slot_idx, int32_t *miss_list, int32_t *miss_count, int32_t *slot_count,
                           int32_t *slot_offset, int32_t *perm, int32_t *pos, int32_t *active_slots,
-                          unsigned *n_active, unsigned *max_tokens, hipStream_t s);
+                          unsigned *n_active, unsigned *n_blocks, hipStream_t s);
 // (epoch: control word stepped by one, so that the FFN kernels of this call have a number of their own)
 // (layout: hash of the workspace layout of this call, checked against the one the workspace has served so far)
 hipError_t launch_lists_from_slots(unsigned layout, const int32_t *slot_idx, int A, int C, int32_t *slot_count,
                                    int32_t *slot_offset, int32_t *perm, int32_t *pos, int32_t *active_slots,
-                                   unsigned *n_active, unsigned *max_tokens, unsigned *epoch, hipStream_t s);
+                                   unsigned *n_active, unsigned *n_blocks, unsigned *epoch, hipStream_t s);
 // join != null (down kernel only, stream_can_join() true): outputs leave as stamped 64-bit entries
 // and the kernel ends with the weighted sum into `out`; no combine launch is needed then
 hipError_t launch_stream(const StreamArgs &a, bool gateup, const JoinArgs *join, hipStream_t s);

@@ -50,6 +50,17 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned x)
     return ab > cd ? ab : cd;
 }
 
+// Sum of x over the 64 lanes, likewise.
+__device__ __forceinline__ unsigned wave_sum_u32(unsigned x)
+{
+    x += row_rotate<1>(x);
+    x += row_rotate<2>(x);
+    x += row_rotate<4>(x);
+    x += row_rotate<8>(x);
+    return (unsigned)__builtin_amdgcn_readlane((int)x, 0) + (unsigned)__builtin_amdgcn_readlane((int)x, 16) +
+           (unsigned)__builtin_amdgcn_readlane((int)x, 32) + (unsigned)__builtin_amdgcn_readlane((int)x, 48);
+}
+
 // One wavefront picks the Top-k of the E logits of one token, best first: k times the maximum over the
 // wavefront, ties to the lower expert id, the winner taken out.  Logits are compared as unsigned keys
 // that order like the floats (-0 counted as +0; key 0 = taken or no expert, below every float).  The
@@ -158,7 +169,7 @@ template <typename IdxPtr, typename TabPtr>
 __device__ void block_post(IdxPtr idx, TabPtr slot_table, int A, int E, int C, int32_t *hist,
                            int32_t *slot_idx, int32_t *miss_list, int32_t *miss_count, int32_t *slot_count,
                            int32_t *slot_offset, int32_t *perm, int32_t *pos, int32_t *active_slots,
-                           unsigned *n_active, unsigned *max_tokens, lds_i32 *hist_s, lds_i32 *cnt_s, lds_i32 *off_s, lds_i32 *scan_s,
+                           unsigned *n_active, unsigned *n_blocks, lds_i32 *hist_s, lds_i32 *cnt_s, lds_i32 *off_s, lds_i32 *scan_s,
                            lds_i32 *sidx_s)
 {
     static_assert(kMaxC <= kRouteThreads && kMaxC <= 1 << 10, "one thread per slot; ten bits of slot id");
@@ -241,9 +252,9 @@ __device__ void block_post(IdxPtr idx, TabPtr slot_table, int A, int E, int C, i
         if (lane >= d) inc_o += v;
     }
     const unsigned long long act = __ballot(cntv > 0);
-    const unsigned most = wave_max_u32((unsigned)cntv);
+    const unsigned blocks = wave_sum_u32((unsigned)(cntv + 31) / 32u);
     if (lane == kWave - 1) {
-        scan_s[w] = (int)most;   // (the misses' counts are no longer needed)
+        scan_s[w] = (int)blocks;   // (the misses' counts are no longer needed)
         scan_s[16 + w] = inc_o;
         scan_s[32 + w] = __popcll(act);
     }
@@ -268,9 +279,9 @@ __device__ void block_post(IdxPtr idx, TabPtr slot_table, int A, int E, int C, i
     if (tid == 0) {
         slot_offset[C] = tot_o;
         *n_active = (unsigned)tot_a;
-        int m = 0;
-        for (int i = 0; i < (C + kWave - 1) / kWave; ++i) m = scan_s[i] > m ? scan_s[i] : m;
-        *max_tokens = (unsigned)m;
+        int nb = 0;
+        for (int i = 0; i < (C + kWave - 1) / kWave; ++i) nb += scan_s[i];
+        *n_blocks = (unsigned)nb;
     }
     __syncthreads();
     // lists: assignment a goes to position off[slot] + (number of earlier assignments of that slot),
@@ -342,8 +353,8 @@ struct SmallLists {
 };
 
 // to_memory false: nothing is written to global memory (a workgroup that only wants the lists for itself).
-// MOST: also r.max_tokens, the most tokens of any slot (a template argument: the small batches' serial path has no use for it).
-template <bool PUBLISH, bool MOST = false>
+// BLOCKS: also r.n_blocks (a template argument: the small batches' serial path has no use for it).
+template <bool PUBLISH, bool BLOCKS = false>
 __device__ __forceinline__ SmallLists block_post_small(lds_i32 *idx_s, lds_i32 *tab_s, int T, int kk, int E, int C, const RouteArgs &r,
                                  lds_i32 *hist_s, lds_i32 *mask_s, lds_i32 *scan_s, lds_i32 *off_s, unsigned tag,
                                  bool to_memory = true)
@@ -384,10 +395,10 @@ __device__ __forceinline__ SmallLists block_post_small(lds_i32 *idx_s, lds_i32 *
     const int inc_a = __popcll(__ballot(cntv > 0) & upto);
     int inc_o = 0;
     for (int bit = 0; (1 << bit) <= T; ++bit) inc_o += __popcll(__ballot((cntv >> bit) & 1) & upto) << bit;
-    const unsigned most = MOST ? wave_max_u32((unsigned)cntv) : 0u;
+    const unsigned blocks = BLOCKS ? wave_sum_u32((unsigned)(cntv + 31) / 32u) : 0u;
     if (lane == kWave - 1) {
         scan_s[16 + w] = inc_o;
-        scan_s[32 + w] = MOST ? inc_a | (int)most << 16 : inc_a;
+        scan_s[32 + w] = BLOCKS ? inc_a | (int)blocks << 16 : inc_a;
     }
     // (only the wavefronts that hold an assignment or a slot have anything to add)
     const int nwv = ((A > C ? A : C) + kWave - 1) / kWave;
@@ -405,10 +416,10 @@ __device__ __forceinline__ SmallLists block_post_small(lds_i32 *idx_s, lds_i32 *
         }
     }
     __syncthreads();
-    int base_o = 0, base_a = 0, tot_o = 0, tot_a = 0, tot_m = 0;
+    int base_o = 0, base_a = 0, tot_o = 0, tot_a = 0, tot_b = 0;
     for (int i = 0; i < nwv; ++i) {
-        const int vo = scan_s[16 + i], vm = scan_s[32 + i], va = MOST ? vm & 0xffff : vm;
-        if (MOST) tot_m = vm >> 16 > tot_m ? vm >> 16 : tot_m;
+        const int vo = scan_s[16 + i], vb = scan_s[32 + i], va = BLOCKS ? vb & 0xffff : vb;
+        if (BLOCKS) tot_b += vb >> 16;
         if (i < w) {
             base_o += vo;
             base_a += va;
@@ -437,7 +448,7 @@ __device__ __forceinline__ SmallLists block_post_small(lds_i32 *idx_s, lds_i32 *
         if (to_memory) {
             r.slot_offset[C] = tot_o;
             *r.n_active = (unsigned)tot_a;
-            if (MOST) *r.max_tokens = (unsigned)tot_m;
+            if (BLOCKS) *r.n_blocks = (unsigned)tot_b;
         }
         publish(0, tot_a);
     }

@@ -27,7 +27,6 @@
 // whole one, since its requests wait in the same queues behind everybody's whole tiles.)
 #include "moe_internal.h"
 #include "route_device.h"
-#include "wide_device.h"
 
 namespace moe {
 
@@ -76,8 +75,8 @@ __device__ inline uint32_t f32_to_bf16_rne(float f)
 // park tile t, put tile t+2 in flight, multiply.  That is what lets the wait before a park leave
 // the younger tile in flight.  The state of the two walks over the run (the tile to load next,
 // the tile being consumed) lives in plain scalars and is stepped, not recomputed.
-// MODE 0: batches up to 16 tokens (one group of 16 token columns per pass); MODE 1: up to 32 tokens
-// (two groups); MODE 2: larger batches in which no expert has more than 32 tokens (two groups).
+// MODE 0: batches up to 16 tokens (one group of 16 token columns); MODE 1: up to 32 tokens (two groups); MODE 2: larger
+// batches (two groups; the item list's entries are an expert's blocks of 32 tokens, see launch_large).
 //
 // JOIN (down kernel, batches of up to 32 tokens): the weighted sum back into token order (Sec. 2.2 last
 // line; the join of App. D when `accumulate` is set) rides at the end of the down kernel instead
@@ -106,8 +105,7 @@ __device__ unsigned long long g_timeline[2][kTimelineGroups][kTimelineWords];
 // its last 16 bytes; the last panel of a row starts early enough to be as wide as the others, and the columns that
 // the panel before had, or that no row has, are zero in both operands; the down kernel's last tile may have 8 rows.
 //
-// WIDE_RB (MODE 2): row blocks of the larger-batch kernel that takes over when an expert has more than 32 tokens.
-template <bool GATEUP, int NPI, int MODE, bool JOIN, bool WSPLIT, bool FUSED, bool RAGGED, int WIDE_RB = 0>
+template <bool GATEUP, int NPI, int MODE, bool JOIN, bool WSPLIT, bool FUSED, bool RAGGED>
 __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_lds_bytes, const JoinArgs &jn,
                                             const RouteArgs &ra)
 {
@@ -128,7 +126,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     unsigned char *tile_s = lds;
     float *red_s = (float *)(lds + tile_lds_bytes);                   // [group][wavefront][lane][4]
     int *ctl_s = (int *)(lds + tile_lds_bytes + NG * kWaves * kWave * 16);
-    int *count_s = ctl_s, *offset_s = ctl_s + a.C, *active_s = ctl_s + 2 * a.C, *perm_s = ctl_s + 3 * a.C;
+    int *count_s = ctl_s, *offset_s = ctl_s + a.C, *active_s = ctl_s + 2 * a.C;
+    int *perm_s = active_s + a.C + (MODE == 2 ? stream_more_entries(a.T, a.k) : 0);
     float *out_s = (float *)(perm_s + a.T * a.k);                     // [kOutCap][NG][kOutPerItem] results waiting to be stored
     int *odesc_s = (int *)(out_s + kOutCap * NG * kOutPerItem);       // [kOutCap][8]: shared?, row of token 0, column bytes, m
 
@@ -148,7 +147,9 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     // (bytes of a tile row in LDS, and its 32-wide column blocks, for a panel row of rs bytes)
     auto lds_row = [](int rs) { return RAGGED ? ((rs + 127) & ~127) + kRowPad : rs + kRowPad; };
     auto col_blocks = [](int rs) { return RAGGED ? (rs + 63) / 64 : rs / 64; };
-    const int n_sh_items = a.n_shared * tiles_sh;
+    // (MODE 2: an entry of the list is an expert's block of 32 tokens: slot | block << 16 in active_s)
+    const int nb_sh = MODE == 2 ? (a.T + 31) / 32 : 1;
+    const int n_sh_items = a.n_shared * nb_sh * tiles_sh;
     const int sh_per = udiv_rcp(n_sh_items, G, a.rcp_G), sh_rem = n_sh_items - sh_per * G;
     // (FUSED: workgroup 0 also writes the step outputs and waits for every workgroup's word before it gives the
     // call its number; it takes the last place in the split, whose run is never the longer one)
@@ -167,15 +168,16 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         psh = sh; pe = e; prt = rt; ppan = 0;
         if (RAGGED) ppoff = 0;
         if (sh) {
-            const int K = a.K_sh;
-            const size_t eoff = ((size_t)e * a.R_sh + (size_t)rt * RPI) * K;
+            const int K = a.K_sh, ex = MODE == 2 ? udiv_rcp(e, nb_sh, a.rcp_nb) : e;
+            const size_t eoff = ((size_t)ex * a.R_sh + (size_t)rt * RPI) * K;
             pw0 = (const unsigned char *)(a.s0 + eoff);
             pw1 = GATEUP ? (const unsigned char *)(a.s1 + eoff) : pw0 + (size_t)16 * K;
             if (RAGGED && !GATEUP && rt * 16 + 8 >= a.R_sh) pw1 = pw0;   // (the last tile has 8 rows)
             pK2 = 2 * K; prs = 2 * a.KP_sh; pnpan = a.np_sh;
         } else {
             const int K = a.K;
-            const size_t eoff = ((size_t)active_s[e] * a.R + (size_t)rt * RPI) * K;
+            const int c = MODE == 2 ? active_s[e] & 0xffff : active_s[e];
+            const size_t eoff = ((size_t)c * a.R + (size_t)rt * RPI) * K;
             pw0 = (const unsigned char *)(a.w0 + eoff);
             pw1 = GATEUP ? (const unsigned char *)(a.w1 + eoff) : pw0 + (size_t)16 * K;
             if (RAGGED && !GATEUP && rt * 16 + 8 >= a.R) pw1 = pw0;
@@ -220,12 +222,13 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         cocol = rt * RPI * OB;
         if (sh) {
             cK = a.K_sh; c_rs = 2 * a.KP_sh; cnpan = a.np_sh;
-            cm = a.T; ckey = ALLTOK ? 0 : e; corow0 = e * a.T;
-            cbrow0 = GATEUP ? 0 : e * a.T;            // hidden[n] | act_sh[e][n]
+            const int ex = MODE == 2 ? udiv_rcp(e, nb_sh, a.rcp_nb) : e, t0 = MODE == 2 ? (e - ex * nb_sh) * 32 : 0;
+            cm = a.T - t0; ckey = ALLTOK ? 0 : e; corow0 = ex * a.T + t0;
+            cbrow0 = GATEUP ? t0 : corow0;            // hidden[t0 + n] | act_sh[e][t0 + n]
         } else {
-            const int c = active_s[e];
+            const int c = MODE == 2 ? active_s[e] & 0xffff : active_s[e], t0 = MODE == 2 ? (active_s[e] >> 16) * 32 : 0;
             cK = a.K; c_rs = 2 * a.KP; cnpan = a.np;
-            cm = count_s[c]; ckey = ALLTOK ? 0 : a.n_shared + c; corow0 = offset_s[c];
+            cm = count_s[c] - t0; ckey = ALLTOK ? 0 : MODE == 2 ? a.n_shared * nb_sh + e : a.n_shared + c; corow0 = offset_s[c] + t0;
             cbrow0 = ALLTOK ? 0 : GATEUP ? -1 : corow0;   // hidden[n] | hidden[token of list entry n] | act[row]
         }
     };
@@ -555,10 +558,29 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         n_act = (int)(*a.n_active);
         if constexpr (MODE == 2) {
             // (asked for here, with the lists: ahead of them it would be a trip to memory of its own)
-            if (*a.max_tokens > 32u) {
+            const int n_ent = (int)*a.n_blocks;
+            if (n_ent != n_act) {
+                // some experts have more than 32 tokens: as many entries as blocks
                 __syncthreads();
-                wide::wide_body<GATEUP, true, WIDE_RB>(a);
-                return;
+                int *const ent_s = (int *)red_s;   // (nobody's yet)
+                if (w == 0) {
+                    int base = 0;
+                    for (int e0 = 0; e0 < n_act; e0 += kWave) {
+                        const int c = e0 + lane < n_act ? active_s[e0 + lane] : 0;
+                        const int own = e0 + lane < n_act ? (count_s[c] + 31) / 32 : 0;
+                        int inc = own;
+#pragma unroll
+                        for (int d = 1; d < kWave; d <<= 1) {
+                            const int v = __shfl_up(inc, d, kWave);
+                            if (lane >= d) inc += v;
+                        }
+                        for (int i = 0; i < own; ++i) ent_s[base + inc - own + i] = c | i << 16;
+                        base += __builtin_amdgcn_readlane(inc, kWave - 1);
+                    }
+                }
+                __syncthreads();
+                for (int i = tid; i < n_ent; i += kThreads) active_s[i] = ent_s[i];
+                n_act = n_ent;
             }
         }
         __syncthreads();
@@ -855,18 +877,6 @@ __global__ __launch_bounds__(kThreads) void stream_kernel(StreamArgs a, int tile
     stream_body<GATEUP, NPI, MODE, JOIN, WSPLIT, false, RAGGED>(a, tile_lds_bytes, jn, none);
 }
 
-// Batches of more than 32 tokens with widths of whole 64s in single panels and no shared experts.  If no expert has more
-// than 32 tokens, its whole B operand fits the registers and the weight rows stream past it; otherwise the kernel of
-// larger batches (wide_device.h), which reads the weights once per 32 tokens.  (64 experts of 2048 x 1408: 128 tokens,
-// routed evenly, 156 against 170 us; 64 tokens, Zipf-skewed, with further passes over the parked tile 370 against 140.)
-template <bool GATEUP, int NPI, int RB>
-__global__ __launch_bounds__(kThreads) void either_kernel(StreamArgs a, int tile_lds_bytes)
-{
-    const JoinArgs no_join = {};
-    const RouteArgs no_route = {};
-    stream_body<GATEUP, NPI, 2, false, false, false, false, RB>(a, tile_lds_bytes, no_join, no_route);
-}
-
 // The small-batch gate/up kernel with steps 1-3 of the layer in front of it (one launch less per layer, and the
 // shared experts' weights stream while the routing runs).
 template <int NPI, int MODE, bool RAGGED = false>
@@ -960,6 +970,7 @@ void fill_derived(StreamArgs &x, bool gateup, int grid)
     x.rcp_np = rcp32((unsigned)x.np);
     x.rcp_k = rcp32((unsigned)x.k);
     x.rcp_S = rcp32((unsigned)(x.k + x.n_shared));
+    x.rcp_nb = rcp32((unsigned)((x.T + 31) / 32));
 }
 // Does the launch need the RAGGED instances?  (On widths that both can take those measured 2 to 12 % slower per layer,
 // from the masks and the longer index arithmetic: 64 experts T = 9 70.6 against 66.9 us, T = 17 127.8 against 125.1,
@@ -972,17 +983,23 @@ bool stream_ragged(const StreamArgs &x, bool gateup)
 }
 }  // namespace
 
-static hipError_t launch_either(const StreamArgs &a, bool gateup, int npi, int tile_lds_bytes, size_t lds, hipStream_t s)
+// Batches of more than 32 tokens (use_stream_large() true: single panels of whole 64s).  An expert with more tokens than
+// the 32 whose B operand the registers hold is several entries of the item list, one for each 32 tokens (a shared expert has
+// all tokens); their weights are streamed once for each, the later times largely from the last-level cache.  Nothing
+// but the item list depends on the other experts' tokens.  Against the kernel with both operands in LDS (wide_device.h), 64 experts of
+// 2048 x 1408, us per layer: 128 tokens 155 | 170; 256 tokens (a mean of 24 an expert) 191 | 217; 512 tokens 347 | 367; 1000 tokens
+// 690 | 675; Zipf-skewed 64 tokens 134 | 143, 128 tokens 181 | 189, 256 tokens 263 | 271; one shared expert, 33 tokens 147 | 159.
+static hipError_t launch_large(const StreamArgs &a, bool gateup, int npi, int tile_lds_bytes, size_t lds, hipStream_t s)
 {
-    if (a.n_shared > 0 || (size_t)a.T * a.k > (size_t)kWideTokCap || stream_ragged(a, gateup) || a.K != a.KP) return hipErrorInvalidValue;
-#define MOE_EITHER_FN(GU, N) {(const void *)either_kernel<GU, N, 2>, (const void *)either_kernel<GU, N, 4>}
-    static const void *const fns[2][4][2] = {
-        {MOE_EITHER_FN(false, 1), MOE_EITHER_FN(false, 2), MOE_EITHER_FN(false, 3), MOE_EITHER_FN(false, 4)},
-        {MOE_EITHER_FN(true, 1), MOE_EITHER_FN(true, 2), MOE_EITHER_FN(true, 3), MOE_EITHER_FN(true, 4)}};
-#undef MOE_EITHER_FN
-    const void *fn = fns[gateup ? 1 : 0][npi - 1][wide_tall(a, gateup) ? 1 : 0];
-    const size_t lds_wide = wide_lds_bytes(a.T, a.k, a.C, 0);
-    lds = lds > lds_wide ? lds : lds_wide;
+    if ((size_t)a.T * a.k > (size_t)kLargeListCap || stream_ragged(a, gateup) || a.K != a.KP || (a.n_shared > 0 && a.K_sh != a.KP_sh))
+        return hipErrorInvalidValue;
+    static const void *const fns[2][4] = {
+        {(const void *)stream_kernel<false, 1, 2, false>, (const void *)stream_kernel<false, 2, 2, false>,
+         (const void *)stream_kernel<false, 3, 2, false>, (const void *)stream_kernel<false, 4, 2, false>},
+        {(const void *)stream_kernel<true, 1, 2, false>, (const void *)stream_kernel<true, 2, 2, false>,
+         (const void *)stream_kernel<true, 3, 2, false>, (const void *)stream_kernel<true, 4, 2, false>}};
+    const void *fn = fns[gateup ? 1 : 0][npi - 1];
+    lds += (size_t)stream_more_entries(a.T, a.k) * 4;
     if (lds > (size_t)kLdsBytes) return hipErrorInvalidValue;
     hipError_t e = allow_full_lds(fn);
     if (e != hipSuccess) return e;
@@ -990,7 +1007,8 @@ static hipError_t launch_either(const StreamArgs &a, bool gateup, int npi, int t
     if (e != hipSuccess) return e;
     StreamArgs args = a;
     fill_derived(args, gateup, grid);
-    void *params[] = {&args, &tile_lds_bytes};
+    JoinArgs jargs = {};
+    void *params[] = {&args, &tile_lds_bytes, &jargs};
     e = launch_timed(fn, dim3(grid), dim3(kThreads), params, lds, s, gateup ? 2 : 4);
     return e != hipSuccess ? e : hipGetLastError();
 }
@@ -1003,7 +1021,7 @@ hipError_t launch_stream(const StreamArgs &a, bool gateup, const JoinArgs *join,
     const size_t lds = stream_lds_need(kp_max, a.T, a.k, a.C, gateup);
     if (lds > (size_t)kLdsBytes) return hipErrorInvalidValue;
     const int npi = ((kp_max + 63) / 64 * 2 + kWaves - 1) / kWaves;   // 1..4 pieces per wavefront and tile
-    if (a.T > 32) return launch_either(a, gateup, npi, (int)tile, lds, s);
+    if (a.T > 32) return launch_large(a, gateup, npi, (int)tile, lds, s);
     const int mode = a.T > 16 ? 1 : 0;
 #define MOE_STREAM_FN(GU, N) {(const void *)stream_kernel<GU, N, 0, false>, (const void *)stream_kernel<GU, N, 1, false>}
 #define MOE_JOIN_FN(N) {(const void *)stream_kernel<false, N, 0, true>, (const void *)stream_kernel<false, N, 1, true>}
