@@ -336,7 +336,7 @@ namespace {
 int run_ffn(const void *hidden, const float *topk_w, const void *w_gate, const void *w_up, const void *w_down,
             const void *sh_gate, const void *sh_up, const void *sh_down, int T, int H, int F, int k, int C,
             int n_shared, int F_shared, const WsLayout &w, char *ws, void *out, int out_bf16, int accumulate,
-            hipStream_t s, bool wide, const RouteArgs *routing = nullptr, bool one_launch = false,
+            hipStream_t s, bool wide, bool may_wait, const RouteArgs *routing = nullptr, bool one_launch = false,
             int32_t *miss_count = nullptr)
 {
     // (the caller's routing / list kernel has given this call its number in the control block)
@@ -392,7 +392,7 @@ int run_ffn(const void *hidden, const float *topk_w, const void *w_gate, const v
         d.out = ws + w.o; d.out_sh = ws + w.o_sh;
         d.R = H; d.K = F; d.R_sh = H; d.K_sh = F_shared;
         d.KP = panel(F); d.KP_sh = n_shared ? panel(F_shared) : 0;
-        if (!wide && stream_can_join(d)) {
+        if (!wide && may_wait && stream_can_join(d)) {
             // small batch: the down kernel also sums the per-assignment outputs into `out`
             JoinArgs j = {};
             j.topk_w = topk_w; j.pos = pos; j.out = out;
@@ -447,8 +447,10 @@ extern "C" int moe_grouped_ffn(const void *hidden, const float *topk_w, const in
                                            (unsigned *)(ws + w.ctrl) + kCtrlBlocks,
                                            (unsigned *)(ws + w.ctrl) + kCtrlEpoch, s);
     if (e != hipSuccess) return launch_failed(e);
+    // Widths that are not whole 64s: no launch of the call waits for another of its workgroups (the final sum is a launch
+    // of its own), so that such calls may run at the same time on several streams.
     return run_ffn(hidden, topk_w, w_gate, w_up, w_down, nullptr, nullptr, nullptr, T, H, F, k, C, 0, 0, w, ws,
-                   out, out_bf16, accumulate, s, w.wide);
+                   out, out_bf16, accumulate, s, w.wide, use_stream64(T, k, C, H, F, 0, 0));
 }
 
 namespace {
@@ -519,13 +521,13 @@ int run_layer(const moe_shape_t *sh, const void *hidden, const float *router_w, 
     if (form == MOE_LAUNCH_ONE || form == MOE_LAUNCH_TWO) {
         r.lists_pub = (unsigned long long *)(ws + w.lists_pub);
         return run_ffn(hidden, topk_w, w_gate, w_up, w_down, shared_gate, shared_up, shared_down, sh->T, sh->H,
-                       sh->F, sh->k, sh->C, n_sh, F_sh, w, ws, out, out_bf16, accumulate, s, false, &r,
+                       sh->F, sh->k, sh->C, n_sh, F_sh, w, ws, out, out_bf16, accumulate, s, false, true, &r,
                        form == MOE_LAUNCH_ONE, miss_count);
     }
     hipError_t e = launch_route(r, s);
     if (e != hipSuccess) return launch_failed(e);
     return run_ffn(hidden, topk_w, w_gate, w_up, w_down, shared_gate, shared_up, shared_down, sh->T, sh->H,
-                   sh->F, sh->k, sh->C, n_sh, F_sh, w, ws, out, out_bf16, accumulate, s, wide, nullptr,
+                   sh->F, sh->k, sh->C, n_sh, F_sh, w, ws, out, out_bf16, accumulate, s, wide, true, nullptr,
                    form == MOE_LAUNCH_ROUTE_PLUS_ONE, miss_count);
 }
 

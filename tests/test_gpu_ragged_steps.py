@@ -1,0 +1,41 @@
+"""moe_grouped_ffn on widths that are multiples of 8 only, batches of up to 32 tokens, with lists of the caller's own."""
+import pytest
+import torch
+
+from paper_2603_09983_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(T, H, F, k, C, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    n = lambda *s, std=1.0: (torch.randn(*s, device="cuda", generator=g) * std).bfloat16()
+    return g, n(T, H), (n(C, F, H, std=0.1), n(C, F, H, std=0.1), n(C, H, F, std=0.1)), torch.rand(T, k, device="cuda", generator=g)
+
+
+def _check(out, x, wts, w, slot):
+    ref = torch.zeros(out.shape, dtype=torch.float64, device="cuda")
+    for c in range(wts[0].shape[0]):
+        t, j = (slot == c).nonzero(as_tuple=True)
+        if t.numel():
+            a = x[t].double() @ wts[0][c].double().T
+            y = (a * torch.sigmoid(a) * (x[t].double() @ wts[1][c].double().T)) @ wts[2][c].double().T
+            ref.index_add_(0, t, w[t, j, None].double() * y)
+    # (activations rounded to bf16: 2^-9 of each; a wrong list entry is off by about rms)
+    assert (out.double() - ref).abs().max() <= 2e-2 * max(ref.square().mean().sqrt(), ref.abs().max() * 0.25)
+
+
+@pytest.mark.parametrize("T,H,F", [(7, 72, 200), (16, 1000, 72), (29, 136, 2056)])
+def test_no_launch_waits_for_another_workgroup(T, H, F):
+    """With a poll limit of 8 and a skew of the stamps no wait inside a launch finds its entry: a call without such waits
+    does not notice."""
+    k, C = 3, 6
+    g, x, wts, w = _case(T, H, F, k, C, T)
+    slot = torch.rand(T, C, device="cuda", generator=g).argsort(1)[:, :k].int().contiguous()
+    ws = B.new_workspace(B.make_shape(T, H, C, k, F, C))
+    out = torch.empty(T, H, device="cuda")
+    print(f"[case] no wait {T} {H} {F}", flush=True)
+    B.moe_workspace_wait_test(ws, 8, 1)
+    B.moe_grouped_ffn(x, w, slot, *wts, T, H, F, k, C, out, False, False, ws)
+    assert B.moe_workspace_status(ws, check=False) == B.OK
+    _check(out, x, wts, w, slot)
