@@ -323,7 +323,7 @@ extern "C" int moe_slot_resolve(const int32_t *topk_idx, const int32_t *slot_tab
                                   (int32_t *)(ws + w.slot_count), (int32_t *)(ws + w.slot_offset),
                                   (int32_t *)(ws + w.perm), (int32_t *)(ws + w.pos),
                                   (int32_t *)(ws + w.active), (unsigned *)(ws + w.ctrl) + kCtrlNActive,
-                                  (unsigned *)(ws + w.ctrl) + kCtrlBlocks, (hipStream_t)stream);
+                                  (unsigned *)(ws + w.ctrl) + kCtrlBlocks, stream_block(T), (hipStream_t)stream);
     return e == hipSuccess ? MOE_OK : launch_failed(e);
 }
 
@@ -336,7 +336,7 @@ namespace {
 int run_ffn(const void *hidden, const float *topk_w, const void *w_gate, const void *w_up, const void *w_down,
             const void *sh_gate, const void *sh_up, const void *sh_down, int T, int H, int F, int k, int C,
             int n_shared, int F_shared, const WsLayout &w, char *ws, void *out, int out_bf16, int accumulate,
-            hipStream_t s, bool wide, bool may_wait, const RouteArgs *routing = nullptr, bool one_launch = false,
+            hipStream_t s, bool wide, bool may_wait, bool own_lists, const RouteArgs *routing = nullptr, bool one_launch = false,
             int32_t *miss_count = nullptr)
 {
     // (the caller's routing / list kernel has given this call its number in the control block)
@@ -378,7 +378,8 @@ int run_ffn(const void *hidden, const float *topk_w, const void *w_gate, const v
         g.slot_count = slot_count; g.slot_offset = slot_offset; g.perm = perm;
         g.active_slots = (const int32_t *)(ws + w.active);
         g.n_active = (const unsigned *)(ws + w.ctrl) + kCtrlNActive;
-        g.n_blocks = (const unsigned *)(ws + w.ctrl) + kCtrlBlocks;
+        // (up to 32 tokens only a caller's own lists can be longer than a pass over the weights takes)
+        g.n_blocks = T > 32 || own_lists ? (const unsigned *)(ws + w.ctrl) + kCtrlBlocks : nullptr;
         g.T = T; g.k = k; g.C = C;
         g.R = F; g.K = H; g.R_sh = F_shared; g.K_sh = H; g.n_shared = n_shared;
         g.KP = g.KP_sh = panel(H);
@@ -444,13 +445,13 @@ extern "C" int moe_grouped_ffn(const void *hidden, const float *topk_w, const in
                                            (int32_t *)(ws + w.slot_offset), (int32_t *)(ws + w.perm),
                                            (int32_t *)(ws + w.pos), (int32_t *)(ws + w.active),
                                            (unsigned *)(ws + w.ctrl) + kCtrlNActive,
-                                           (unsigned *)(ws + w.ctrl) + kCtrlBlocks,
+                                           (unsigned *)(ws + w.ctrl) + kCtrlBlocks, stream_block(T),
                                            (unsigned *)(ws + w.ctrl) + kCtrlEpoch, s);
     if (e != hipSuccess) return launch_failed(e);
     // Widths that are not whole 64s: no launch of the call waits for another of its workgroups (the final sum is a launch
     // of its own), so that such calls may run at the same time on several streams.
     return run_ffn(hidden, topk_w, w_gate, w_up, w_down, nullptr, nullptr, nullptr, T, H, F, k, C, 0, 0, w, ws,
-                   out, out_bf16, accumulate, s, w.wide, use_stream64(T, k, C, H, F, 0, 0));
+                   out, out_bf16, accumulate, s, w.wide, use_stream64(T, k, C, H, F, 0, 0), true);
 }
 
 namespace {
@@ -521,13 +522,13 @@ int run_layer(const moe_shape_t *sh, const void *hidden, const float *router_w, 
     if (form == MOE_LAUNCH_ONE || form == MOE_LAUNCH_TWO) {
         r.lists_pub = (unsigned long long *)(ws + w.lists_pub);
         return run_ffn(hidden, topk_w, w_gate, w_up, w_down, shared_gate, shared_up, shared_down, sh->T, sh->H,
-                       sh->F, sh->k, sh->C, n_sh, F_sh, w, ws, out, out_bf16, accumulate, s, false, true, &r,
+                       sh->F, sh->k, sh->C, n_sh, F_sh, w, ws, out, out_bf16, accumulate, s, false, true, false, &r,
                        form == MOE_LAUNCH_ONE, miss_count);
     }
     hipError_t e = launch_route(r, s);
     if (e != hipSuccess) return launch_failed(e);
     return run_ffn(hidden, topk_w, w_gate, w_up, w_down, shared_gate, shared_up, shared_down, sh->T, sh->H,
-                   sh->F, sh->k, sh->C, n_sh, F_sh, w, ws, out, out_bf16, accumulate, s, wide, true, nullptr,
+                   sh->F, sh->k, sh->C, n_sh, F_sh, w, ws, out, out_bf16, accumulate, s, wide, true, false, nullptr,
                    form == MOE_LAUNCH_ROUTE_PLUS_ONE, miss_count);
 }
 

@@ -50,18 +50,21 @@ static inline bool use_stream64(int T, int k, int C, int H, int F, int n_shared,
            stream_lds_need(kp_f > kp_s ? kp_f : kp_s, T, k, C, false) <= (size_t)kLdsBytes;
 }
 
+// Tokens of an expert that one pass of the streaming kernels holds, and the entries of their item list beyond one for each
+// slot when a list's blocks of so many tokens are entries of their own.
+__host__ __device__ static inline int stream_block(int T) { return T > 16 ? 32 : 16; }
+__host__ __device__ static inline int stream_more_entries(int T, int k) { return T * k / stream_block(T); }
+
 // ... and batches of up to 32 tokens of any width (multiples of 8) in the RAGGED instances.
 static inline bool use_stream_kernels(int T, int k, int C, int H, int F, int n_shared, int F_shared)
 {
     if (use_stream64(T, k, C, H, F, n_shared, F_shared)) return true;
     if (T > 32 || H < 8 || F < 8 || H % 8 != 0 || F % 8 != 0 || (n_shared > 0 && (F_shared < 8 || F_shared % 8 != 0))) return false;
     const int kp_f = stream_panel(F), kp_s = n_shared > 0 ? stream_panel(F_shared) : 0;
-    return stream_lds_need(stream_panel(H), T, k, C, true) <= (size_t)kLdsBytes &&
-           stream_lds_need(kp_f > kp_s ? kp_f : kp_s, T, k, C, false) <= (size_t)kLdsBytes;
+    const size_t more = (size_t)stream_more_entries(T, k) * 4;
+    return stream_lds_need(stream_panel(H), T, k, C, true) + more <= (size_t)kLdsBytes &&
+           stream_lds_need(kp_f > kp_s ? kp_f : kp_s, T, k, C, false) + more <= (size_t)kLdsBytes;
 }
-
-// entries of the item list beyond one for each slot when an expert's 32-token blocks are entries of their own
-__host__ __device__ static inline int stream_more_entries(int T, int k) { return T * k / 32; }
 
 // Batches of more than 32 tokens in the streaming kernels: single panels of whole 64s, lists of up to kLargeListCap entries
 // (beyond, with a mean of a hundred tokens an expert, the larger-batch kernels are the faster ones; launch_large has the figures).
@@ -138,7 +141,7 @@ constexpr int kCtrlEpoch = 3;     // routing calls completed on this workspace (
 constexpr int kCtrlSpin = 4;      // polls before a wait gives up (0 = the built-in bound)
 constexpr int kCtrlSkew = 5;      // added to the call number that producers stamp their entries with (0)
 constexpr int kCtrlLayout = 6;    // hash of the layout the workspace has been used with since it was initialised (0: none yet)
-constexpr int kCtrlBlocks = 7;    // blocks of 32 tokens (the last one of a list may be short) that the slots' lists consist of
+constexpr int kCtrlBlocks = 7;    // blocks of stream_block(T) tokens (a list's last one may be short) that the slots' lists consist of
 constexpr unsigned kErrWait = 1u, kErrLayout = 2u;   // bits of the error word
 
 // The first kernel of a call: the workspace serves one layout between two initialisations (a region that held
@@ -259,7 +262,7 @@ struct RouteArgs {
     int32_t *pos;              // [T*k]
     int32_t *active_slots;     // [C] slots with at least one token, ascending
     unsigned *n_active;        // [1]
-    unsigned *n_blocks;        // [1] blocks of 32 tokens that the slots' lists consist of
+    unsigned *n_blocks;        // [1] blocks of stream_block(T) tokens that the slots' lists consist of
     unsigned *error_flag;      // control word set when a bounded wait inside a kernel ran out
     unsigned long long *tagged_logits;   // [T*E] (tag << 32 | value bits)
     unsigned long long *tagged_idx;      // [T*k] (tag << 32 | expert id), batches above 16 tokens
@@ -276,7 +279,7 @@ struct StreamArgs {
     void *out, *out_sh;        // gate/up: act, act_sh (bf16); down: o [A,H], o_sh [n_shared,T,H] (fp32)
     const int32_t *slot_count, *slot_offset, *perm, *active_slots;
     const unsigned *n_active;
-    const unsigned *n_blocks;     // blocks of 32 tokens that the slots' lists consist of (read for batches of more than 32)
+    const unsigned *n_blocks;     // blocks of stream_block(T) tokens that the slots' lists consist of; null: as many as active slots
     int T, k;
     int R, K, R_sh, K_sh, n_shared, C;
     int KP, KP_sh;             // panel widths (columns parked in LDS at a time)
@@ -352,12 +355,13 @@ hipError_t launch_histogram(const int32_t *topk_idx, int A, int E, int32_t *hist
 hipError_t launch_resolve(const int32_t *topk_idx, const int32_t *slot_table, int A, int E, int C,
                           int32_t *slot_idx, int32_t *miss_list, int32_t *miss_count, int32_t *slot_count,
                           int32_t *slot_offset, int32_t *perm, int32_t *pos, int32_t *active_slots,
-                          unsigned *n_active, unsigned *n_blocks, hipStream_t s);
+                          unsigned *n_active, unsigned *n_blocks, int block, hipStream_t s);
 // (epoch: control word stepped by one, so that the FFN kernels of this call have a number of their own)
-// (layout: hash of the workspace layout of this call, checked against the one the workspace has served so far)
+// (layout: hash of the workspace layout of this call, checked against the one the workspace has served so far; block: tokens
+// of a block as n_blocks counts them)
 hipError_t launch_lists_from_slots(unsigned layout, const int32_t *slot_idx, int A, int C, int32_t *slot_count,
                                    int32_t *slot_offset, int32_t *perm, int32_t *pos, int32_t *active_slots,
-                                   unsigned *n_active, unsigned *n_blocks, unsigned *epoch, hipStream_t s);
+                                   unsigned *n_active, unsigned *n_blocks, int block, unsigned *epoch, hipStream_t s);
 // join != null (down kernel only, stream_can_join() true): outputs leave as stamped 64-bit entries
 // and the kernel ends with the weighted sum into `out`; no combine launch is needed then
 hipError_t launch_stream(const StreamArgs &a, bool gateup, const JoinArgs *join, hipStream_t s);

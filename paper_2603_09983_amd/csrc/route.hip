@@ -147,11 +147,11 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs a)
         // ids and slot table are read through LDS-typed pointers when they are in LDS (the usual case)
         if (idx_in_lds)
             block_post(L.idx_s, L.tab_s, A, E, a.C, a.hist, a.slot_idx, a.miss_list, a.miss_count, a.slot_count,
-                       a.slot_offset, a.perm, a.pos, a.active_slots, a.n_active, a.n_blocks, L.hist_s, L.cnt_s, L.off_s,
+                       a.slot_offset, a.perm, a.pos, a.active_slots, a.n_active, a.n_blocks, stream_block(T), L.hist_s, L.cnt_s, L.off_s,
                        L.scan_s, L.sidx_s);
         else
             block_post(idx, L.tab_s, A, E, a.C, a.hist, a.slot_idx, a.miss_list, a.miss_count, a.slot_count,
-                       a.slot_offset, a.perm, a.pos, a.active_slots, a.n_active, a.n_blocks, L.hist_s, L.cnt_s, L.off_s,
+                       a.slot_offset, a.perm, a.pos, a.active_slots, a.n_active, a.n_blocks, stream_block(T), L.hist_s, L.cnt_s, L.off_s,
                        L.scan_s, L.sidx_s);
     } else if (a.hist) {
         block_histogram(idx, A, E, a.hist, L.hist_s);
@@ -199,13 +199,13 @@ __global__ __launch_bounds__(kRouteThreads) void resolve_kernel(const int32_t *i
                                                                  int32_t *slot_count, int32_t *slot_offset,
                                                                  int32_t *perm, int32_t *pos,
                                                                  int32_t *active_slots, unsigned *n_active,
-                                                                 unsigned *n_blocks, unsigned *epoch, unsigned layout)
+                                                                 unsigned *n_blocks, int block, unsigned *epoch, unsigned layout)
 {
     extern __shared__ int dyn[];
     if (epoch && threadIdx.x == 0) check_layout(epoch - kCtrlEpoch, layout);
     PostLds L = carve_lds(dyn, 0, C, A);
     block_post(idx, slot_table, A, E, C, nullptr, slot_idx, miss_list, miss_count, slot_count, slot_offset,
-               perm, pos, active_slots, n_active, n_blocks, L.hist_s, L.cnt_s, L.off_s, L.scan_s, L.sidx_s);
+               perm, pos, active_slots, n_active, n_blocks, block, L.hist_s, L.cnt_s, L.off_s, L.scan_s, L.sidx_s);
     if (epoch && threadIdx.x == 0) *epoch += 1u;   // the kernels that follow stamp their entries with this number
 }
 
@@ -251,7 +251,7 @@ hipError_t launch_histogram(const int32_t *topk_idx, int A, int E, int32_t *hist
 hipError_t launch_resolve(const int32_t *topk_idx, const int32_t *slot_table, int A, int E, int C,
                           int32_t *slot_idx, int32_t *miss_list, int32_t *miss_count, int32_t *slot_count,
                           int32_t *slot_offset, int32_t *perm, int32_t *pos, int32_t *active_slots,
-                          unsigned *n_active, unsigned *n_blocks, hipStream_t s)
+                          unsigned *n_active, unsigned *n_blocks, int block, hipStream_t s)
 {
     size_t lds = post_lds_bytes(0, C, A, false);
     if (lds > (size_t)kLdsBytes - 1024) return hipErrorInvalidValue;
@@ -259,13 +259,13 @@ hipError_t launch_resolve(const int32_t *topk_idx, const int32_t *slot_table, in
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(kRouteThreads), lds, s, topk_idx, slot_table, A, E, C,
                        slot_idx, miss_list, miss_count, slot_count, slot_offset, perm, pos, active_slots,
-                       n_active, n_blocks, (unsigned *)nullptr, 0u);
+                       n_active, n_blocks, block, (unsigned *)nullptr, 0u);
     return hipGetLastError();
 }
 
 hipError_t launch_lists_from_slots(unsigned layout, const int32_t *slot_idx, int A, int C, int32_t *slot_count,
                                    int32_t *slot_offset, int32_t *perm, int32_t *pos, int32_t *active_slots,
-                                   unsigned *n_active, unsigned *n_blocks, unsigned *epoch, hipStream_t s)
+                                   unsigned *n_active, unsigned *n_blocks, int block, unsigned *epoch, hipStream_t s)
 {
     size_t lds = post_lds_bytes(0, C, A, false);
     if (lds > (size_t)kLdsBytes - 1024) return hipErrorInvalidValue;
@@ -275,7 +275,7 @@ hipError_t launch_lists_from_slots(unsigned layout, const int32_t *slot_idx, int
     hipLaunchKernelGGL(resolve_kernel, dim3(1), dim3(kRouteThreads), lds, s, (const int32_t *)nullptr,
                        (const int32_t *)nullptr, A, 0, C, const_cast<int32_t *>(slot_idx),
                        (int32_t *)nullptr, (int32_t *)nullptr, slot_count, slot_offset, perm, pos,
-                       active_slots, n_active, n_blocks, epoch, layout);
+                       active_slots, n_active, n_blocks, block, epoch, layout);
     prof_end(1, s);
     return hipGetLastError();
 }

@@ -158,6 +158,7 @@ __device__ void block_histogram(const int32_t *idx, int A, int E, int32_t *hist,
 // Histogram (optional), slot lookup, ascending miss list, per-slot assignment lists and the
 // list of active slots, by one workgroup.  idx / slot_table may point to LDS copies.
 //   hist == nullptr: no histogram.   slot_table == nullptr: slot_idx is an input (lists only).
+//   block: 16 or 32, the tokens of a block as n_blocks counts them.
 // LDS: hist_s[E], cnt_s[kRouteWaves][C], off_s[C+1], scan_s[48], sidx_s[min(A, kLdsCopy)].
 //
 // A stable counting sort in blocks of one assignment per thread.  Inside a wavefront the lanes of one slot find
@@ -169,7 +170,7 @@ template <typename IdxPtr, typename TabPtr>
 __device__ void block_post(IdxPtr idx, TabPtr slot_table, int A, int E, int C, int32_t *hist,
                            int32_t *slot_idx, int32_t *miss_list, int32_t *miss_count, int32_t *slot_count,
                            int32_t *slot_offset, int32_t *perm, int32_t *pos, int32_t *active_slots,
-                           unsigned *n_active, unsigned *n_blocks, lds_i32 *hist_s, lds_i32 *cnt_s, lds_i32 *off_s, lds_i32 *scan_s,
+                           unsigned *n_active, unsigned *n_blocks, int block, lds_i32 *hist_s, lds_i32 *cnt_s, lds_i32 *off_s, lds_i32 *scan_s,
                            lds_i32 *sidx_s)
 {
     static_assert(kMaxC <= kRouteThreads && kMaxC <= 1 << 10, "one thread per slot; ten bits of slot id");
@@ -252,7 +253,7 @@ __device__ void block_post(IdxPtr idx, TabPtr slot_table, int A, int E, int C, i
         if (lane >= d) inc_o += v;
     }
     const unsigned long long act = __ballot(cntv > 0);
-    const unsigned blocks = wave_sum_u32((unsigned)(cntv + 31) / 32u);
+    const unsigned blocks = wave_sum_u32((unsigned)(cntv + block - 1) >> (block == 32 ? 5 : 4));
     if (lane == kWave - 1) {
         scan_s[w] = (int)blocks;   // (the misses' counts are no longer needed)
         scan_s[16 + w] = inc_o;
@@ -395,7 +396,7 @@ __device__ __forceinline__ SmallLists block_post_small(lds_i32 *idx_s, lds_i32 *
     const int inc_a = __popcll(__ballot(cntv > 0) & upto);
     int inc_o = 0;
     for (int bit = 0; (1 << bit) <= T; ++bit) inc_o += __popcll(__ballot((cntv >> bit) & 1) & upto) << bit;
-    const unsigned blocks = BLOCKS ? wave_sum_u32((unsigned)(cntv + 31) / 32u) : 0u;
+    const unsigned blocks = BLOCKS ? wave_sum_u32((unsigned)(cntv + stream_block(T) - 1) >> (T > 16 ? 5 : 4)) : 0u;
     if (lane == kWave - 1) {
         scan_s[16 + w] = inc_o;
         scan_s[32 + w] = BLOCKS ? inc_a | (int)blocks << 16 : inc_a;

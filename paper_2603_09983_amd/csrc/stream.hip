@@ -121,13 +121,17 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     // (the arithmetic is free), so the B operand never changes and no expert change stalls the
     // stream; the expert's own tokens are picked out when the results are stored.
     constexpr bool ALLTOK = GATEUP && MODE == 1;
+    // An entry of the item list may be one of several blocks of kTok tokens of an expert: with more than 32 tokens, and where
+    // the lists are a caller's own, in which a token may name a slot several times (slot | block << 16 in active_s).
+    constexpr bool BLOCKS = MODE == 2 || (RAGGED && !JOIN && !FUSED);
+    constexpr int kTok = 16 * NG;
 
     extern __shared__ __align__(16) unsigned char lds[];
     unsigned char *tile_s = lds;
     float *red_s = (float *)(lds + tile_lds_bytes);                   // [group][wavefront][lane][4]
     int *ctl_s = (int *)(lds + tile_lds_bytes + NG * kWaves * kWave * 16);
     int *count_s = ctl_s, *offset_s = ctl_s + a.C, *active_s = ctl_s + 2 * a.C;
-    int *perm_s = active_s + a.C + (MODE == 2 ? stream_more_entries(a.T, a.k) : 0);
+    int *perm_s = active_s + a.C + (BLOCKS ? stream_more_entries(a.T, a.k) : 0);
     float *out_s = (float *)(perm_s + a.T * a.k);                     // [kOutCap][NG][kOutPerItem] results waiting to be stored
     int *odesc_s = (int *)(out_s + kOutCap * NG * kOutPerItem);       // [kOutCap][8]: shared?, row of token 0, column bytes, m
 
@@ -147,7 +151,6 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     // (bytes of a tile row in LDS, and its 32-wide column blocks, for a panel row of rs bytes)
     auto lds_row = [](int rs) { return RAGGED ? ((rs + 127) & ~127) + kRowPad : rs + kRowPad; };
     auto col_blocks = [](int rs) { return RAGGED ? (rs + 63) / 64 : rs / 64; };
-    // (MODE 2: an entry of the list is an expert's block of 32 tokens: slot | block << 16 in active_s)
     const int nb_sh = MODE == 2 ? (a.T + 31) / 32 : 1;
     const int n_sh_items = a.n_shared * nb_sh * tiles_sh;
     const int sh_per = udiv_rcp(n_sh_items, G, a.rcp_G), sh_rem = n_sh_items - sh_per * G;
@@ -176,7 +179,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
             pK2 = 2 * K; prs = 2 * a.KP_sh; pnpan = a.np_sh;
         } else {
             const int K = a.K;
-            const int c = MODE == 2 ? active_s[e] & 0xffff : active_s[e];
+            const int c = BLOCKS ? active_s[e] & 0xffff : active_s[e];
             const size_t eoff = ((size_t)c * a.R + (size_t)rt * RPI) * K;
             pw0 = (const unsigned char *)(a.w0 + eoff);
             pw1 = GATEUP ? (const unsigned char *)(a.w1 + eoff) : pw0 + (size_t)16 * K;
@@ -226,9 +229,9 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
             cm = a.T - t0; ckey = ALLTOK ? 0 : e; corow0 = ex * a.T + t0;
             cbrow0 = GATEUP ? t0 : corow0;            // hidden[t0 + n] | act_sh[e][t0 + n]
         } else {
-            const int c = MODE == 2 ? active_s[e] & 0xffff : active_s[e], t0 = MODE == 2 ? (active_s[e] >> 16) * 32 : 0;
+            const int c = BLOCKS ? active_s[e] & 0xffff : active_s[e], t0 = BLOCKS ? (active_s[e] >> 16) * kTok : 0;
             cK = a.K; c_rs = 2 * a.KP; cnpan = a.np;
-            cm = count_s[c] - t0; ckey = ALLTOK ? 0 : MODE == 2 ? a.n_shared * nb_sh + e : a.n_shared + c; corow0 = offset_s[c] + t0;
+            cm = count_s[c] - t0; ckey = ALLTOK ? 0 : BLOCKS ? a.n_shared * nb_sh + e : a.n_shared + c; corow0 = offset_s[c] + t0;
             cbrow0 = ALLTOK ? 0 : GATEUP ? -1 : corow0;   // hidden[n] | hidden[token of list entry n] | act[row]
         }
     };
@@ -556,18 +559,18 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         else if (JOIN)
             for (int i = tid; i < a.T * a.k; i += kThreads) perm_s[i] = jn.pos[i];
         n_act = (int)(*a.n_active);
-        if constexpr (MODE == 2) {
+        if constexpr (BLOCKS) {
             // (asked for here, with the lists: ahead of them it would be a trip to memory of its own)
-            const int n_ent = (int)*a.n_blocks;
+            const int n_ent = a.n_blocks ? (int)*a.n_blocks : n_act;
             if (n_ent != n_act) {
-                // some experts have more than 32 tokens: as many entries as blocks
+                // some lists are longer than kTok: as many entries as blocks
                 __syncthreads();
                 int *const ent_s = (int *)red_s;   // (nobody's yet)
                 if (w == 0) {
                     int base = 0;
                     for (int e0 = 0; e0 < n_act; e0 += kWave) {
                         const int c = e0 + lane < n_act ? active_s[e0 + lane] : 0;
-                        const int own = e0 + lane < n_act ? (count_s[c] + 31) / 32 : 0;
+                        const int own = e0 + lane < n_act ? (count_s[c] + kTok - 1) / kTok : 0;
                         int inc = own;
 #pragma unroll
                         for (int d = 1; d < kWave; d <<= 1) {
@@ -1054,6 +1057,8 @@ hipError_t launch_stream(const StreamArgs &a, bool gateup, const JoinArgs *join,
 #undef MOE_RAGGED_FNS
         fn = ragged_fns[gateup ? 0 : join ? 2 : 1][npi - 1][mode];
     }
+    const size_t lds_all = lds + (stream_ragged(a, gateup) && !join ? (size_t)stream_more_entries(a.T, a.k) * 4 : 0);
+    if (lds_all > (size_t)kLdsBytes) return hipErrorInvalidValue;
     hipError_t e = allow_full_lds(fn);
     if (e != hipSuccess) return e;
     const int grid = device_cus(&e);
@@ -1064,7 +1069,7 @@ hipError_t launch_stream(const StreamArgs &a, bool gateup, const JoinArgs *join,
     JoinArgs jargs = {};
     if (join) jargs = *join;
     void *params[] = {&args, &tile_i, &jargs};
-    hipError_t le = launch_timed(fn, dim3(grid), dim3(kThreads), params, lds, s, gateup ? 2 : 4);
+    hipError_t le = launch_timed(fn, dim3(grid), dim3(kThreads), params, lds_all, s, gateup ? 2 : 4);
     if (le != hipSuccess) return le;
     return hipGetLastError();
 }

@@ -39,3 +39,18 @@ def test_no_launch_waits_for_another_workgroup(T, H, F):
     B.moe_grouped_ffn(x, w, slot, *wts, T, H, F, k, C, out, False, False, ws)
     assert B.moe_workspace_status(ws, check=False) == B.OK
     _check(out, x, wts, w, slot)
+
+
+@pytest.mark.parametrize("T,H,F,k,C", [(3, 72, 200, 20, 2), (16, 40, 72, 2, 1), (9, 2056, 24, 6, 3), (17, 72, 104, 4, 1), (32, 24, 2056, 8, 5)])
+def test_a_token_that_names_a_slot_several_times(T, H, F, k, C):
+    """Lists of more entries than the batch has tokens (and than a pass over the weights multiplies)."""
+    g, x, wts, w = _case(T, H, F, k, C, 100 + T)
+    slot = torch.randint(-1, C, (T, k), device="cuda", generator=g).int()
+    slot[: (T + 1) // 2] = C - 1
+    ws = B.new_workspace(B.make_shape(T, H, max(C, k), k, F, C))
+    out = torch.empty(T, H, device="cuda")
+    print(f"[case] repeated {T} {H} {F} {k} {C}", flush=True)
+    for _ in range(2):
+        B.moe_grouped_ffn(x, w, slot, *wts, T, H, F, k, C, out, False, False, ws)
+    B.moe_workspace_status(ws)
+    _check(out, x, wts, w, slot)
