@@ -441,17 +441,18 @@ extern "C" int moe_grouped_ffn(const void *hidden, const float *topk_w, const in
     if (!ws_choose(T, 0, k, C, H, F, 0, 0, workspace_bytes, w)) return MOE_ERR_WORKSPACE;
     char *ws = (char *)workspace;
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = launch_lists_from_slots(layout_hash(w), slot_idx, T * k, C, (int32_t *)(ws + w.slot_count),
+    // Widths that are not whole 64s: no launch of the call waits for another of its workgroups (the final sum is a launch
+    // of its own), so that such calls may run at the same time on several streams.
+    const bool may_wait = use_stream64(T, k, C, H, F, 0, 0);
+    hipError_t e = launch_lists_from_slots(layout_hash(w, w.stream && !w.wide && T <= 32 && may_wait), slot_idx, T * k, C, (int32_t *)(ws + w.slot_count),
                                            (int32_t *)(ws + w.slot_offset), (int32_t *)(ws + w.perm),
                                            (int32_t *)(ws + w.pos), (int32_t *)(ws + w.active),
                                            (unsigned *)(ws + w.ctrl) + kCtrlNActive,
                                            (unsigned *)(ws + w.ctrl) + kCtrlBlocks, stream_block(T),
                                            (unsigned *)(ws + w.ctrl) + kCtrlEpoch, s);
     if (e != hipSuccess) return launch_failed(e);
-    // Widths that are not whole 64s: no launch of the call waits for another of its workgroups (the final sum is a launch
-    // of its own), so that such calls may run at the same time on several streams.
     return run_ffn(hidden, topk_w, w_gate, w_up, w_down, nullptr, nullptr, nullptr, T, H, F, k, C, 0, 0, w, ws,
-                   out, out_bf16, accumulate, s, w.wide, use_stream64(T, k, C, H, F, 0, 0), true);
+                   out, out_bf16, accumulate, s, w.wide, may_wait, true);
 }
 
 namespace {
@@ -496,7 +497,6 @@ int run_layer(const moe_shape_t *sh, const void *hidden, const float *router_w, 
     r.epoch = (unsigned *)(ws + w.ctrl) + kCtrlEpoch;
     r.error_flag = (unsigned *)(ws + w.ctrl) + kCtrlError;
     r.topk_idx = topk_idx; r.topk_w = topk_w; r.logits_opt = nullptr; r.hist = hist;
-    r.layout = layout_hash(w);
     r.slot_table = slot_table; r.C = sh->C;
     r.slot_idx = slot_idx; r.miss_list = miss_list; r.miss_count = miss_count;
     r.slot_count = (int32_t *)(ws + w.slot_count); r.slot_offset = (int32_t *)(ws + w.slot_offset);
@@ -513,6 +513,7 @@ int run_layer(const moe_shape_t *sh, const void *hidden, const float *router_w, 
     // (the library's choice: routing inside the gate/up launch where the shape allows, one launch less per layer)
     // (the kernels of larger batches start behind the routing kernel; up to 32 tokens a named form is the streaming kernels')
     const bool wide = w.wide && (sh->T > 32 || form == MOE_LAUNCH_AUTO);
+    r.layout = layout_hash(w, w.stream && !wide && sh->T <= 32);
     if (form == MOE_LAUNCH_AUTO) form = can_route_inside && !wide ? MOE_LAUNCH_TWO : MOE_LAUNCH_THREE;
     if (form == MOE_LAUNCH_ONE && !(can_layer && can_route_inside)) return MOE_ERR_SHAPE;
     if (form == MOE_LAUNCH_ROUTE_PLUS_ONE && !can_layer) return MOE_ERR_SHAPE;

@@ -223,12 +223,13 @@ static inline size_t ws_bytes(int T, int E, int k, int C, int H, int F, int n_sh
     return own > fit ? own : fit;
 }
 
-// Non-zero hash of where the regions of a layout lie: two shapes with the same offsets keep the same kind of
-// entry in every place, and may share a workspace without a new initialisation.
-static inline unsigned layout_hash(const WsLayout &w)
+// Non-zero hash of where the regions of a layout lie and what a call keeps there (stamped: its per-assignment outputs are
+// (call number, value) entries, else plain floats): calls with the same hash keep the same kind of entry in every place, and
+// may share a workspace without a new initialisation.
+static inline unsigned layout_hash(const WsLayout &w, bool stamped)
 {
     const size_t f[] = {w.perm, w.pos, w.slot_count, w.slot_offset, w.active, w.part, w.part_sh, w.act, w.act_sh,
-                        w.o, w.o_sh, w.lists_pub, w.total};
+                        w.o, w.o_sh, w.lists_pub, w.total, stamped ? (size_t)1 : (size_t)0};
     unsigned long long h = 1469598103934665603ull;   // FNV-1a over the offsets
     for (size_t v : f)
         for (int i = 0; i < 8; ++i) {
