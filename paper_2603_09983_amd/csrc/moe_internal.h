@@ -79,12 +79,12 @@ static inline bool use_stream_large(int T, int k, int C, int H, int F, int n_sha
 }
 
 // Larger batches (wide.hip), any width that is a multiple of 8.
-size_t wide_lds_bytes(int T, int k, int C, int n_shared);
+size_t wide_lds_bytes(int T, int k, int C);
 constexpr int kWideTokCap = 6144;   // list entries whose tokens are kept in LDS
 static inline bool use_wide_kernels(int T, int k, int C, int H, int F, int n_shared, int F_shared)
 {
-    if (T <= 16 || T > 65535 || H < 8 || F < 8 || H % 8 != 0 || F % 8 != 0 || n_shared > kMaxC ||
-        (n_shared > 0 && (F_shared < 8 || F_shared % 8 != 0)) || wide_lds_bytes(T, k, C, n_shared) > (size_t)kLdsBytes)
+    if (T <= 16 || T > 65535 || H < 8 || F < 8 || H % 8 != 0 || F % 8 != 0 ||
+        (n_shared > 0 && (F_shared < 8 || F_shared % 8 != 0)) || wide_lds_bytes(T, k, C) > (size_t)kLdsBytes)
         return false;
     // Two token groups and rows of several panels: the streaming kernels reload the B operand for every tile (8 experts
     // of 4096 x 14336: 17 tokens 576 us, 32 tokens 749 us; here 445 and 446).  Two launches more have to pay, though: pools

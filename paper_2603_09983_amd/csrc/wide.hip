@@ -15,11 +15,11 @@ __global__ __launch_bounds__(wide::kThreads) void wide_kernel(StreamArgs a)
 }  // namespace
 
 static_assert((size_t)wide::kItemLds + (kMaxC + 1) * 16 + kWideTokCap * 2 <= (size_t)kLdsBytes,
-              "any number of slots without shared experts");
+              "any number of slots");
 
-size_t wide_lds_bytes(int T, int k, int C, int n_shared)
+size_t wide_lds_bytes(int T, int k, int C)
 {
-    const size_t A = (size_t)T * k, n = (size_t)n_shared + C + 1;
+    const size_t A = (size_t)T * k, n = (size_t)C + 1;
     return (size_t)wide::kItemLds + n * 16 + (A <= (size_t)wide::kTokCap ? (A * 2 + 15) / 16 * 16 : 0);
 }
 
@@ -33,7 +33,7 @@ bool wide_tall(const StreamArgs &a, bool gateup)
 
 hipError_t launch_wide(const StreamArgs &a, bool gateup, hipStream_t s)
 {
-    const size_t lds = wide_lds_bytes(a.T, a.k, a.C, a.n_shared);
+    const size_t lds = wide_lds_bytes(a.T, a.k, a.C);
     if (lds > (size_t)kLdsBytes) return hipErrorInvalidValue;
     const bool in_lds = (size_t)a.T * a.k <= (size_t)wide::kTokCap;
     const bool tall = wide_tall(a, gateup);
