@@ -103,11 +103,16 @@ def _ptr_store(t: torch.Tensor):
     return t.data_ptr()
 
 
+# torch.cuda.current_stream() makes a Stream object, 2.8 us of a call that took 7.9; the handle alone takes 0.2.  (torch has
+# these two for its own compiled code and may drop them: then the public call does.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
-        # (torch.cuda.current_stream() makes a Stream object, 2.8 us of a call that took 7.9; the handle alone takes 0.2)
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream and _current_device and torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
