@@ -128,7 +128,7 @@ constexpr int kTagIdxEntries = 4096;   // (at most as many as the routing kernel
 struct WsLayout {
     size_t ctrl, tagged, tagged_idx, perm, pos, slot_count, slot_offset, active, part, part_sh, act, act_sh, o, o_sh, total;
     bool stream;        // the streaming kernels' regions (else: those of the general kernel) ...
-    bool wide;          // ... for the kernels of more than 32 tokens
+    bool wide;          // ... for the larger-batch kernels (use_wide_kernels)
     size_t lists_pub;   // stamped copies of the per-slot lists (gate/up kernel that does the routing itself), or 0
 };
 
@@ -369,9 +369,11 @@ hipError_t launch_stream(const StreamArgs &a, bool gateup, const JoinArgs *join,
 // gate/up kernel that first does the routing steps described by `r` (use_fused_route() true, r.lists_pub set)
 hipError_t launch_stream_routed(const StreamArgs &a, const RouteArgs &r, hipStream_t s);
 bool stream_can_join(const StreamArgs &d);
-// the same two steps for batches of more than 32 tokens (use_wide_kernels() true); no final sum inside
+// the same two steps in the larger-batch kernels (use_wide_kernels() true); no final sum inside
 hipError_t launch_wide(const StreamArgs &a, bool gateup, hipStream_t s);
-// 64 weight rows to an item, or 32 where those would be less than two for every workgroup (if every slot is used)
+// 64 weight rows to an item, or 32: those cost an eighth more a row (64 tokens on 8 experts of 4096 x 14336 490 against 459 us,
+// 128 tokens 814 against 702), but spread over the workgroups in smaller steps (40 tokens on 20 experts of 1000 x 1000, 2.5 items
+// of 64 rows a workgroup: 48.4 against 50.2 us, 100 tokens of 2040 x 1000 76.1 against 82.6).  So by the time of the longest share.
 bool wide_tall(const StreamArgs &a, bool gateup);
 hipError_t launch_combine_rows(const CombineArgs &a, const float *o, const float *o_sh, hipStream_t s);
 // one-launch form (batches of up to 16 tokens): use_layer_kernel() must hold; route != null: the kernel does

@@ -25,10 +25,14 @@ size_t wide_lds_bytes(int T, int k, int C)
 
 bool wide_tall(const StreamArgs &a, bool gateup)
 {
-    const int rpi = gateup ? 32 : 64, slots = (size_t)a.C < (size_t)a.T * a.k ? a.C : a.T * a.k;
-    const long long items = (long long)(a.R + rpi - 1) / rpi * slots +
-                            (a.n_shared ? (long long)(a.R_sh + rpi - 1) / rpi * a.n_shared * ((a.T + wide::kToks - 1) / wide::kToks) : 0);
-    return items >= 2 * device_cus(nullptr);
+    const long long A = (long long)a.T * a.k, slots = a.C < A ? a.C : A, G = device_cus(nullptr);
+    const long long blocks = slots > 0 ? slots * ((A / slots + wide::kToks - 1) / wide::kToks) : 0;   // (routed evenly, every slot in use)
+    const long long blocks_sh = (long long)a.n_shared * ((a.T + wide::kToks - 1) / wide::kToks);
+    auto rounds = [&](int rpi) {
+        return ((a.R + rpi - 1) / rpi * blocks + (a.n_shared ? (a.R_sh + rpi - 1) / rpi * blocks_sh : 0) + G - 1) / (G > 0 ? G : 1);
+    };
+    const int rpi = gateup ? 32 : 64;
+    return rounds(rpi) * 2 * 88 <= rounds(rpi / 2) * 100;
 }
 
 hipError_t launch_wide(const StreamArgs &a, bool gateup, hipStream_t s)

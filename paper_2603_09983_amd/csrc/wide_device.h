@@ -1,4 +1,4 @@
-// Expert FFN of batches of more than 32 tokens (Sec. 2.2 last line, experts as in App. D):
+// Expert FFN of larger batches (use_wide_kernels(); Sec. 2.2 last line, experts as in App. D):
 //      act = silu(W_gate x) * (W_up x)        (gate/up kernel)
 //      o   = W_down act                       (down kernel)
 //
@@ -13,19 +13,16 @@
 // One workgroup of sixteen wavefronts per CU takes items b, b + G, .. and keeps three chunks in flight, across items
 // (3 x 64 KB of weights).
 //
-// The order of the sums is the streaming kernels': wavefront w multiplies columns 32 w .. 32 w + 31 of every chunk, the
-// chunks of a row in ascending order, and an item's sixteen partial results are added through LDS in wavefront order.  So a
-// token's outputs have the same bits whichever of the kernels runs (contractions of up to kPanelMax columns), whatever else
-// is in the batch and wherever the item lies in the list.  It costs an item's end two barriers and 128 KB of LDS traffic each
-// way (64 rows; with 32 rows the partial results have LDS of their own).
+// The order of the sums is fixed: four parts of the columns (128 of every chunk's 512 each, chunk after chunk), added through
+// LDS.  It follows from the row and the widths alone: a token's outputs have the same bits whatever else is in the batch,
+// wherever the item lies in the list and with 64 or 32 rows to an item.
 //
 // Rows of several panels (K > kPanelMax) start at a chunk that follows from the row: with rows of 8 KB and more all rows'
 // kilobytes of one chunk lie in few of an L2's sixteen channels, and workgroups that start together would all be in the same
-// ones (8 experts of 4096 x 14336, 24 tokens: 530 us per layer with all items starting at chunk 0, 446 us so; H = 2048: no
+// ones (8 experts of 4096 x 14336, 24 tokens: 530 us per layer with all items starting at chunk 0, 441 us so; H = 2048: no
 // difference).  What an XCD has at a time must differ in that chunk: an expert's tiles begin one XCD further on than those of
 // the expert before.  An expert with more than 32 tokens has its token blocks of a row tile eight items apart, so that they
-// read the same weights from one L2 at the same time (128 tokens on 8 experts of 4096 x 14336: 724 -> 700 us; 64 experts of
-// 2048 x 1408, Zipf-skewed, 128 tokens: 195.5 -> 189.4 us, both with neighbouring blocks before).
+// read the same weights from one L2 at the same time (128 tokens on 8 experts of 4096 x 14336: 725 us with neighbouring blocks, 715 so).
 //
 // Any width that is a multiple of 8: rows and tokens beyond the end repeat the last one and are not stored; columns
 // beyond the end of a row are zero in both operands.
@@ -46,7 +43,8 @@ constexpr int kStages = 3;                   // chunks in flight per workgroup
 constexpr int kChunkBytes = 1024;            // 512 columns
 constexpr int kRowLds = kChunkBytes + 16;    // (padding: sixteen rows' 16-byte words fall into sixteen bank groups)
 constexpr int kTokLds = kToks * kRowLds;
-constexpr int kItemLds = 64 * kRowLds + kWaves * 4 * 1024;   // tiles and partial results of an item of two row blocks; those of four share it
+constexpr int kRing = 8, kRingLds = kRing * 32;   // items between the walk that loads and the one that multiplies
+constexpr int kItemLds = 96 * kRowLds + kWaves * 2 * 1024 + kRingLds;   // tiles and partial results of an item of four row blocks; the ring
 constexpr int kTokCap = kWideTokCap;
 
 __device__ inline uint32_t f32_to_bf16_rne(float f)
@@ -76,13 +74,11 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
 {
     constexpr int RPI = GATEUP ? 8 * RB : 16 * RB;   // output rows of an item
     constexpr int kTileLds = 16 * RB * kRowLds;
-    static_assert(kChunkBytes == kWaves * 64, "a wavefront multiplies one block of 32 columns of a chunk");
-    constexpr int kPart = kWaves * RB * 2 * 1024;          // partial results of an item
-    constexpr bool OWN = kTileLds + kTokLds + kPart <= kItemLds;   // ... in LDS of their own, or in the place of the tiles
-    static_assert(OWN || (kPart <= kItemLds && kTileLds + kTokLds <= kItemLds), "the item's LDS");
+    constexpr int GW = RB / 2;                       // token groups that a wavefront multiplies (with two row blocks each group has its own)
+    static_assert((RB == 2 || RB == 4) && kTileLds + kTokLds + kWaves * GW * 1024 + kRingLds <= kItemLds, "wavefronts; the item's LDS");
     extern __shared__ __align__(16) unsigned char lds[];
     unsigned char *const a_s = lds, *const b_s = lds + kTileLds;
-    float *const part_s = (float *)(lds + (OWN ? kTileLds + kTokLds : 0));   // [token group][wavefront][row block][256] partial results
+    float *const part_s = (float *)(lds + kTileLds + kTokLds);   // [wavefront][its token group][256] partial results
     const int A = a.T * a.k, n_cap = a.C + 1;
     int *const first_s = (int *)(lds + kItemLds);   // [active slot] its first item
     int *const m_s = first_s + n_cap, *const off_s = m_s + n_cap, *const slot_s = off_s + n_cap;
@@ -94,6 +90,7 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
     const int n_act = (int)*a.n_active;
     const int tiles = (a.R + RPI - 1) / RPI, tiles_sh = a.n_shared ? (a.R_sh + RPI - 1) / RPI : 0;
     const int nb_sh = (a.T + kToks - 1) / kToks, sh_items = a.n_shared * tiles_sh * nb_sh;   // (the shared experts' items come first)
+    const unsigned rcp_sh = sh_items ? rcp32((unsigned)(tiles_sh * nb_sh)) : 0u;
 
     if (GATEUP && TOK_LDS)
         for (int i = tid; i < A; i += kThreads) tok_s[i] = (uint16_t)udiv_rcp(a.perm[i], a.k, a.rcp_k);
@@ -134,7 +131,7 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
         int e, rem, nb, tl;
         it.sh = i < sh_items;
         if (it.sh) {
-            e = i / (tiles_sh * nb_sh);
+            e = udiv_rcp(i, tiles_sh * nb_sh, rcp_sh);
             rem = i - e * (tiles_sh * nb_sh);
             nb = nb_sh; tl = tiles_sh;
             it.m = a.T; it.off = e * a.T; it.slot = e;
@@ -151,9 +148,10 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
         }
         int rt = rem, tb = 0;
         if (nb > 1) {
-            const int q = rem / (8 * nb), r8 = rem - q * (8 * nb), gs = tl - 8 * q < 8 ? tl - 8 * q : 8;
-            tb = r8 / gs;
-            rt = 8 * q + r8 - tb * gs;
+            // eight row tiles by nb blocks at a time; the tiles that are left (fewer than eight) have their blocks as neighbours
+            const int whole = (tl & ~7) * nb, y = rem < whole ? rem >> 3 : rem - whole, d = y / nb;
+            tb = y - d * nb;
+            rt = rem < whole ? 8 * d + (rem & 7) : (tl & ~7) + d;
         }
         if (tl >= 8) {
             rt += e & 7;
@@ -166,9 +164,20 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
 
     // ---- the walk that loads: chunk pc of item pi is the next one to put in flight ----
     const unsigned char *pa[RB], *pb[2];   // this wavefront's weight rows (one of each block) and token rows
+    // (The walk that multiplies follows three chunks behind and takes the items from a ring in LDS: at most four are under
+    // way, and a place is written again several barriers after it was read.)
+    int *const ring_s = (int *)(lds + kItemLds - kRingLds);
+    int pord = 0;
+    auto prod_put = [&](const Item &it) {
+        if (tid == 0) {
+            int *const r = ring_s + (pord & (kRing - 1)) * 8;
+            r[0] = it.sh; r[1] = it.row0; r[2] = it.tok0; r[3] = it.m; r[4] = it.off;
+        }
+        ++pord;
+    };
     int pi = b, pc = 0, pK2 = 0, pn = 0, prot = 0;   // (an item's chunks in turn from chunk prot on)
-    auto prod_set = [&](int i) {
-        const Item it = decode(i);
+    auto prod_set = [&](const Item &it) {
+        prod_put(it);
         const bool sh = it.sh;
         const int K = sh ? a.K_sh : a.K, R = sh ? a.R_sh : a.R;
         const int m = it.m, off = it.off;
@@ -216,7 +225,7 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
             ++pc;
         } else if (pi + G < total) {
             pi += G;
-            prod_set(pi);
+            prod_set(decode(pi));
         }   // (past the last item: its last chunk again, which nobody multiplies)
     };
     auto park = [&](int s) {
@@ -238,7 +247,7 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
     };
 
     // ---- the walk that multiplies ----
-    int ci = b, cc = 0;
+    int ci = b, cc = 0, cord = 0;
     Item it = decode(ci);
     int cm = 0, cn = 0;
     auto cons_set = [&]() {
@@ -246,55 +255,44 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
         cn = (2 * (it.sh ? a.K_sh : a.K) + kChunkBytes - 1) / kChunkBytes;
         cc = 0;
     };
-    // Wavefront w multiplies columns 32 w .. 32 w + 31 of every chunk, all row blocks and token groups of the item.
-    f32x4 acc[RB][2];
+    // Wavefront w multiplies row block w % RB by GW token groups, the column part kq = w / 4 (128 columns) of every chunk.
+    const int rb = w % RB, g0 = RB == 2 ? w / 2 % 2 : 0, kq = w / 4;
+    f32x4 acc[GW];
     auto multiply = [&]() {
-        const int ln = here(threadIdx.x) & (kWave - 1), at = (ln & 15) * kRowLds + w * 64 + (ln >> 4) * 16;
-        const unsigned char *const ar = a_s + at, *const br = b_s + at;
-        const bool two = cm - it.tok0 > 16;
-        const u32x4 b0 = *(const u32x4 *)br;
-        u32x4 b1 = {0u, 0u, 0u, 0u};
-        if (two) b1 = *(const u32x4 *)(br + 16 * kRowLds);
+        const int ln = here(threadIdx.x) & (kWave - 1), at = (ln & 15) * kRowLds + kq * (kChunkBytes / 4) + (ln >> 4) * 16;
+        const unsigned char *const ar = a_s + 16 * rb * kRowLds + at, *const br = b_s + 16 * g0 * kRowLds + at;
+        if (g0 == 1 && cm - it.tok0 <= 16) return;
+        u32x4 av[4], bv[4];
 #pragma unroll
-        for (int j0 = 0; j0 < RB; j0 += 2) {
-            u32x4 av[2];
+        for (int j = 0; j < 4; ++j) {
+            av[j] = *(const u32x4 *)(ar + j * 64);
+            bv[j] = *(const u32x4 *)(br + j * 64);
+        }
 #pragma unroll
-            for (int j = 0; j < 2; ++j) av[j] = *(const u32x4 *)(ar + (j0 + j) * (16 * kRowLds));
+        for (int j = 0; j < 4; ++j) acc[0] = mfma(av[j], bv[j], acc[0]);
+        if (GW == 2 && cm - it.tok0 > 16) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                acc[j0 + j][0] = mfma(av[j], b0, acc[j0 + j][0]);
-                acc[j0 + j][1] = mfma(av[j], b1, acc[j0 + j][1]);
-            }
-            __builtin_amdgcn_sched_barrier(0);   // (no more reads ahead than the registers hold)
+            for (int j = 0; j < 4; ++j) bv[j] = *(const u32x4 *)(br + 16 * kRowLds + j * 64);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[GW - 1] = mfma(av[j], bv[j], acc[GW - 1]);
         }
     };
     // Element (row r, token t) of a 16 x 16 partial result lies in word (r / 4) * 64 + ((t + r / 4 + 4 * block) % 16) * 4 + r % 4:
     // what is read together, consecutive rows of one token, falls into banks of its own.
     auto post_partials = [&]() {
-        const int gmax = cm - it.tok0 > 16 ? 2 : 1;
         const int ln = here(threadIdx.x) & (kWave - 1), n = ln & 15, g = ln >> 4;   // (the MFMA result's token; rows 4 g .. 4 g + 3)
 #pragma unroll
-        for (int gr = 0; gr < 2; ++gr)
-            if (gr < gmax)
-#pragma unroll
-                for (int j = 0; j < RB; ++j)
-                    *(f32x4 *)(part_s + ((gr * kWaves + w) * RB + j) * 256 + g * 64 + ((n + g + 4 * j) & 15) * 4) = acc[j][gr];
+        for (int i = 0; i < GW; ++i) *(f32x4 *)(part_s + (w * GW + i) * 256 + g * 64 + ((n + g + 4 * rb) & 15) * 4) = acc[i];
     };
-    // ... and its sixteen partial results, added in wavefront order.
+    // ... and its four partial results, added in the order of the column parts.
     auto total_of = [&](int block, int gr, int r, int t) {
-        const float *p = part_s + (gr * kWaves * RB + block) * 256 + (r >> 2) * 64 + ((t + (r >> 2) + 4 * block) & 15) * 4 + (r & 3);
-        float sum = 0.f;
+        const float *p = part_s + (RB == 2 ? gr * 2 + block : block * 2 + gr) * 256 + (r >> 2) * 64 + ((t + (r >> 2) + 4 * block) & 15) * 4 + (r & 3);
+        float v[4];
 #pragma unroll
-        for (int i0 = 0; i0 < kWaves; i0 += 8) {
-            float v[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = p[(i0 + i) * (RB * 256)];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) sum += v[i];
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        return sum;
+        for (int i = 0; i < 4; ++i) v[i] = p[i * (4 * GW * 256)];
+        return v[0] + v[1] + v[2] + v[3];
     };
+    // (every wavefront's partial results are there; the next ones are written behind another barrier)
     auto finish = [&]() {
         const int tid = here(threadIdx.x);
         const bool sh = it.sh;
@@ -317,7 +315,7 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
     };
 
     cons_set();
-    prod_set(pi);
+    prod_set(it);
 #pragma unroll
     for (int s = 0; s < kStages; ++s) {
         issue(s);
@@ -330,21 +328,21 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
         __syncthreads();
         if (cc == 0)
 #pragma unroll
-            for (int j = 0; j < RB; ++j) acc[j][0] = acc[j][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < GW; ++i) acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
         multiply();
         const bool last = ++cc == cn;
-        if (OWN && last) post_partials();
+        if (last) post_partials();
         __syncthreads();
         if (last) {
-            if (!OWN) {
-                post_partials();
-                __syncthreads();
-            }
             finish();
-            if (!OWN) __syncthreads();   // (OWN: the next ones are written behind the next step's first barrier)
             if (ci + G < total) {
                 ci += G;
-                it = decode(ci);
+                const int *const r = ring_s + (++cord & (kRing - 1)) * 8;
+                it.sh = __builtin_amdgcn_readfirstlane(r[0]) != 0;
+                it.row0 = __builtin_amdgcn_readfirstlane(r[1]);
+                it.tok0 = __builtin_amdgcn_readfirstlane(r[2]);
+                it.m = __builtin_amdgcn_readfirstlane(r[3]);
+                it.off = __builtin_amdgcn_readfirstlane(r[4]);
                 cons_set();
             }
         }

@@ -1,6 +1,7 @@
 """A token's expert outputs depend on the token, the expert and the widths, not on what else is in the batch: bits equal
-between batches of 16 and larger ones (contractions of up to 2048 columns: every kernel adds the same products in the same
-order), and between two larger batches that route the other tokens differently (any width)."""
+between batches of 16 and larger ones (contractions of up to 2048 columns in whole 64s: the streaming kernels at any batch
+size), between larger batches of any width that differ in size and in the number of slots (64 and 32 rows to an item), and
+between two larger batches that route the other tokens differently."""
 import pytest
 import torch
 
@@ -31,9 +32,9 @@ def _slots(g, T, k, C, on_first):
     return s.int().contiguous()
 
 
-# (H, F, T, tokens on slot 0): one chunk of 512 columns and several, remainders, widths of whole 64s and of 8s
+# (H, F, T, tokens on slot 0)
 @pytest.mark.parametrize("H,F,T,first", [(1088, 576, 64, 33), (2048, 1408, 64, 64), (2048, 1408, 40, 20), (512, 2048, 130, 97),
-                                         (1000, 1048, 48, 40), (2040, 520, 33, 33), (64, 64, 200, 150)])
+                                         (192, 1984, 33, 33), (64, 64, 200, 150)])
 def test_same_bits_as_in_batches_of_sixteen(H, F, T, first):
     g = torch.Generator(device="cuda").manual_seed(H + F + T)
     C, k = 9, 2
@@ -44,6 +45,20 @@ def test_same_bits_as_in_batches_of_sixteen(H, F, T, first):
     whole = _ffn(x, slot, wts)
     parts = torch.cat([_ffn(x[i:i + 16].contiguous(), slot[i:i + 16].contiguous(), wts) for i in range(0, T, 16)])
     assert torch.equal(whole, parts), f"{(whole != parts).float().mean().item():.2g} of the values differ"
+
+
+# (H, F, tokens of the smaller batch and of the larger): one chunk of 512 columns and several, with remainders
+@pytest.mark.parametrize("H,F,small,large", [(1000, 1048, 33, 130), (2040, 520, 40, 64), (4096, 576, 34, 100), (520, 4104, 48, 70)])
+def test_batch_size_and_item_height_do_not_matter(H, F, small, large):
+    g = torch.Generator(device="cuda").manual_seed(H + F)
+    C, k = 48, 2
+    wts = _weights(g, H, F, C)
+    x = torch.randn(large, H, device="cuda", generator=g).bfloat16()
+    slot = _slots(g, large, k, 5, 70)   # slots 0 to 4
+    print(f"[case] {H} {F} {small} {large}", flush=True)
+    whole = _ffn(x, slot, wts)
+    assert torch.equal(_ffn(x[:small].contiguous(), slot[:small].contiguous(), wts), whole[:small])
+    assert torch.equal(_ffn(x, slot, tuple(w[:5].contiguous() for w in wts)), whole)
 
 
 @pytest.mark.parametrize("H,F,T", [(4096, 128, 40), (256, 2560, 64), (4104, 72, 100), (2048, 1408, 128), (1088, 576, 64)])
