@@ -25,11 +25,20 @@
  *     was launched.  No exceptions, no abort, nothing printed.
  *   - Supported sizes: 1 <= k <= min(E, 64); E <= 512; T*E <= 65536;
  *     C <= 1024; H, F and F_shared multiples of 8 (rows of 16 bytes); bf16
- *     tensors and `out` 16-byte aligned.  Batches of up to 32 tokens run
- *     in the weight-streaming kernels, with H, F and F_shared multiples of 64
- *     at any H; every other shape is limited to H <= 4992 (MOE_ERR_SHAPE
- *     beyond): larger batches may run in a kernel that keeps a token tile's
- *     hidden rows in LDS.
+ *     tensors and `out` 16-byte aligned.  Any H with H, F and F_shared
+ *     multiples of 64 and up to 32 tokens; every other shape is limited to
+ *     H <= 4960 (MOE_ERR_SHAPE beyond), as it may run in a kernel that keeps
+ *     a token tile's hidden rows in LDS.
+ *   - Which FFN kernels run follows from the sizes alone, the workspace's
+ *     among them: the weight-streaming kernels up to 32 tokens, and beyond for
+ *     widths of up to 2048 in whole 64s (T*k <= 6144); the larger-batch
+ *     kernels for the rest, and from 17 tokens on where H or F is beyond 2048
+ *     and the call's weights come to 64 MB; the general kernel where the
+ *     workspace has room for no more than its partial sums.
+ *   - With the same widths in the same of these three, a token's row of `out`
+ *     depends, to the last bit, neither on the other tokens of the batch nor
+ *     on the experts' slots, and a repeated call gives the same bits.  Between
+ *     the three the order of the sums differs (differences of rounding only).
  *   - Two calls that share a workspace must not overlap in time.  A
  *     workspace holds state between calls (a call counter and regions whose
  *     entries are stamped with it): initialise it with moe_workspace_init
@@ -166,7 +175,12 @@ int moe_slot_resolve(const int32_t *topk_idx, const int32_t *slot_table, int T, 
  * rounded to bf16 before the down projection.  Missed assignments add
  * nothing.  out [T,H] fp32, or bf16 when out_bf16 != 0; accumulate != 0 adds
  * to what `out` holds (the join with the host's partial result), else `out`
- * is overwritten.  Slots outside [0,C) in slot_idx are treated as -1. */
+ * is overwritten.  Slots outside [0,C) in slot_idx are treated as -1.  A token
+ * may name a slot several times, except with widths of whole 64s and up to 32
+ * tokens in the streaming kernels, where a slot's list must not exceed 16
+ * entries (T <= 16) or 32 (beyond, the call's results are not valid).
+ * With H or F not a multiple of 64, or more than 32 tokens, or in the
+ * larger-batch kernels no launch of this call waits for another workgroup. */
 int moe_grouped_ffn(const void *hidden, const float *topk_w, const int32_t *slot_idx, const void *w_gate,
                     const void *w_up, const void *w_down, int T, int H, int F, int k, int C, void *out,
                     int out_bf16, int accumulate, void *workspace, size_t workspace_bytes, void *stream);
@@ -174,7 +188,8 @@ int moe_grouped_ffn(const void *hidden, const float *topk_w, const int32_t *slot
 /* Steps 1-4 for one verification batch on `stream`, in the launch form that
  * shape->launch_form names (MOE_LAUNCH_AUTO: two launches, the routing steps
  * at the head of the gate/up kernel, for batches of up to 32 tokens and 128
- * experts with a non-empty pool; else three launches; four above 32 tokens).
+ * experts with a non-empty pool; else three launches; four in the
+ * larger-batch kernels and above 32 tokens).
  * Every form computes the same outputs to the same bar.
  * The workspace carries state from call to call (see moe_workspace_init): it
  * must have been initialised once, be used by one call at a time, and be

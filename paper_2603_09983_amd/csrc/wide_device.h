@@ -7,8 +7,9 @@
 // rows of several panels, that operand has to come again for every tile.  Here an item is 64 weight rows (32 gate rows
 // on 32 up rows, or 64 down rows) against 32 tokens of one expert's list; both operands pass through LDS in chunks of
 // 512 columns, every load instruction one row's consecutive kilobyte, and the accumulators stay in registers for the
-// whole contraction.  Bound: HBM for the weights (each is read from HBM once; an expert with more than 32 tokens reads
-// its weights once per 32, the later times from the caches, as neighbouring items run at the same time).
+// whole contraction.  Bound: HBM for the weights.  An expert's weights are read once for each 32 of its tokens, and the
+// L2s do not keep them in between (FETCH_SIZE, 8 experts of 4096 x 14336: gate/up 1.92 GB for 1.88 GB of weights at 64 tokens,
+// all lists within 32; 2.31 GB at 128 tokens, 10 blocks on 8 experts, where 2.35 GB would be no reuse at all).
 //
 // One workgroup of sixteen wavefronts per CU takes items b, b + G, .. and keeps three chunks in flight, across items
 // (3 x 64 KB of weights).
@@ -21,8 +22,8 @@
 // kilobytes of one chunk lie in few of an L2's sixteen channels, and workgroups that start together would all be in the same
 // ones (8 experts of 4096 x 14336, 24 tokens: 530 us per layer with all items starting at chunk 0, 441 us so; H = 2048: no
 // difference).  What an XCD has at a time must differ in that chunk: an expert's tiles begin one XCD further on than those of
-// the expert before.  An expert with more than 32 tokens has its token blocks of a row tile eight items apart, so that they
-// read the same weights from one L2 at the same time (128 tokens on 8 experts of 4096 x 14336: 725 us with neighbouring blocks, 715 so).
+// the expert before.  An expert with more than 32 tokens has its token blocks of a row tile eight items apart, on one XCD, with
+// the same first chunk (128 tokens on 8 experts of 4096 x 14336: 725 us with neighbouring blocks at chunks of their own, 715 so).
 //
 // Any width that is a multiple of 8: rows and tokens beyond the end repeat the last one and are not stored; columns
 // beyond the end of a row are zero in both operands.
@@ -124,7 +125,7 @@ __device__ __forceinline__ void wide_body(const StreamArgs &a)
 
     // Item i: its expert, first row, first token, and the expert's tokens, first list entry (or act row) and place in
     // the pool.  Which workgroup (so: which XCD, i mod 8) gets a row tile: the token blocks of a tile lie eight items apart, on
-    // one L2 at the same time; and an expert's tiles begin one XCD further on than those of the one before (see `prot`).
+    // one XCD; and an expert's tiles begin one XCD further on than those of the one before (see `prot`).
     struct Item { bool sh; int row0, tok0, m, off, slot; };
     auto decode = [&](int i) {
         Item it;

@@ -1,6 +1,6 @@
 """Batches of more than 32 tokens against the oracle: experts with one token, with 16 / 17 / 32 / 33 / many (several
-blocks of 32), rows and contractions at the edges of the 512-column chunks and the 16- and 32-row tiles, shared experts,
-bf16 output and accumulation, fewer items than workgroups."""
+blocks of 32), rows and contractions at the edges of the 512-column chunks and of the larger-batch kernels' items of 32 rows,
+shared experts, bf16 output and accumulation, fewer items than workgroups.  (Items of 64 rows: test_gpu_wide_tall.py.)"""
 import numpy as np
 import pytest
 
@@ -37,8 +37,8 @@ def test_wide(i):
 
 @pytest.mark.parametrize("T,most", [(33, 32), (34, 32), (33, 33), (128, 32), (128, 33)])
 def test_either_side_of_32_tokens_an_expert(T, most):
-    """Widths of whole 64s: the kernel streams whole rows while no expert has more than 32 tokens.  A router bias sends
-    exactly `most` tokens to expert 0."""
+    """Widths of whole 64s: an expert with more than 32 tokens is several entries of the streaming kernels' list.  Column 0
+    of the hidden states sends exactly `most` tokens to expert 0."""
     import gpu_util as G
     import torch
     E, k, H, F = 64, 2, 64, 128
