@@ -330,9 +330,10 @@ extern "C" int moe_slot_resolve(const int32_t *topk_idx, const int32_t *slot_tab
 namespace {
 
 // The expert FFN and the combine, given the per-slot lists in the workspace.
-// Shapes the LDS-staged streaming kernels take (use_stream_kernels) run gate/up,
-// then down with the combine inside it (small batches) or followed by it; the
-// rest takes the fused per-slice kernel and its combine.
+// A workspace laid out for the streaming or the larger-batch kernels (w.stream;
+// wide: the latter): gate/up, then down with the combine inside it (up to 32
+// tokens, may_wait) or followed by it.  One laid out for the general kernel: that
+// kernel and its combine.  own_lists: the lists are a caller's own.
 int run_ffn(const void *hidden, const float *topk_w, const void *w_gate, const void *w_up, const void *w_down,
             const void *sh_gate, const void *sh_up, const void *sh_down, int T, int H, int F, int k, int C,
             int n_shared, int F_shared, const WsLayout &w, char *ws, void *out, int out_bf16, int accumulate,

@@ -87,7 +87,7 @@ static inline bool use_wide_kernels(int T, int k, int C, int H, int F, int n_sha
         (n_shared > 0 && (F_shared < 8 || F_shared % 8 != 0)) || wide_lds_bytes(T, k, C) > (size_t)kLdsBytes)
         return false;
     // Two token groups and rows of several panels: the streaming kernels reload the B operand for every tile (8 experts
-    // of 4096 x 14336: 17 tokens 576 us, 32 tokens 749 us; here 445 and 446).  Two launches more have to pay, though: pools
+    // of 4096 x 14336: 17 tokens 576 us, 24 tokens 650 us, 32 tokens 749 us; here 441 at 24).  Two launches more have to pay, though: pools
     // of 7 MB 23.7 against 25.8 us, 50 MB 33.6 against 34.0, 91 MB 44.2 against 39.5, 201 MB 64.1 against 58.8.
     if (T <= 32)
         return (H > kPanelMax || F > kPanelMax) && 6ll * H * ((long long)C * F + (long long)n_shared * F_shared) >= 64ll << 20;
@@ -285,11 +285,12 @@ struct StreamArgs {
     int R, K, R_sh, K_sh, n_shared, C;
     int KP, KP_sh;             // panel widths (columns parked in LDS at a time)
     // Filled in by the launch functions: panels per routed / shared item, and floor(2^32 / d) for the divisors of
-    // the kernel's index arithmetic (grid size, items per routed / shared expert, panels per item, k, k + n_shared, blocks of 32 tokens).  A division by a
+    // the kernel's index arithmetic (grid size, items per routed / shared expert, panels per item or, beyond 32 tokens,
+    // blocks of 32 tokens, k, k + n_shared).  A division by a
     // value only known at run time is ~30 instructions, and in the prologue of a launch sixteen wavefronts execute
     // them one after the other on the compute unit's one scalar unit.
     int np, np_sh;
-    unsigned rcp_G, rcp_tiles, rcp_tiles_sh, rcp_np, rcp_k, rcp_S, rcp_nb;
+    unsigned rcp_G, rcp_tiles, rcp_tiles_sh, rcp_np, rcp_k, rcp_S;
 };
 
 // n / d with rcp = floor(2^32 / d) (d = 1: 2^32 - 1): the estimate is never too large and at most one short.

@@ -130,8 +130,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     unsigned char *tile_s = lds;
     float *red_s = (float *)(lds + tile_lds_bytes);                   // [group][wavefront][lane][4]
     int *ctl_s = (int *)(lds + tile_lds_bytes + NG * kWaves * kWave * 16);
-    int *count_s = ctl_s, *offset_s = ctl_s + a.C, *active_s = ctl_s + 2 * a.C;
-    int *perm_s = active_s + a.C + (BLOCKS ? stream_more_entries(a.T, a.k) : 0);
+    int *count_s = ctl_s, *offset_s = ctl_s + a.C, *active_s = ctl_s + 2 * a.C, *perm_s = ctl_s + 3 * a.C;
+    if (BLOCKS) perm_s += stream_more_entries(a.T, a.k);
     float *out_s = (float *)(perm_s + a.T * a.k);                     // [kOutCap][NG][kOutPerItem] results waiting to be stored
     int *odesc_s = (int *)(out_s + kOutCap * NG * kOutPerItem);       // [kOutCap][8]: shared?, row of token 0, column bytes, m
 
@@ -171,7 +171,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         psh = sh; pe = e; prt = rt; ppan = 0;
         if (RAGGED) ppoff = 0;
         if (sh) {
-            const int K = a.K_sh, ex = MODE == 2 ? udiv_rcp(e, nb_sh, a.rcp_nb) : e;
+            const int K = a.K_sh, ex = MODE == 2 ? udiv_rcp(e, nb_sh, a.rcp_np) : e;
             const size_t eoff = ((size_t)ex * a.R_sh + (size_t)rt * RPI) * K;
             pw0 = (const unsigned char *)(a.s0 + eoff);
             pw1 = GATEUP ? (const unsigned char *)(a.s1 + eoff) : pw0 + (size_t)16 * K;
@@ -225,7 +225,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         cocol = rt * RPI * OB;
         if (sh) {
             cK = a.K_sh; c_rs = 2 * a.KP_sh; cnpan = a.np_sh;
-            const int ex = MODE == 2 ? udiv_rcp(e, nb_sh, a.rcp_nb) : e, t0 = MODE == 2 ? (e - ex * nb_sh) * 32 : 0;
+            const int ex = MODE == 2 ? udiv_rcp(e, nb_sh, a.rcp_np) : e, t0 = MODE == 2 ? (e - ex * nb_sh) * 32 : 0;
             cm = a.T - t0; ckey = ALLTOK ? 0 : e; corow0 = ex * a.T + t0;
             cbrow0 = GATEUP ? t0 : corow0;            // hidden[t0 + n] | act_sh[e][t0 + n]
         } else {
@@ -943,7 +943,10 @@ int stream_panel_width(int K)
 int stream_panel(int K)
 {
     // A step of the kernels costs about the same whatever its panel's width, so a K whose only equal split is into
-    // many narrow panels (K = 64 times a prime: 64 columns each) is split like a ragged one.
+    // many narrow panels (K = 64 times a prime: 64 columns each) is split like a ragged one.  Layers of 9 tokens on 12 experts,
+    // the other width 1024, equal panels | as ragged: K = 2368, 37 panels for 2, 170 | 41 us; 2240, 5 for 2, 50.5 | 39.5 (as the down
+    // contraction 42.7 | 37.5); 3520, 5 for 2, 50.1 | 48.2; 2112, 3 for 2, 41.5 | 40.4 (down 37.6 | 37.4); 4160, 5 for 3, 55.1 | 54.3; 4480,
+    // 5 for 3, 55.8 | 55.4.  The line lies where the two meet.
     const int equal = stream_panel_width(K);
     const int np = (K + kPanelMax - 1) / kPanelMax;
     if (equal > 0 && K / equal <= np + np / 2 + 1) return equal;
@@ -970,10 +973,9 @@ void fill_derived(StreamArgs &x, bool gateup, int grid)
     x.rcp_G = rcp32((unsigned)grid);
     x.rcp_tiles = rcp32((unsigned)((x.R + rpi - 1) / rpi));
     x.rcp_tiles_sh = rcp32((unsigned)(x.n_shared > 0 ? (x.R_sh + rpi - 1) / rpi : 1));
-    x.rcp_np = rcp32((unsigned)x.np);
+    x.rcp_np = rcp32((unsigned)(x.T > 32 ? (x.T + 31) / 32 : x.np));
     x.rcp_k = rcp32((unsigned)x.k);
     x.rcp_S = rcp32((unsigned)(x.k + x.n_shared));
-    x.rcp_nb = rcp32((unsigned)((x.T + 31) / 32));
 }
 // Does the launch need the RAGGED instances?  (On widths that both can take those measured 2 to 12 % slower per layer,
 // from the masks and the longer index arithmetic: 64 experts T = 9 70.6 against 66.9 us, T = 17 127.8 against 125.1,
