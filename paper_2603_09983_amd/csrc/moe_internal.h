@@ -374,7 +374,8 @@ bool stream_can_join(const StreamArgs &d);
 hipError_t launch_wide(const StreamArgs &a, bool gateup, hipStream_t s);
 // 64 weight rows to an item, or 32: those cost an eighth more a row (64 tokens on 8 experts of 4096 x 14336 490 against 459 us,
 // 128 tokens 814 against 702), but spread over the workgroups in smaller steps (40 tokens on 20 experts of 1000 x 1000, 2.5 items
-// of 64 rows a workgroup: 48.4 against 50.2 us, 100 tokens of 2040 x 1000 76.1 against 82.6).  So by the time of the longest share.
+// of 64 rows a workgroup: 48.4 against 50.2 us, 100 tokens of 2040 x 1000 76.1 against 82.6; 17 tokens top-1 on 43 slots of
+// 2944 x 320, of which a few are used: 34.4 against 40.2).  So by the time of the longest share, and 32 below two rounds.
 bool wide_tall(const StreamArgs &a, bool gateup);
 hipError_t launch_combine_rows(const CombineArgs &a, const float *o, const float *o_sh, hipStream_t s);
 // one-launch form (batches of up to 16 tokens): use_layer_kernel() must hold; route != null: the kernel does

@@ -28,11 +28,11 @@ bool wide_tall(const StreamArgs &a, bool gateup)
     const long long A = (long long)a.T * a.k, slots = a.C < A ? a.C : A, G = device_cus(nullptr);
     const long long blocks = slots > 0 ? slots * ((A / slots + wide::kToks - 1) / wide::kToks) : 0;   // (routed evenly, every slot in use)
     const long long blocks_sh = (long long)a.n_shared * ((a.T + wide::kToks - 1) / wide::kToks);
-    auto rounds = [&](int rpi) {
-        return ((a.R + rpi - 1) / rpi * blocks + (a.n_shared ? (a.R_sh + rpi - 1) / rpi * blocks_sh : 0) + G - 1) / (G > 0 ? G : 1);
-    };
+    auto items = [&](int rpi) { return (a.R + rpi - 1) / rpi * blocks + (a.n_shared ? (a.R_sh + rpi - 1) / rpi * blocks_sh : 0); };
+    auto rounds = [&](int rpi) { return (items(rpi) + G - 1) / (G > 0 ? G : 1); };
     const int rpi = gateup ? 32 : 64;
-    return rounds(rpi) * 2 * 88 <= rounds(rpi / 2) * 100;
+    // (fewer than two rounds, if so many: with slots that nobody uses there is less than one)
+    return items(rpi) >= 2 * G && rounds(rpi) * 2 * 88 <= rounds(rpi / 2) * 100;
 }
 
 hipError_t launch_wide(const StreamArgs &a, bool gateup, hipStream_t s)
