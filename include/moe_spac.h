@@ -214,7 +214,8 @@ int moe_verify_layer(const moe_shape_t *shape, const void *hidden, const float *
  * the process ends.  The call allocates and frees nothing.
  *   - A shape that needs more scratch memory than MOE_STATIC_SCRATCH_BYTES is
  *     rejected with MOE_ERR_SCRATCH before anything is launched (16 MiB holds
- *     every shape up to 128 tokens x top-6 at H = 2048, F = 1408); shapes
+ *     every shape up to 122 tokens x top-6 at H = 2048, F = 1408 without shared
+ *     experts); shapes
  *     whose widths are not multiples of 64, or wider than 2048 with more than
  *     32 tokens, count with 4 T k H ceil(F / 128) bytes.
  *   - The array keeps the last call's contents.  The first call on a device,
