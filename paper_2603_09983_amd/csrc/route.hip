@@ -49,16 +49,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs a)
     const uint16_t *x = (const uint16_t *)a.hidden;
     for (int q = b + w * G; q < TE; q += G * kRouteWaves) {
         const int t = q / E, e = q - t * E;
-        const float *wrow = a.router_w + (size_t)e * H;
-        const uint16_t *xr = x + (size_t)t * H;
         const float bias = a.router_bias ? a.router_bias[e] : 0.f;
-        float acc = 0.f;
-#pragma unroll 8
-        for (int h = lane * 4; h < H; h += kWave * 4) {
-            float4 wv = *(const float4 *)(wrow + h);
-            uint2 xv = *(const uint2 *)(xr + h);
-            acc += wv.x * bf16_lo(xv.x) + wv.y * bf16_hi(xv.x) + wv.z * bf16_lo(xv.y) + wv.w * bf16_hi(xv.y);
-        }
+        float acc = wave_dot(a.router_w + (size_t)e * H, x + (size_t)t * H, H);
 #pragma unroll
         for (int m = kWave / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, kWave);
         acc += bias;

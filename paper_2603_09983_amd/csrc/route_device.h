@@ -25,6 +25,9 @@ typedef float f32x4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) const f32x4v lds_f32x4;
 typedef __attribute__((address_space(1))) int32_t g_i32;
 typedef __attribute__((address_space(1))) float g_f32;
+typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(1))) const f32x4v g_f32x4;
+typedef __attribute__((address_space(1))) const u32x2v g_u32x2;
 
 // Value of v in the lane n places further on inside the row of 16 lanes, wrapping round (register to
 // register, no trip through LDS): data-parallel-primitive control row_ror:n = 0x120 + n.
@@ -34,9 +37,9 @@ __device__ __forceinline__ unsigned row_rotate(unsigned v)
     return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + N, 0xf, 0xf, false);
 }
 
-// Maximum of x over the 64 lanes of a wavefront (all of them active), as a uniform value.  Four
-// rotations leave each row's maximum in every lane of the row; the four row results are then read
-// into scalar registers.
+// Maximum of x over the 64 lanes of a wavefront (all of them active), in every lane: four rotations inside the rows of
+// sixteen, then the rows exchanged pairwise and by halves.  All in vector registers: through four readlanes and scalar maxima the
+// value changes register file twice, and each of the k steps of a ranking took 0.16 us instead of 0.07.
 __device__ __forceinline__ unsigned wave_max_u32(unsigned x)
 {
     unsigned y;
@@ -44,10 +47,10 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned x)
     y = row_rotate<2>(x); x = x > y ? x : y;
     y = row_rotate<4>(x); x = x > y ? x : y;
     y = row_rotate<8>(x); x = x > y ? x : y;
-    const unsigned a = (unsigned)__builtin_amdgcn_readlane((int)x, 0), b = (unsigned)__builtin_amdgcn_readlane((int)x, 16);
-    const unsigned c = (unsigned)__builtin_amdgcn_readlane((int)x, 32), d = (unsigned)__builtin_amdgcn_readlane((int)x, 48);
-    const unsigned ab = a > b ? a : b, cd = c > d ? c : d;
-    return ab > cd ? ab : cd;
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = r[0] > r[1] ? r[0] : r[1];
+    const auto h = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return h[0] > h[1] ? h[0] : h[1];
 }
 
 // Sum of x over the 64 lanes, likewise.
@@ -65,9 +68,13 @@ __device__ __forceinline__ unsigned wave_sum_u32(unsigned x)
 // wavefront, ties to the lower expert id, the winner taken out.  Logits are compared as unsigned keys
 // that order like the floats (-0 counted as +0; key 0 = taken or no expert, below every float).  The
 // gate is exp(s - s_max) normalised over the k, summed in rank order.  Lane l owns experts l, l+64, ...;
-// the caller has put the logits into `lg` (LDS private to the wavefront: E floats, NaN replaced by -inf).
-// Lane j < k ends up with the j-th expert and writes it out.  Needs k <= E and all 64 lanes active.
-// Returns the gate weight of the lane's pick (lanes >= k: unspecified).
+// the caller has put the logits into `lg` (LDS private to the wavefront: E floats, NaN replaced by -inf; overwritten).
+// Needs k <= E and all 64 lanes active.  Returns the gate weight of the pick of rank `lane` (lanes >= k: unspecified); with
+// idx_out null the ids are wanted in LDS only, and there is no gate.
+//
+// Bound by the latency of the k dependent steps (about a hundred cycles each), so a step does nothing but find the winner and
+// take it out: the winner's own lane notes the rank, and the picks are put in order through LDS at the end.  Six of 64
+// experts with the gate: 0.95 -> 0.55 us.
 template <int NLOC>
 __device__ __forceinline__ float wave_topk_gate_n(int E, int k, int32_t *idx_out_, lds_i32 *idx_lds,
                                                   float *w_out_, lds_f32 *lg)
@@ -76,56 +83,55 @@ __device__ __forceinline__ float wave_topk_gate_n(int E, int k, int32_t *idx_out
     g_f32 *w_out = (g_f32 *)(uintptr_t)w_out_;
     const int lane = threadIdx.x & (kWave - 1);
     unsigned key[NLOC];
+    float val[NLOC];
+    int rank[NLOC];
 #pragma unroll
     for (int i = 0; i < NLOC; ++i) {
         const int e = lane + kWave * i;
         float f = e < E ? lg[e] : 0.f;
         f = f == 0.f ? 0.f : f;
         const unsigned u = __float_as_uint(f);
+        val[i] = f;
         key[i] = e < E ? ((u & 0x80000000u) ? ~u : (u | 0x80000000u)) : 0u;
+        rank[i] = k;
     }
-    unsigned my_key = 0x80000000u;   // (the key of 0.0f)
-    int my_e = 0;
     for (int j = 0; j < k; ++j) {
         unsigned m = key[0];
 #pragma unroll
         for (int i = 1; i < NLOC; ++i) m = m > key[i] ? m : key[i];
         const unsigned best = wave_max_u32(m);
         // lowest id among the experts that hold it: the lowest i that has one, then the lowest lane
-        int win_i = 0;
-        unsigned long long win_bal = 0ull;
+        bool open = true;
 #pragma unroll
-        for (int i = NLOC - 1; i >= 0; --i) {
+        for (int i = 0; i < NLOC; ++i) {
             const unsigned long long bal = __ballot(key[i] == best);
-            if (bal) {
-                win_bal = bal;
-                win_i = i;
+            const int win = open && bal ? __ffsll((long long)bal) - 1 : -1;
+            open = open && bal == 0ull;
+            if (lane == win) {
+                rank[i] = j;
+                key[i] = 0u;
             }
         }
-        const int win_lane = win_bal ? __ffsll((long long)win_bal) - 1 : 0;
-        int e = win_lane + kWave * win_i;
-        e = e < E ? e : E - 1;   // (only if k > E: stay inside every table)
-        if (lane == j) {
-            my_key = best;
-            my_e = e;
-        }
-#pragma unroll
-        for (int i = 0; i < NLOC; ++i)
-            if (i == win_i && lane == win_lane) key[i] = 0u;
     }
-    const float my_s = __uint_as_float((my_key & 0x80000000u) ? (my_key ^ 0x80000000u) : ~my_key);
+    // (LDS operations of one wavefront execute in order: every logit has been read above)
+#pragma unroll
+    for (int i = 0; i < NLOC; ++i) {
+        if (rank[i] < k) {
+            const int e = lane + kWave * i;
+            lg[rank[i]] = val[i];
+            if (idx_lds) idx_lds[rank[i]] = e;
+            if (idx_out_) idx_out[rank[i]] = e;
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (!idx_out_) return 0.f;
+    const float my_s = lane < k ? lg[lane] : 0.f;
     const float smax = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(my_s), 0));
     const float ex = lane < k ? __expf(my_s - smax) : 0.f;
     float den = 0.f;
     for (int j = 0; j < k; ++j) den += __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(ex), j));
     const float gate = ex / den;
-    if (lane < k) {
-        if (idx_lds) idx_lds[lane] = my_e;
-        if (idx_out_) {   // (null: the ids are wanted in LDS only)
-            idx_out[lane] = my_e;
-            w_out[lane] = gate;
-        }
-    }
+    if (lane < k) w_out[lane] = gate;
     return gate;
 }
 
@@ -136,6 +142,50 @@ __device__ __forceinline__ void wave_topk_gate(int E, int k, int32_t *idx_out, l
     else if (E <= 2 * kWave) wave_topk_gate_n<2>(E, k, idx_out, idx_lds, w_out, lg);
     else if (E <= 4 * kWave) wave_topk_gate_n<4>(E, k, idx_out, idx_lds, w_out, lg);
     else wave_topk_gate_n<kMaxEPL>(E, k, idx_out, idx_lds, w_out, lg);
+}
+
+// One lane's part of the dot product of a router row with a token's hidden row: columns 4 lane, 4 lane + 256, .. in
+// ascending order.  The loads of up to 2048 columns are on their way together; where fewer are left, a lane beyond the
+// row's end re-reads its last columns and adds nothing.  (A plain loop fetches the columns of an H below 2048 one kilobyte
+// after the other: H = 2040, 7 tokens, 2.7 us instead of 1.2.)
+__device__ __forceinline__ float wave_dot(const float *wrow, const uint16_t *xr, int H)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    float acc = 0.f;
+    auto term = [](f32x4v wv, u32x2v xv) __attribute__((always_inline)) {
+        return wv.x * bf16_lo(xv.x) + wv.y * bf16_hi(xv.x) + wv.z * bf16_lo(xv.y) + wv.w * bf16_hi(xv.y);
+    };
+    int h0 = 0;
+    for (; h0 + 8 * kWave * 4 <= H; h0 += 8 * kWave * 4) {
+        f32x4v wv[8];
+        u32x2v xv[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            wv[i] = *(g_f32x4 *)(uintptr_t)(wrow + h0 + lane * 4 + i * kWave * 4);
+            xv[i] = *(g_u32x2 *)(uintptr_t)(xr + h0 + lane * 4 + i * kWave * 4);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc += term(wv[i], xv[i]);
+    }
+    if (h0 < H) {
+        f32x4v wv[8] = {};
+        u32x2v xv[8] = {};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (h0 + i * kWave * 4 >= H) break;
+            const int h = h0 + i * kWave * 4 + lane * 4;
+            const unsigned o = (unsigned)(h < H ? h : H - 4);
+            wv[i] = *(g_f32x4 *)((uintptr_t)wrow + o * 4u);
+            xv[i] = *(g_u32x2 *)((uintptr_t)xr + o * 2u);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (h0 + i * kWave * 4 >= H) break;
+            const float p = term(wv[i], xv[i]);
+            acc += h0 + i * kWave * 4 + lane * 4 < H ? p : 0.f;
+        }
+    }
+    return acc;
 }
 
 // logits of one token in LDS: E floats, each wavefront's row starting on a multiple of four
@@ -329,7 +379,7 @@ __device__ inline PostLds carve_lds(int *dyn_, int E, int C, int A)
     return p;
 }
 
-inline size_t post_lds_bytes(int E, int C, int A, bool with_topk)
+__host__ __device__ inline size_t post_lds_bytes(int E, int C, int A, bool with_topk)
 {
     const int cap = A < kLdsCopy ? A : kLdsCopy;
     size_t n = (size_t)2 * E + (size_t)kRouteWaves * C + (C + 1) + 48 + 2 * cap;

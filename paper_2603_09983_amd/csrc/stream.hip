@@ -45,6 +45,39 @@ constexpr int kPieces = 4;     // 1 KB pieces per wavefront per tile (64 KB tile
 constexpr int kRowPad = kStreamRowPad;
 constexpr int kOutCap = kStreamOutCap;
 
+// Arguments of the gate/up kernel that does the routing steps.  Those of the routing steps are not passed on by value: with
+// all of them in scalar registers from the start a hundred scalar registers were kept in lanes of vector registers, and
+// writing and reading those was 0.5 us of the launch.  They are read from the argument segment where they are used.
+struct RoutedArgs {
+    RouteArgs r;
+    StreamArgs a;
+    int tile_lds_bytes;
+};
+typedef const __attribute__((address_space(4))) RouteArgs k_route;
+__device__ __forceinline__ k_route *route_args()   // (of a routed_stream_kernel)
+{
+    k_route *p = (k_route *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));   // (not the loads of an earlier place kept)
+    return p;
+}
+// One word of each of the arguments' cache lines, all asked for at once: what is read from them later is in the scalar cache by
+// then (line by line, where each was first used, the dot products began 0.3 us later).
+__device__ __forceinline__ void touch_route_args()
+{
+    typedef const __attribute__((address_space(4))) unsigned k_word;
+    k_word *const p = (k_word *)route_args();
+    unsigned x = 0;
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(RouteArgs) / 4; i += 16) x |= p[i];
+    asm volatile("" : : "s"(x));
+}
+// A pointer read from there, said to point to global memory (or its accesses would be flat ones, which count as LDS accesses too).
+template <typename V>
+__device__ __forceinline__ __attribute__((address_space(1))) V *glob(V *p)
+{
+    return (__attribute__((address_space(1))) V *)(uintptr_t)p;
+}
+
 __device__ inline u32x4 ld_stream(const unsigned char *p)
 {
     return __builtin_nontemporal_load((const u32x4 *)p);
@@ -106,8 +139,7 @@ __device__ unsigned long long g_timeline[2][kTimelineGroups][kTimelineWords];
 // the panel before had, or that no row has, are zero in both operands; the down kernel's last tile may have 8 rows.
 //
 template <bool GATEUP, int NPI, int MODE, bool JOIN, bool WSPLIT, bool FUSED, bool RAGGED>
-__device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_lds_bytes, const JoinArgs &jn,
-                                            const RouteArgs &ra)
+__device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_lds_bytes, const JoinArgs &jn)
 {
     static_assert(!WSPLIT || !GATEUP, "gate/up items all have the panels of the hidden size");
     static_assert(!FUSED || (GATEUP && MODE <= 1 && !JOIN && !WSPLIT), "the routing steps ride on the gate/up kernels of up to 32 tokens");
@@ -140,6 +172,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     unsigned long long tl_start, tl_lists = 0, tl_first = 0, tl_loop = 0, tl_flush = 0;
 #endif
     MOE_STAMP(tl_start);
+    if (FUSED) touch_route_args();
     const int w = __builtin_amdgcn_readfirstlane(tid / kWave);   // wavefront id, known to be uniform
     const int n = lane & 15, g = lane >> 4;
 
@@ -395,46 +428,42 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     unsigned rtag = 0, rwtag = 0;
     int rspin = kSpinLimit;
     int n_act = 0;
+    bool short_lists = false;
     if (FUSED) {
-        const int T = ra.T, H = ra.H, E = ra.E, TE = T * E, A = T * ra.k, C = ra.C;
-        rtag = *ra.epoch + 1u;
+        k_route *R = route_args();
+        const int T = a.T, H = R->H, E = R->E, TE = T * E, A = T * a.k, C = a.C;
+        const auto ctrl = glob(R->epoch - kCtrlEpoch);
+        rtag = ctrl[kCtrlEpoch] + 1u;
         // (two words of the control block that only a test sets: the bound of the polls, and a number added to
         // what producers stamp their entries with, so that the host can make every wait run out)
-        rwtag = rtag + (ra.epoch - kCtrlEpoch)[kCtrlSkew];
-        if (b == 0 && tid == 0) check_layout(ra.epoch - kCtrlEpoch, ra.layout);
-        if ((ra.epoch - kCtrlEpoch)[kCtrlSpin]) rspin = (int)(ra.epoch - kCtrlEpoch)[kCtrlSpin];
-        const size_t n_pub = list_pub_entries(T, ra.k, C);
+        rwtag = rtag + ctrl[kCtrlSkew];
+        if (b == 0 && tid == 0) check_layout(R->epoch - kCtrlEpoch, R->layout);
+        if (ctrl[kCtrlSpin]) rspin = (int)ctrl[kCtrlSpin];
+        const size_t n_pub = list_pub_entries(T, a.k, C);
         // (workgroup 0 gives the call its number in the control block only when every workgroup has read the
         // old one: each says so with a stamped word of its own)
-        unsigned long long *const seen = ra.lists_pub + (size_t)kListReplicas * n_pub;
+        const auto seen = glob(R->lists_pub) + (size_t)kListReplicas * n_pub;
         if (tid == 0)
             __hip_atomic_store(seen + b, ((unsigned long long)rtag << 32) | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int tab_v = -1;
-        if (tid < E) tab_v = ra.slot_table[tid];
-        const uint16_t *x = (const uint16_t *)ra.hidden;
+        if (tid < E) tab_v = *glob(R->slot_table + tid);
+        const uint16_t *x = (const uint16_t *)R->hidden;
         for (int q = b + w * G; q < TE; q += G * kWaves) {
             const int t = q / E, e = q - t * E;
-            const float *wrow = ra.router_w + (size_t)e * H;
-            const uint16_t *xr = x + (size_t)t * H;
-            const float bias = ra.router_bias ? ra.router_bias[e] : 0.f;
-            float dot = 0.f;
-#pragma unroll 8
-            for (int h = lane * 4; h < H; h += kWave * 4) {
-                const float4 wv = *(const float4 *)(wrow + h);
-                const uint2 xv = *(const uint2 *)(xr + h);
-                dot += wv.x * bf16_lo(xv.x) + wv.y * bf16_hi(xv.x) + wv.z * bf16_lo(xv.y) + wv.w * bf16_hi(xv.y);
-            }
+            const float bias = R->router_bias ? *glob(R->router_bias + e) : 0.f;
+            float dot = wave_dot(R->router_w + (size_t)e * H, x + (size_t)t * H, H);
 #pragma unroll
             for (int m = kWave / 2; m >= 1; m >>= 1) dot += __shfl_xor(dot, m, kWave);
             dot += bias;
             // lane r: the copy that the workgroups with b % kLogitReplicas == r read
             if (lane < kLogitReplicas)
-                __hip_atomic_store(ra.tagged_logits + (size_t)lane * TE + q,
+                __hip_atomic_store(glob(R->tagged_logits) + (size_t)lane * TE + q,
                                    ((unsigned long long)rwtag << 32) | __float_as_uint(dot), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
-            if (lane == 0 && ra.logits_opt) ra.logits_opt[q] = dot;
+            if (lane == 0 && R->logits_opt) *glob(R->logits_opt + q) = dot;
         }
         first_shared_item();
+        R = route_args();
         {
             // one wavefront per token ranks its logits; then histogram, slot lookup, miss list and per-slot lists
             // out of LDS (which nothing else uses yet: the first tile is still on its way)
@@ -446,7 +475,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
             for (int i = tid; i < C * ((T + 31) >> 5); i += kThreads) L.cnt_s[i] = 0;
             lds_f32 *lg = L.lg_s + w * lg_stride(E);
             for (int t = w; t < T; t += kWaves) {   // (one token per wavefront up to 16 tokens, two up to 32)
-                const unsigned long long *src = ra.tagged_logits + (size_t)(b % kLogitReplicas) * TE + (size_t)t * E;
+                const auto src = glob(R->tagged_logits) + (size_t)(b % kLogitReplicas) * TE + (size_t)t * E;
                 for (int e0 = 0; e0 < E; e0 += kWave) {
                     const int e = e0 + lane;
                     unsigned long long v = (unsigned long long)rtag << 32;
@@ -455,7 +484,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
                         if (e < E) v = __hip_atomic_load(src + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         if (__ballot((unsigned)(v >> 32) != rtag) == 0ull) break;
                         if (++polls > rspin) {   // cannot happen on a healthy device; never wait for ever
-                            if (lane == 0) atomicOr(ra.error_flag, 1u);
+                            if (lane == 0) atomicOr(R->error_flag, 1u);
                             break;
                         }
                         __builtin_amdgcn_s_sleep(2);
@@ -468,55 +497,75 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
                 __builtin_amdgcn_wave_barrier();
                 // (up to 128 experts here: the ranking of more needs so many registers that the whole
                 // kernel would be launched with scratch memory; those batches keep the routing kernel)
-                int32_t *const idx_out = b == 0 ? ra.topk_idx + (size_t)t * ra.k : nullptr;
-                float *const w_out = b == 0 ? ra.topk_w + (size_t)t * ra.k : nullptr;
+                int32_t *const idx_out = b == 0 ? R->topk_idx + (size_t)t * a.k : nullptr;
+                float *const w_out = b == 0 ? R->topk_w + (size_t)t * a.k : nullptr;
                 if (E <= kWave)
-                    wave_topk_gate_n<1>(E, ra.k, idx_out, L.idx_s + t * ra.k, w_out, lg);
+                    wave_topk_gate_n<1>(E, a.k, idx_out, L.idx_s + t * a.k, w_out, lg);
                 else
-                    wave_topk_gate_n<2>(E, ra.k, idx_out, L.idx_s + t * ra.k, w_out, lg);
+                    wave_topk_gate_n<2>(E, a.k, idx_out, L.idx_s + t * a.k, w_out, lg);
             }
+            // (few slots, and the lists' places below not where the ranking keeps its own data)
+            short_lists = C <= kWave && (size_t)((unsigned char *)ctl_s - lds) >= post_lds_bytes(E, C, A, true);
             __syncthreads();
-            if (b != 0 && A <= kWave && C <= kWave) {
-                // Few enough for one wavefront: no barrier between the steps, every LDS read before the first write
-                // (the lists' places may lie where the ranking kept its own data), offsets and masks from lane to lane.
-                // Only workgroup 0, which also writes the step outputs, goes the long way.  (5 tokens, 8 experts of 256 x 512:
-                // 16.8 -> 16.1 us per layer, 64 experts one token 30.9 -> 30.7; with shared experts, whose first tiles
-                // are on their way meanwhile, 0.2 us.)
-                if (w == 0) {
-                    const int tok = udiv_rcp(lane, a.k, a.rcp_k);
-                    int c = -1;
-                    if (lane < A) {
-                        c = L.tab_s[L.idx_s[lane]];
-                        if ((unsigned)c >= (unsigned)C) c = -1;
-                        if (c >= 0) __hip_atomic_fetch_or(&L.cnt_s[c], 1 << tok, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    }
-                    __builtin_amdgcn_wave_barrier();   // (LDS operations of one wavefront execute in order)
+            if (short_lists) {
+                // Every wavefront that has an assignment works the slots' prefix sums out for itself, from ballots; with up to 64
+                // assignments that is the first one only, and no barrier.  What of this the step outputs and the down kernel
+                // want in memory, workgroup 0 writes later, with its first tiles on their way: it used to build the lists through memory
+                // and was 2 us behind the others (5 tokens, 8 experts of 256 x 512: its end was the launch's).
+                for (int i = tid; i < A; i += kThreads) {
+                    const int c = L.tab_s[L.idx_s[i]];
+                    if ((unsigned)c < (unsigned)C)
+                        __hip_atomic_fetch_or(&L.cnt_s[c], 1 << udiv_rcp(i, a.k, a.rcp_k), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+                if (A <= kWave) __builtin_amdgcn_wave_barrier();   // (LDS operations of one wavefront execute in order)
+                else __syncthreads();
+                const int i = w * kWave + lane;   // (A <= kThreads)
+                if (w * kWave < A) {
                     const unsigned mask = lane < C ? (unsigned)__hip_atomic_load(&L.cnt_s[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0u;
                     const int cntv = __popc(mask);
                     const unsigned long long before = (1ull << lane) - 1ull, act = __ballot(cntv > 0);
-                    int off = 0;   // prefix sum of the counts, from a ballot for each bit of them
-                    for (int bit = 0; (1 << bit) <= T; ++bit) off += __popcll(__ballot((cntv >> bit) & 1) & before) << bit;
+                    int off = 0, n_listed = 0;   // prefix sum of the counts, from a ballot for each bit of them
+                    for (int bit = 0; (1 << bit) <= T; ++bit) {
+                        const unsigned long long on = __ballot((cntv >> bit) & 1);
+                        off += __popcll(on & before) << bit;
+                        n_listed += __popcll(on) << bit;
+                    }
+                    int c = -1;
+                    const int tok = udiv_rcp(i, a.k, a.rcp_k);
+                    if (i < A) {
+                        c = L.tab_s[L.idx_s[i]];
+                        if ((unsigned)c >= (unsigned)C) c = -1;
+                    }
                     const int at = c >= 0 ? c : 0;
                     const int off_c = __builtin_amdgcn_ds_bpermute(at << 2, off);
                     const unsigned mask_c = (unsigned)__builtin_amdgcn_ds_bpermute(at << 2, (int)mask);
-                    const int n_listed = __popcll(__ballot(c >= 0));
-                    __builtin_amdgcn_wave_barrier();
-                    if (lane < C) {
-                        count_s[lane] = cntv;
-                        offset_s[lane] = off;
-                        if (lane >= __popcll(act)) active_s[lane] = 0;       // (never used; stay inside the pool)
-                        if (cntv > 0) active_s[__popcll(act & before)] = lane;
+                    if (w == 0) {
+                        if (lane < C) {
+                            count_s[lane] = cntv;
+                            offset_s[lane] = off;
+                            if (lane >= __popcll(act)) active_s[lane] = 0;       // (never used; stay inside the pool)
+                            if (cntv > 0) active_s[__popcll(act & before)] = lane;
+                        }
+                        if (lane == 0) odesc_s[0] = __popcll(act);
                     }
-                    if (lane < A) {
-                        if (lane >= n_listed) perm_s[lane] = 0;
-                        if (c >= 0) perm_s[off_c + __popc(mask_c & ((1u << tok) - 1u))] = tok;   // token of each list entry
+                    if (i < A) {
+                        const int p = c >= 0 ? off_c + __popc(mask_c & ((1u << tok) - 1u)) : -1;
+                        if (i >= n_listed) perm_s[i] = 0;
+                        if (p >= 0) perm_s[p] = tok;   // token of each list entry
+                        L.sidx_s[i] = p;
                     }
-                    if (lane == 0) odesc_s[0] = __popcll(act);
                 }
                 __syncthreads();
                 n_act = __builtin_amdgcn_readfirstlane(odesc_s[0]);
             } else {
-                const SmallLists sl = block_post_small<false>(L.idx_s, L.tab_s, T, ra.k, E, C, ra, L.hist_s, L.cnt_s, L.scan_s,
+                RouteArgs ra = {};
+                {
+                    k_route *const Q = route_args();
+                    ra.slot_idx = Q->slot_idx; ra.miss_list = Q->miss_list; ra.miss_count = Q->miss_count; ra.hist = Q->hist;
+                    ra.slot_count = Q->slot_count; ra.slot_offset = Q->slot_offset; ra.active_slots = Q->active_slots;
+                    ra.n_active = Q->n_active; ra.perm = Q->perm; ra.pos = Q->pos;
+                }
+                const SmallLists sl = block_post_small<false>(L.idx_s, L.tab_s, T, a.k, E, C, ra, L.hist_s, L.cnt_s, L.scan_s,
                                                               L.off_s, rwtag, b == 0);
                 __syncthreads();   // (the lists' places below may lie where the ranking kept its own data)
                 if (tid < C) {
@@ -526,27 +575,69 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
                     if (tid >= sl.n_active) active_s[tid] = 0;       // (never used; stay inside the pool)
                 }
                 if (tid < A) {
-                    if (sl.pos >= 0) perm_s[sl.pos] = tid / ra.k;    // token of each list entry
+                    if (sl.pos >= 0) perm_s[sl.pos] = tid / a.k;    // token of each list entry
                     if (tid >= sl.n_listed) perm_s[tid] = 0;
                 }
                 n_act = __builtin_amdgcn_readfirstlane(sl.n_active);
             }
-            if (b == 0) {
-                for (int i = tid; i < G; i += kThreads) {
-                    int polls = 0;
-                    while ((unsigned)(__hip_atomic_load(seen + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32) != rtag) {
-                        if (++polls > rspin) {
-                            atomicOr(ra.error_flag, 1u);
-                            break;
-                        }
-                        __builtin_amdgcn_s_sleep(2);
-                    }
-                }
-            }
             __syncthreads();
-            if (b == 0 && tid == 0) *ra.epoch = rtag;
         }
     }
+    // FUSED, workgroup 0: the step outputs and the lists in memory, out of what the routing steps left in LDS (where nothing has
+    // been parked yet).
+    auto step_outputs = [&]() {
+        k_route *const R = route_args();
+        const int A = a.T * a.k, C = a.C, E = R->E;
+        const PostLds L = carve_lds((int *)lds, E, C, A);
+        if (tid < A) {
+            const int e = L.idx_s[tid], p = L.sidx_s[tid];
+            int c = L.tab_s[e];
+            if ((unsigned)c >= (unsigned)C) c = -1;
+            __hip_atomic_fetch_add(&L.hist_s[e], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            *glob(R->slot_idx + tid) = c;
+            *glob(R->pos + tid) = p;
+            if (p >= 0) *glob(R->perm + p) = tid;
+        }
+        if (tid < C) {
+            *glob(R->slot_count + tid) = count_s[tid];
+            *glob(R->slot_offset + tid) = offset_s[tid];
+            if (tid < n_act) *glob(R->active_slots + tid) = active_s[tid];
+        }
+        if (w == kWaves - 1) {
+            int base = 0;
+            for (int i0 = 0; i0 < A; i0 += kWave) {
+                const bool miss = i0 + lane < A && L.sidx_s[i0 + lane] < 0;
+                const unsigned long long bal = __ballot(miss);
+                if (miss) *glob(R->miss_list + base + __popcll(bal & ((1ull << lane) - 1ull))) = i0 + lane;
+                base += __popcll(bal);
+            }
+            if (lane == 0) {
+                *glob(R->miss_count) = base;
+                *glob(R->slot_offset + C) = offset_s[C - 1] + count_s[C - 1];
+                *glob(R->n_active) = (unsigned)n_act;
+            }
+        }
+        __syncthreads();
+        if (tid < E) *glob(R->hist + tid) = L.hist_s[tid];
+        __syncthreads();   // (the tile goes where the counts are)
+    };
+    // ... and the call's number in the control block, once every workgroup has read the old one.
+    auto count_call = [&]() {
+        k_route *const R = route_args();
+        const auto seen = glob(R->lists_pub) + (size_t)kListReplicas * list_pub_entries(a.T, a.k, a.C);
+        for (int i = tid; i < G; i += kThreads) {
+            int polls = 0;
+            while ((unsigned)(__hip_atomic_load(seen + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32) != rtag) {
+                if (++polls > rspin) {
+                    atomicOr(R->error_flag, 1u);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(2);
+            }
+        }
+        __syncthreads();
+        if (tid == 0) *glob(R->epoch) = rtag;
+    };
     if (FUSED) {
         // (the lists are in LDS already)
     } else {
@@ -683,6 +774,10 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         }
     };
     if (cnt == 0) {
+        if (FUSED && b == 0) {
+            if (short_lists) step_outputs();
+            count_call();
+        }
         join();
         return;
     }
@@ -849,6 +944,10 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     prod_advance();
     issue(1);
     prod_advance();
+    if (FUSED && b == 0) {
+        if (short_lists) step_outputs();
+        count_call();
+    }
     static_assert(NPI >= 1 && NPI <= 4, "the wait below names the number of loads of one tile");
     __builtin_amdgcn_s_waitcnt(0x0F70 | NPI);   // vmcnt(NPI)
 
@@ -879,17 +978,16 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
 template <bool GATEUP, int NPI, int MODE, bool JOIN, bool WSPLIT = false, bool RAGGED = false>
 __global__ __launch_bounds__(kThreads) void stream_kernel(StreamArgs a, int tile_lds_bytes, JoinArgs jn)
 {
-    const RouteArgs none = {};
-    stream_body<GATEUP, NPI, MODE, JOIN, WSPLIT, false, RAGGED>(a, tile_lds_bytes, jn, none);
+    stream_body<GATEUP, NPI, MODE, JOIN, WSPLIT, false, RAGGED>(a, tile_lds_bytes, jn);
 }
 
 // The small-batch gate/up kernel with steps 1-3 of the layer in front of it (one launch less per layer, and the
 // shared experts' weights stream while the routing runs).
 template <int NPI, int MODE, bool RAGGED = false>
-__global__ __launch_bounds__(kThreads) void routed_stream_kernel(StreamArgs a, int tile_lds_bytes, RouteArgs ra)
+__global__ __launch_bounds__(kThreads) void routed_stream_kernel(RoutedArgs r)
 {
     const JoinArgs none = {};
-    stream_body<true, NPI, MODE, false, false, true, RAGGED>(a, tile_lds_bytes, none, ra);
+    stream_body<true, NPI, MODE, false, false, true, RAGGED>(r.a, r.tile_lds_bytes, none);
 }
 
 // out[t,:] (+)= sum_j w[t,j] * o[pos[t,j],:] + sum_i o_sh[i,t,:], in a fixed order
@@ -1104,11 +1202,9 @@ hipError_t launch_stream_routed(const StreamArgs &a, const RouteArgs &r, hipStre
     if (e != hipSuccess) return e;
     const int grid = device_cus(&e);
     if (e != hipSuccess) return e;
-    int tile_i = (int)tile;
-    StreamArgs args = a;
-    fill_derived(args, true, grid);
-    RouteArgs rargs = r;
-    void *params[] = {&args, &tile_i, &rargs};
+    RoutedArgs args = {r, a, (int)tile};
+    fill_derived(args.a, true, grid);
+    void *params[] = {&args};
     hipError_t le = launch_timed(fn, dim3(grid), dim3(kThreads), params, lds, s, 2);
     if (le != hipSuccess) return le;
     return hipGetLastError();

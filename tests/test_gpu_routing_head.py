@@ -1,0 +1,46 @@
+"""The routing steps where their paths meet: rows of the router that are not whole 2048s (dot products), 64 and 128 experts
+(ranking), 64 and 1024 assignments, 64 slots, and scratch memory that does or does not reach the lists' place (lists)."""
+import numpy as np
+import pytest
+
+from paper_2603_09983_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # T, k, E, C, H
+    (1, 1, 1, 1, 8), (13, 5, 70, 64, 256), (16, 64, 128, 64, 64), (32, 32, 128, 64, 64), (32, 8, 64, 63, 264),
+    (9, 8, 128, 64, 1408), (4, 6, 64, 64, 2040), (17, 6, 65, 65, 2056), (3, 2, 9, 9, 4104), (33, 4, 64, 20, 520),
+    (70, 3, 64, 40, 2040), (129, 2, 64, 33, 72)]
+
+
+@pytest.mark.parametrize("T,k,E,C,H", CASES)
+def test_layer(T, k, E, C, H):
+    import gpu_util as G
+    li = synth.make_layer(synth.small_recipe("head", 70 + T + k, T=T, H=H, F=64, E=E, k=k, C=C, hidden="unit"), margin=1e-5)
+    print(f"[case] {T} {k} {E} {C} {H}", flush=True)
+    d = G.upload(li)
+    buf = G.run_layer(d)
+    G.run_layer(d, buf)   # again on the same workspace
+    G.check_against_oracle(li, buf, tag=f"{T} {k} {E} {C} {H}", rms_over_nonzero_rows=True)
+
+
+@pytest.mark.parametrize("T,H,E", [(1, 8, 5), (5, 264, 64), (70, 2040, 64), (129, 2056, 64), (257, 2048, 130), (513, 4104, 64)])
+def test_logits(T, H, E):
+    import torch
+    from paper_2603_09983_amd import binding as B
+    print(f"[case] {T} {H} {E}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + H)
+    x = torch.randn(T, H, device="cuda", generator=g).bfloat16()
+    w = torch.randn(E, H, device="cuda", generator=g) * 0.02
+    bias = torch.randn(E, device="cuda", generator=g)
+    idx = torch.zeros(T, 2, dtype=torch.int32, device="cuda")
+    gate, logits = torch.zeros(T, 2, device="cuda"), torch.zeros(T, E, device="cuda")
+    ws = B.new_workspace(B.make_shape(T, H, E, 2, 64, 0))
+    B.moe_route_topk(x, w, bias, T, H, E, 2, idx, gate, logits, ws)
+    ref = x.double() @ w.double().T + bias.double()
+    # a lane adds H / 256 + 1 terms of four products, six more additions over the wavefront, one of the bias: so many roundings
+    # of at most the sum of the magnitudes
+    bound = (x.double().abs() @ w.double().abs().T + bias.double().abs()) * (H / 256 + 13) * 2.0 ** -24
+    assert bool(((logits.double() - ref).abs() <= bound).all())
+    assert torch.equal(idx.long(), logits.topk(2, dim=1).indices)
