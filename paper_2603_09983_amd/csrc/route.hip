@@ -25,6 +25,12 @@ namespace moe {
 
 namespace {
 
+// More dot products than this: four tokens to a wavefront.  256 workgroups of sixteen wavefronts do 4096 at a time, so with more than
+// three times as many every wavefront still has four tokens' loads in flight, and the router row comes once for them (256 tokens, 64
+// experts, H = 2048: 17.6 -> 13.6 us behind a layer's weights).  With fewer, half of the wavefronts would have none: 128 tokens 14.8 us so,
+// 12.6 with one dot product each.
+constexpr int kFourTokens = 12288;
+
 __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs a)
 {
     extern __shared__ int dyn[];
@@ -47,6 +53,30 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs a)
 
     // s[t,e] = W_g[e,:] . h[t,:]: one wavefront per dot product, lanes stride H four at a time
     const uint16_t *x = (const uint16_t *)a.hidden;
+    if (TE > kFourTokens) {
+        // ... or four tokens' dot products with one expert (lane i of the wavefront hands on the i-th)
+        const int n_tasks = (T + 3) / 4 * E;
+        for (int q = b + w * G; q < n_tasks; q += G * kRouteWaves) {
+            const int t0 = q / E * 4, e = q - t0 / 4 * E;
+            const float bias = a.router_bias ? a.router_bias[e] : 0.f;
+            const uint16_t *xr[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) xr[i] = x + (size_t)(t0 + i < T ? t0 + i : T - 1) * H;
+            float acc[4];
+            wave_dot4(a.router_w + (size_t)e * H, xr, H, acc);
+#pragma unroll
+            for (int m = kWave / 2; m >= 1; m >>= 1)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[i] += __shfl_xor(acc[i], m, kWave);
+            const float s = (lane == 0 ? acc[0] : lane == 1 ? acc[1] : lane == 2 ? acc[2] : acc[3]) + bias;
+            if (lane < 4 && t0 + lane < T) {
+                const size_t at = (size_t)(t0 + lane) * E + e;
+                __hip_atomic_store(a.tagged_logits + at, ((unsigned long long)wtag << 32) | __float_as_uint(s), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+                if (a.logits_opt) a.logits_opt[at] = s;
+            }
+        }
+    } else
     for (int q = b + w * G; q < TE; q += G * kRouteWaves) {
         const int t = q / E, e = q - t * E;
         const float bias = a.router_bias ? a.router_bias[e] : 0.f;

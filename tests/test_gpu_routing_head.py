@@ -24,7 +24,8 @@ def test_layer(T, k, E, C, H):
     G.check_against_oracle(li, buf, tag=f"{T} {k} {E} {C} {H}", rms_over_nonzero_rows=True)
 
 
-@pytest.mark.parametrize("T,H,E", [(1, 8, 5), (5, 264, 64), (70, 2040, 64), (129, 2056, 64), (257, 2048, 130), (513, 4104, 64)])
+@pytest.mark.parametrize("T,H,E", [(1, 8, 5), (5, 264, 64), (70, 2040, 64), (129, 2056, 64), (257, 2048, 130), (513, 4104, 64), (193, 1032, 64), (192, 264, 65),
+                                   (3073, 8, 5)])
 def test_logits(T, H, E):
     import torch
     from paper_2603_09983_amd import binding as B
