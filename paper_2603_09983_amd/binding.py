@@ -25,6 +25,12 @@ if not os.path.exists(LIB_PATH):
 
 _lib = ctypes.CDLL(LIB_PATH)
 
+try:
+    from ._pointers import pointers as _pointers
+except ImportError as e:
+    raise ImportError(f"{os.path.join(_HERE, '_pointers.so')} is missing or does not load ({e}): build it with "
+                      "`python -c 'import __graft_entry__ as g; g.build()'`") from e
+
 OK, ERR_NULL, ERR_SHAPE, ERR_ALIGN, ERR_WORKSPACE, ERR_LAUNCH, ERR_SCRATCH = 0, -1, -2, -3, -4, -5, -6
 STATIC_SCRATCH_BYTES = 16 << 20
 
@@ -203,53 +209,50 @@ def new_workspace(shape: MoeShape, device="cuda") -> torch.Tensor:
 
 def moe_route_topk(hidden, router_w, router_bias, T, H, E, k, topk_idx, topk_w, logits_opt, workspace,
                    stream=None, check=True) -> int:
-    rc = _lib.moe_route_topk(_ptr(hidden), _ptr(router_w), _ptr(router_bias), T, H, E, k, _ptr(topk_idx),
-                             _ptr(topk_w), _ptr(logits_opt), _ptr(workspace),
-                             0 if workspace is None else workspace.numel(), _stream(stream))
+    p = _pointers(hidden, router_w, router_bias, topk_idx, topk_w, logits_opt, workspace)
+    rc = _lib.moe_route_topk(p[0], p[1], p[2], T, H, E, k, *p[3:], 0 if workspace is None else workspace.numel(),
+                             _stream(stream))
     return _check(rc, "moe_route_topk", check)
 
 
 def moe_expert_histogram(topk_idx, T, k, E, hist, stream=None, check=True) -> int:
-    return _check(_lib.moe_expert_histogram(_ptr(topk_idx), T, k, E, _ptr(hist), _stream(stream)),
+    p = _pointers(topk_idx, hist)
+    return _check(_lib.moe_expert_histogram(p[0], T, k, E, p[1], _stream(stream)),
                   "moe_expert_histogram", check)
 
 
 def moe_slot_resolve(topk_idx, slot_table, T, k, E, C, slot_idx, miss_list, miss_count, workspace,
                      stream=None, check=True) -> int:
-    rc = _lib.moe_slot_resolve(_ptr(topk_idx), _ptr(slot_table), T, k, E, C, _ptr(slot_idx), _ptr(miss_list),
-                               _ptr(miss_count), _ptr(workspace),
-                               0 if workspace is None else workspace.numel(), _stream(stream))
+    p = _pointers(topk_idx, slot_table, slot_idx, miss_list, miss_count, workspace)
+    rc = _lib.moe_slot_resolve(p[0], p[1], T, k, E, C, *p[2:], 0 if workspace is None else workspace.numel(),
+                               _stream(stream))
     return _check(rc, "moe_slot_resolve", check)
 
 
 def moe_grouped_ffn(hidden, topk_w, slot_idx, w_gate, w_up, w_down, T, H, F, k, C, out, out_bf16, accumulate,
                     workspace, stream=None, check=True) -> int:
-    rc = _lib.moe_grouped_ffn(_ptr(hidden), _ptr(topk_w), _ptr(slot_idx), _ptr(w_gate), _ptr(w_up),
-                              _ptr(w_down), T, H, F, k, C, _ptr(out), int(out_bf16), int(accumulate),
-                              _ptr(workspace), 0 if workspace is None else workspace.numel(), _stream(stream))
+    p = _pointers(hidden, topk_w, slot_idx, w_gate, w_up, w_down, out, workspace)
+    rc = _lib.moe_grouped_ffn(*p[:6], T, H, F, k, C, p[6], int(out_bf16), int(accumulate), p[7],
+                              0 if workspace is None else workspace.numel(), _stream(stream))
     return _check(rc, "moe_grouped_ffn", check)
 
 
 def moe_verify_layer(shape: MoeShape, hidden, router_w, router_bias, slot_table, w_gate, w_up, w_down,
                      shared_gate, shared_up, shared_down, topk_idx, topk_w, hist, slot_idx, miss_list,
                      miss_count, out, out_bf16, accumulate, workspace, stream=None, check=True) -> int:
-    rc = _lib.moe_verify_layer(ctypes.byref(shape), _ptr(hidden), _ptr(router_w), _ptr(router_bias),
-                               _ptr(slot_table), _ptr(w_gate), _ptr(w_up), _ptr(w_down), _ptr(shared_gate),
-                               _ptr(shared_up), _ptr(shared_down), _ptr(topk_idx), _ptr(topk_w), _ptr(hist),
-                               _ptr(slot_idx), _ptr(miss_list), _ptr(miss_count), _ptr(out), int(out_bf16),
-                               int(accumulate), _ptr(workspace), 0 if workspace is None else workspace.numel(),
-                               _stream(stream))
+    p = _pointers(hidden, router_w, router_bias, slot_table, w_gate, w_up, w_down, shared_gate, shared_up, shared_down,
+                  topk_idx, topk_w, hist, slot_idx, miss_list, miss_count, out, workspace)
+    rc = _lib.moe_verify_layer(ctypes.byref(shape), *p[:17], int(out_bf16), int(accumulate), p[17],
+                               0 if workspace is None else workspace.numel(), _stream(stream))
     return _check(rc, "moe_verify_layer", check)
 
 
 def moe_verify_layer_static(shape: MoeShape, hidden, router_w, router_bias, slot_table, w_gate, w_up, w_down,
                             shared_gate, shared_up, shared_down, topk_idx, topk_w, hist, slot_idx, miss_list,
                             miss_count, out, out_bf16, accumulate, stream=None, check=True) -> int:
-    rc = _lib.moe_verify_layer_static(ctypes.byref(shape), _ptr(hidden), _ptr(router_w), _ptr(router_bias),
-                                      _ptr(slot_table), _ptr(w_gate), _ptr(w_up), _ptr(w_down), _ptr(shared_gate),
-                                      _ptr(shared_up), _ptr(shared_down), _ptr(topk_idx), _ptr(topk_w), _ptr(hist),
-                                      _ptr(slot_idx), _ptr(miss_list), _ptr(miss_count), _ptr(out), int(out_bf16),
-                                      int(accumulate), _stream(stream))
+    p = _pointers(hidden, router_w, router_bias, slot_table, w_gate, w_up, w_down, shared_gate, shared_up, shared_down,
+                  topk_idx, topk_w, hist, slot_idx, miss_list, miss_count, out)
+    rc = _lib.moe_verify_layer_static(ctypes.byref(shape), *p, int(out_bf16), int(accumulate), _stream(stream))
     return _check(rc, "moe_verify_layer_static", check)
 
 
@@ -260,30 +263,29 @@ def moe_utility_init(f_prev, s, theta_up, theta_dn, L, N, gamma, stream=None, ch
 
 def moe_utility_update(f, f_prev, s, theta_up, theta_dn, slot_table, n_tau, L, N, K, lam_num, lam_den,
                        stream=None, check=True) -> int:
-    rc = _lib.moe_utility_update(_ptr(f), _ptr(f_prev), _ptr(s), _ptr(theta_up), _ptr(theta_dn),
-                                 _ptr(slot_table), _ptr(n_tau), L, N, K, lam_num, lam_den, _stream(stream))
+    rc = _lib.moe_utility_update(*_pointers(f, f_prev, s, theta_up, theta_dn, slot_table, n_tau), L, N, K, lam_num, lam_den,
+                                 _stream(stream))
     return _check(rc, "moe_utility_update", check)
 
 
 def moe_balance_threshold(f, n_tau, r_c, r_g, L, N, K, gamma, k, params: BalanceParams, tau_out, b_out=None,
                           stream=None, check=True) -> int:
-    rc = _lib.moe_balance_threshold(_ptr(f), _ptr(n_tau), _ptr(r_c), _ptr(r_g), L, N, K, gamma, k,
-                                    ctypes.byref(params), _ptr(tau_out), _ptr(b_out), _stream(stream))
+    p = _pointers(f, n_tau, r_c, r_g, tau_out, b_out)
+    rc = _lib.moe_balance_threshold(*p[:4], L, N, K, gamma, k, ctypes.byref(params), *p[4:], _stream(stream))
     return _check(rc, "moe_balance_threshold", check)
 
 
 def moe_cache_plan(s, in_use, slot_table, tau, budget, L, N, C, K, evict_list, n_evict, fetch_list, fetch_slot,
                    n_fetch, stream=None, check=True) -> int:
-    rc = _lib.moe_cache_plan(_ptr(s), _ptr(in_use), _ptr(slot_table), _ptr(tau), _ptr(budget), L, N, C, K,
-                             _ptr(evict_list), _ptr(n_evict), _ptr(fetch_list), _ptr(fetch_slot), _ptr(n_fetch),
-                             _stream(stream))
+    p = _pointers(s, in_use, slot_table, tau, budget, evict_list, n_evict, fetch_list, fetch_slot, n_fetch)
+    rc = _lib.moe_cache_plan(*p[:5], L, N, C, K, *p[5:], _stream(stream))
     return _check(rc, "moe_cache_plan", check)
 
 
 def moe_pool_load(store_gate, store_up, store_down, pool_gate, pool_up, pool_down, fetch_list, fetch_slot, n_fetch,
                   max_fetch, H, F, stream=None, check=True) -> int:
-    rc = _lib.moe_pool_load(_ptr_store(store_gate), _ptr_store(store_up), _ptr_store(store_down), _ptr(pool_gate), _ptr(pool_up),
-                            _ptr(pool_down), _ptr(fetch_list), _ptr(fetch_slot), _ptr(n_fetch), max_fetch, H, F,
+    rc = _lib.moe_pool_load(_ptr_store(store_gate), _ptr_store(store_up), _ptr_store(store_down),
+                            *_pointers(pool_gate, pool_up, pool_down, fetch_list, fetch_slot, n_fetch), max_fetch, H, F,
                             _stream(stream))
     return _check(rc, "moe_pool_load", check)
 

@@ -1,4 +1,4 @@
-"""Builds libmoe_spac.so (HIP, gfx950 only) next to this file.
+"""Builds libmoe_spac.so (HIP, gfx950 only) and the binding's _pointers.so (host code) next to this file.
 
 Each source is compiled to an object of its own (in parallel; objects live in _build/, which is not
 tracked) and the objects are linked into the shared library."""
@@ -14,6 +14,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmoe_spac.so")
+LIB_POINTERS = os.path.join(HERE, "_pointers.so")        # the binding's reading of tensor addresses (host code only)
 LIB_TRACE = os.path.join(HERE, "libmoe_spac_trace.so")   # same sources with the timeline stamps compiled in
 SOURCES = ["api.hip", "route.hip", "ffn.hip", "stream.hip", "wide.hip", "layer.hip", "estimator.hip", "balancer.hip", "cache.hip"]
 HEADERS = [os.path.join(CSRC, h) for h in ("moe_internal.h", "route_device.h", "wide_device.h")] + \
@@ -33,9 +34,11 @@ def _headers():
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB):
+    if not (os.path.exists(LIB) and os.path.exists(LIB_POINTERS)):
         return True
-    t = os.path.getmtime(LIB)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(LIB_POINTERS))
+    if os.path.getmtime(os.path.join(CSRC, "pointers.cpp")) > t:
+        return True
     return any(os.path.getmtime(p) > t for p in [os.path.join(CSRC, s) for s in _sources()] + _headers())
 
 
@@ -48,6 +51,17 @@ def _run(cmd, verbose):
         raise RuntimeError("hipcc failed:\n" + out)
     if verbose and out.strip():
         print(out)
+
+
+def pointers_cmd():
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+            + ["-isystem" + d for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]]
+            + [os.path.join(CSRC, "pointers.cpp"), "-L" + lib_dir, "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", LIB_POINTERS])
 
 
 def build_hip(force: bool = True, verbose: bool = False, trace: bool = False, jobs: int = 8) -> str:
@@ -65,6 +79,7 @@ def build_hip(force: bool = True, verbose: bool = False, trace: bool = False, jo
         objs.append(obj)
         if force or not os.path.exists(obj) or os.path.getmtime(obj) < max(os.path.getmtime(src), newest_header):
             todo.append(["hipcc"] + FLAGS + extra + ["-c", src, "-o", obj])
+    todo.append(pointers_cmd())
     with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(todo) or 1))) as ex:
         list(ex.map(lambda c: _run(c, verbose), todo))
     _run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", out_path], verbose)
