@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs a)
         const int n_tasks = (T + 3) / 4 * E;
         for (int q = b + w * G; q < n_tasks; q += G * kRouteWaves) {
             const int t0 = q / E * 4, e = q - t0 / 4 * E;
-            const float bias = a.router_bias ? a.router_bias[e] : 0.f;
+            const float bias = a.router_bias ? load_bias(a.router_bias, e) : 0.f;
             const uint16_t *xr[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) xr[i] = x + (size_t)(t0 + i < T ? t0 + i : T - 1) * H;
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs a)
     } else
     for (int q = b + w * G; q < TE; q += G * kRouteWaves) {
         const int t = q / E, e = q - t * E;
-        const float bias = a.router_bias ? a.router_bias[e] : 0.f;
+        const float bias = a.router_bias ? load_bias(a.router_bias, e) : 0.f;
         float acc = wave_dot(a.router_w + (size_t)e * H, x + (size_t)t * H, H);
 #pragma unroll
         for (int m = kWave / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, kWave);

@@ -450,7 +450,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         const uint16_t *x = (const uint16_t *)R->hidden;
         for (int q = b + w * G; q < TE; q += G * kWaves) {
             const int t = q / E, e = q - t * E;
-            const float bias = R->router_bias ? *glob(R->router_bias + e) : 0.f;
+            const float bias = R->router_bias ? load_bias(R->router_bias, e) : 0.f;
             float dot = wave_dot(R->router_w + (size_t)e * H, x + (size_t)t * H, H);
 #pragma unroll
             for (int m = kWave / 2; m >= 1; m >>= 1) dot += __shfl_xor(dot, m, kWave);
