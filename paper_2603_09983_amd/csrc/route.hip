@@ -105,7 +105,23 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs a)
     }
     const bool idx_in_lds = A <= kLdsCopy;
     lds_f32 *lg = L.lg_s + w * lg_stride(E);
-    for (int t = share_ids ? b * kRouteWaves + w : w; t < T; t += share_ids ? T : kRouteWaves) {
+    // (a workgroup's sixteen tokens, few experts: four to a wavefront)
+    const bool by_rows = share_ids && idx_in_lds && E <= kWave && a.k <= 16;
+    if (by_rows) {
+        const int t0 = b * kRouteWaves + w * 4, t_end = T < (b + 1) * kRouteWaves ? T : (b + 1) * kRouteWaves;
+        if (t0 < t_end) {
+            if (!rows_topk_gate(E, a.k, t0, t_end, a.tagged_logits, tag, spin, L.idx_s, a.topk_idx, a.topk_w) && lane == 0)
+                atomicOr(a.error_flag, 1u);
+            // (LDS operations of one wavefront execute in order: the ids written above are visible)
+            __builtin_amdgcn_wave_barrier();
+            const int n = (t_end - t0 < 4 ? t_end - t0 : 4) * a.k;
+            if (lane < n)
+                __hip_atomic_store(a.tagged_idx + (size_t)t0 * a.k + lane,
+                                   ((unsigned long long)wtag << 32) | (unsigned)L.idx_s[t0 * a.k + lane], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    for (int t = by_rows ? T : share_ids ? b * kRouteWaves + w : w; t < T; t += share_ids ? T : kRouteWaves) {
         // wait (a bounded number of polls) until every logit of token t carries the tag
         const unsigned long long *src = a.tagged_logits + (size_t)t * E;
         for (int e0 = 0; e0 < E; e0 += kWave) {

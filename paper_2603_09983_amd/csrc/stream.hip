@@ -474,7 +474,13 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
             }
             for (int i = tid; i < C * ((T + 31) >> 5); i += kThreads) L.cnt_s[i] = 0;
             lds_f32 *lg = L.lg_s + w * lg_stride(E);
-            for (int t = w; t < T; t += kWaves) {   // (one token per wavefront up to 16 tokens, two up to 32)
+            // (more tokens than wavefronts, and few enough experts: four to a wavefront)
+            const bool by_rows = MODE == 1 && E <= kWave && a.k <= 16;
+            if (by_rows && w * 4 < T &&
+                !rows_topk_gate(E, a.k, w * 4, T, R->tagged_logits + (size_t)(b % kLogitReplicas) * TE, rtag, rspin, L.idx_s,
+                                b == 0 ? R->topk_idx : nullptr, R->topk_w) && lane == 0)
+                atomicOr(R->error_flag, 1u);
+            for (int t = by_rows ? T : w; t < T; t += kWaves) {   // (one token per wavefront up to 16 tokens, two up to 32)
                 const auto src = glob(R->tagged_logits) + (size_t)(b % kLogitReplicas) * TE + (size_t)t * E;
                 for (int e0 = 0; e0 < E; e0 += kWave) {
                     const int e = e0 + lane;

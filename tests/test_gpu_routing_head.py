@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 CASES = [  # T, k, E, C, H
     (1, 1, 1, 1, 8), (13, 5, 70, 64, 256), (16, 64, 128, 64, 64), (32, 32, 128, 64, 64), (32, 8, 64, 63, 264),
     (9, 8, 128, 64, 1408), (4, 6, 64, 64, 2040), (17, 6, 65, 65, 2056), (3, 2, 9, 9, 4104), (33, 4, 64, 20, 520),
-    (70, 3, 64, 40, 2040), (129, 2, 64, 33, 72)]
+    (70, 3, 64, 40, 2040), (129, 2, 64, 33, 72), (17, 6, 64, 48, 256), (19, 16, 64, 64, 64), (31, 17, 64, 64, 64), (50, 16, 33, 10, 64),
+    (18, 7, 7, 7, 128)]
 
 
 @pytest.mark.parametrize("T,k,E,C,H", CASES)
@@ -45,3 +46,25 @@ def test_logits(T, H, E):
     bound = (x.double().abs() @ w.double().abs().T + bias.double().abs()) * (H / 256 + 13) * 2.0 ** -24
     assert bool(((logits.double() - ref).abs() <= bound).all())
     assert torch.equal(idx.long(), logits.topk(2, dim=1).indices)
+
+
+@pytest.mark.parametrize("T", [9, 18, 50])
+def test_ties_over_rows_of_lanes(T):
+    """Experts with the same router row tie exactly, within a row of lanes and between rows: the lower id comes first."""
+    import torch
+    from paper_2603_09983_amd import binding as B
+    print(f"[case] {T}", flush=True)
+    E, H, k, F, C = 64, 64, 12, 64, 8
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T)
+    w = (torch.randn(8, H, device="cuda", generator=g) * 0.02)[torch.randint(0, 8, (E,), generator=g, device="cuda")].contiguous()
+    x = torch.randn(T, H, device="cuda", generator=g).bfloat16()
+    table = torch.full((E,), -1, dtype=torch.int32, device="cuda")
+    sh = B.make_shape(T, H, E, k, F, C)
+    buf = B.LayerBuffers.allocate(sh)
+    pools = [torch.zeros(C, F, H, dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    B.moe_verify_layer(sh, x, w, None, table, *pools, None, None, None, buf.topk_idx, buf.topk_w, buf.hist, buf.slot_idx,
+                       buf.miss_list, buf.miss_count, buf.out, False, False, buf.workspace)
+    s = (x.double() @ w.double().T).cpu().numpy()
+    want = np.argsort(-s.round(9), axis=1, kind="stable")[:, :k]   # (equal rows give equal sums; stable: the lower id first)
+    assert np.array_equal(buf.topk_idx.cpu().numpy(), want)
