@@ -328,11 +328,6 @@ __global__ __launch_bounds__(1024) void layer_kernel(LayerArgs a, RouteArgs ra)
         // every workgroup: its share of the T*E dot products, one per wavefront, each logit stored with the
         // call's number as one 64-bit word
         const int E = ra.E, TE = T * E;
-        const size_t n_pub = list_pub_entries(T, kk, C);
-        // (workgroup 0 gives the call its number in the control block, at its end, only when every workgroup
-        // has read the old one: each says so with a stamped word of its own)
-        u64 *const seen = ra.lists_pub + (size_t)kListReplicas * n_pub;
-        if (tid == 0) store_entry(seen + b, tag, 1u);
         int tab_v = -1;
         if (b == 0 && tid < E) tab_v = ra.slot_table[tid];
         const uint16_t *x = (const uint16_t *)ra.hidden;
@@ -399,7 +394,7 @@ __global__ __launch_bounds__(1024) void layer_kernel(LayerArgs a, RouteArgs ra)
                 // the final sum of every workgroup needs the gate weights: plain stores of this workgroup are
                 // not visible to the others inside the launch, so they travel as stamped entries too
                 if (lane < kk) {
-                    u64 *gw_pub = seen + kMaxGroups;
+                    u64 *gw_pub = ra.lists_pub + (size_t)kListReplicas * list_pub_entries(T, kk, C) + kMaxGroups;
                     for (int rep = 0; rep < kListReplicas; ++rep)
                         store_entry(gw_pub + (size_t)rep * A + t * kk + lane, wtag, __float_as_uint(gate));
                 }
@@ -539,7 +534,11 @@ __global__ __launch_bounds__(1024) void layer_kernel(LayerArgs a, RouteArgs ra)
             }
         }
         for (int i = tid; i < A; i += kThreads) pos_s[i] = -1;
+        asm volatile("" : : "s"(tag));   // (read by now in every wavefront)
         __syncthreads();
+        // Workgroup 0 gives the call its number in the control block, at its end, only when every workgroup has read the old
+        // one: each says so with a stamped word of its own, behind a barrier, for each wavefront reads the number for itself.
+        if (tid == 0) store_entry(ra.lists_pub + (size_t)kListReplicas * n_pub + b, tag, 1u);
         for (int i = tid; i < (int)n_pub; i += kThreads) {
             u64 v = 0;
             int polls = 0;
