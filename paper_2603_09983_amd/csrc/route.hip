@@ -6,16 +6,19 @@
 //
 // These steps move a few hundred kilobytes; what they cost is the chain of
 // dependent trips to memory and of workgroup barriers, so the kernel is built
-// to keep that chain short.  The T*E dot products are dealt one per wavefront,
-// round-robin over as many workgroups as the device has CUs (a CU that had to
-// fetch the operands of sixteen of them takes microseconds longer than one
-// that fetches two or three).  Each logit goes to memory together with the
-// number of the call as ONE 64-bit atomic store; workgroup 0, one wavefront
-// per token, reads the entries with atomic loads until they carry that number
-// (a bounded number of times), so the hand-over needs no counter, no fence and
-// no cache write-back.  It then picks each token's Top-k out of registers (k
-// maxima over the wavefront) and produces histogram, slot counts, miss list and
-// per-slot lists out of LDS with independent threads between a few barriers.
+// to keep that chain short.  The T*E dot products are dealt one per wavefront
+// (many of them: four tokens' with one expert), round-robin over as many
+// workgroups as the device has CUs (a CU that had to fetch the operands of
+// sixteen of them takes microseconds longer than one that fetches two or three).
+// Each logit goes to memory together with the number of the call as ONE 64-bit
+// atomic store; the workgroups that rank read the entries with atomic loads until
+// they carry that number (a bounded number of times), so the hand-over needs no
+// counter, no fence and no cache write-back.  Up to 16 tokens workgroup 0 ranks, one
+// wavefront per token; beyond (up to 4096 picks), each workgroup ranks sixteen tokens,
+// four to a wavefront where there are few experts, and hands the ids to workgroup 0
+// the same way.  A token's Top-k is picked out of registers (k maxima); workgroup 0
+// then produces histogram, slot counts, miss list and per-slot lists out of LDS with
+// independent threads between a few barriers.
 // On this one serial path every instruction counts: a wavefront issues one
 // about every four cycles.
 #include "moe_internal.h"
@@ -25,11 +28,14 @@ namespace moe {
 
 namespace {
 
-// More dot products than this: four tokens to a wavefront.  256 workgroups of sixteen wavefronts do 4096 at a time, so with more than
-// three times as many every wavefront still has four tokens' loads in flight, and the router row comes once for them (256 tokens, 64
-// experts, H = 2048: 17.6 -> 13.6 us behind a layer's weights).  With fewer, half of the wavefronts would have none: 128 tokens 14.8 us so,
-// 12.6 with one dot product each.
-constexpr int kFourTokens = 12288;
+// More dot products than this for each wavefront of the launch: four tokens of one expert to a wavefront, and the router row comes
+// once for them.  Just above the line three of four wavefronts have work, below it fewer, and what the idle ones cost is more than
+// the rows that are not fetched again.  Measured behind a read of 256 MB, one token | four tokens a wavefront, us
+// (4096 wavefronts; T E = 8192, 11264, 12288, 16384):  64 experts, H = 2048  13.9 | 14.6, 15.4 | 15.2, 16.3 | 15.4, 19.2 | 16.1;
+// 128 experts  14.4 | 15.6, 15.6 | 16.0, 16.9 | 16.1, 19.7 | 17.0;  64 experts, H = 4096  18.5 | 19.7, 21.8 | 20.6, 23.5 | 21.0,
+// 27.9 | 22.1.  (The rows of H = 512 take less than their hand-over: there four are ahead from T E = 6144 on, 10.3 | 9.5; not
+// a line of its own.)
+constexpr int kFourTokens = 3;
 
 __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs a)
 {
@@ -51,10 +57,10 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs a)
     int tab_v = -1;
     if (b == 0 && a.slot_table && tid < E) tab_v = a.slot_table[tid];   // (E <= kMaxE <= kRouteThreads)
 
-    // s[t,e] = W_g[e,:] . h[t,:]: one wavefront per dot product, lanes stride H four at a time
+    // s[t,e] = W_g[e,:] . h[t,:]: lanes stride H four at a time
     const uint16_t *x = (const uint16_t *)a.hidden;
-    if (TE > kFourTokens) {
-        // ... or four tokens' dot products with one expert (lane i of the wavefront hands on the i-th)
+    if (TE > kFourTokens * kRouteWaves * G) {
+        // four tokens' dot products with one expert to a wavefront (its lane i hands on the i-th)
         const int n_tasks = (T + 3) / 4 * E;
         for (int q = b + w * G; q < n_tasks; q += G * kRouteWaves) {
             const int t0 = q / E * 4, e = q - t0 / 4 * E;
@@ -76,21 +82,23 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs a)
                 if (a.logits_opt) a.logits_opt[at] = s;
             }
         }
-    } else
-    for (int q = b + w * G; q < TE; q += G * kRouteWaves) {
-        const int t = q / E, e = q - t * E;
-        const float bias = a.router_bias ? load_bias(a.router_bias, e) : 0.f;
-        float acc = wave_dot(a.router_w + (size_t)e * H, x + (size_t)t * H, H);
+    } else {
+        // one dot product
+        for (int q = b + w * G; q < TE; q += G * kRouteWaves) {
+            const int t = q / E, e = q - t * E;
+            const float bias = a.router_bias ? load_bias(a.router_bias, e) : 0.f;
+            float acc = wave_dot(a.router_w + (size_t)e * H, x + (size_t)t * H, H);
 #pragma unroll
-        for (int m = kWave / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, kWave);
-        acc += bias;
-        if (lane == 0) {
-            __hip_atomic_store(a.tagged_logits + q, ((unsigned long long)wtag << 32) | __float_as_uint(acc),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (a.logits_opt) a.logits_opt[q] = acc;
+            for (int m = kWave / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, kWave);
+            acc += bias;
+            if (lane == 0) {
+                __hip_atomic_store(a.tagged_logits + q, ((unsigned long long)wtag << 32) | __float_as_uint(acc),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (a.logits_opt) a.logits_opt[q] = acc;
+            }
         }
     }
-    // ---- ranking: workgroup b ranks tokens 16b .. 16b+15, one wavefront each ----
+    // ---- ranking: workgroup b ranks tokens 16b .. 16b+15 ----
     const int n_rank = (T + kRouteWaves - 1) / kRouteWaves;
     const bool share_ids = n_rank > 1 && A <= kTagIdxEntries;   // ids handed to workgroup 0 as stamped entries
     if (b >= (share_ids ? n_rank : 1)) return;
@@ -105,7 +113,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(RouteArgs a)
     }
     const bool idx_in_lds = A <= kLdsCopy;
     lds_f32 *lg = L.lg_s + w * lg_stride(E);
-    // (a workgroup's sixteen tokens, few experts: four to a wavefront)
+    // (four to a wavefront where rows_topk_gate takes them, else one)
     const bool by_rows = share_ids && idx_in_lds && E <= kWave && a.k <= 16;
     if (by_rows) {
         const int t0 = b * kRouteWaves + w * 4, t_end = T < (b + 1) * kRouteWaves ? T : (b + 1) * kRouteWaves;
