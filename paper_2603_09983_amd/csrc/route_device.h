@@ -149,7 +149,8 @@ __device__ __forceinline__ void wave_topk_gate(int E, int k, int32_t *idx_out, l
 // row owns experts l, l + 16, l + 32, l + 48.  Returns false if the wait ran out.
 // For batches of which every wavefront would have tokens: sixteen wavefronts that rank one token each share four vector units, and
 // a step costs half as many instructions a token so (17 tokens on 64 experts of 2048 x 1408, two a wavefront before: the layer 118.9 ->
-// 117.3 us; 1 to 16 tokens, one a wavefront, gain nothing: 25.6 | 25.8 us at one, 74.5 | 75.0 at nine).
+// 117.3 us; 1 to 16 tokens, one a wavefront, gain nothing: 25.6 | 25.8 us at one, 74.5 | 75.0 at nine).  E <= 64 because a lane holds
+// four experts; more would take eight keys a lane, which was not measured: there one token to a wavefront stays.
 __device__ __forceinline__ bool rows_topk_gate(int E, int k, int t0, int t_end, const unsigned long long *src_, unsigned tag, int spin,
                                                lds_i32 *idx_lds, int32_t *idx_out_, float *w_out_)
 {

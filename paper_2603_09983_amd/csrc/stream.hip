@@ -459,8 +459,8 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         first_shared_item();
         R = route_args();
         {
-            // one wavefront per token ranks its logits; then histogram, slot lookup, miss list and per-slot lists
-            // out of LDS (which nothing else uses yet: the first tile is still on its way)
+            // a wavefront ranks the logits of one token, or of four; then the per-slot lists out of LDS (which nothing else uses yet:
+            // the first tile is still on its way)
             PostLds L = carve_lds((int *)lds, E, C, A);
             if (tid < E) {
                 L.tab_s[tid] = tab_v;
@@ -468,7 +468,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
             }
             for (int i = tid; i < C * ((T + 31) >> 5); i += kThreads) L.cnt_s[i] = 0;
             lds_f32 *lg = L.lg_s + w * lg_stride(E);
-            // (more tokens than wavefronts, and few enough experts: four to a wavefront)
+            // (more tokens than wavefronts, and few enough experts for rows_topk_gate: four to a wavefront)
             const bool by_rows = MODE == 1 && E <= kWave && a.k <= 16;
             if (by_rows && w * 4 < T &&
                 !rows_topk_gate(E, a.k, w * 4, T, R->tagged_logits + (size_t)(b % kLogitReplicas) * TE, rtag, rspin, L.idx_s,
