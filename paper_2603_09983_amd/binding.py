@@ -3,7 +3,9 @@
 Every function has the name and argument meaning of its C entry point in
 include/moe_spac.h.  Tensors are torch CUDA(HIP) tensors used as typed device
 pointers; the stream is torch's current stream unless one is given.  There is
-no fallback: if the library is not built, importing this module raises.
+no fallback: if the library is not built, importing this module raises.  (Only the
+reading of tensor addresses has two forms, a native one built beside the library
+for one torch, and Python for any other.)
 """
 from __future__ import annotations
 
@@ -13,6 +15,8 @@ from dataclasses import dataclass
 from typing import Optional
 
 import torch
+
+from .build import torch_build
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # (MOE_SPAC_LIB names another build of the same library, e.g. the one with the timeline stamps)
@@ -24,12 +28,6 @@ if not os.path.exists(LIB_PATH):
         "(hipcc, gfx950). There is no CPU or PyTorch fallback for the MoE layer.")
 
 _lib = ctypes.CDLL(LIB_PATH)
-
-try:
-    from ._pointers import pointers as _pointers
-except ImportError as e:
-    raise ImportError(f"{os.path.join(_HERE, '_pointers.so')} is missing or does not load ({e}): build it with "
-                      "`python -c 'import __graft_entry__ as g; g.build()'`") from e
 
 OK, ERR_NULL, ERR_SHAPE, ERR_ALIGN, ERR_WORKSPACE, ERR_LAUNCH, ERR_SCRATCH = 0, -1, -2, -3, -4, -5, -6
 STATIC_SCRATCH_BYTES = 16 << 20
@@ -99,6 +97,21 @@ def _ptr(t: Optional[torch.Tensor]):
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("device-resident contiguous tensors only")
     return t.data_ptr()
+
+
+def _choose_pointers(native):
+    """pointers(*tensors) -> their addresses: in one call of the native module where it was built for this torch, else one by one."""
+    if getattr(native, "torch_build", None) != torch_build():
+        return lambda *tensors: tuple(map(_ptr, tensors))
+    native.general(_ptr)
+    return native.pointers
+
+
+try:
+    from . import _pointers as _native
+except ImportError:   # (none for this Python, or for another torch whose symbols are not here)
+    _native = None
+_pointers = _choose_pointers(_native)
 
 
 def _ptr_store(t: torch.Tensor):
@@ -257,8 +270,8 @@ def moe_verify_layer_static(shape: MoeShape, hidden, router_w, router_bias, slot
 
 
 def moe_utility_init(f_prev, s, theta_up, theta_dn, L, N, gamma, stream=None, check=True) -> int:
-    return _check(_lib.moe_utility_init(_ptr(f_prev), _ptr(s), _ptr(theta_up), _ptr(theta_dn), L, N, gamma,
-                                        _stream(stream)), "moe_utility_init", check)
+    return _check(_lib.moe_utility_init(*_pointers(f_prev, s, theta_up, theta_dn), L, N, gamma, _stream(stream)),
+                  "moe_utility_init", check)
 
 
 def moe_utility_update(f, f_prev, s, theta_up, theta_dn, slot_table, n_tau, L, N, K, lam_num, lam_den,
