@@ -63,7 +63,7 @@ def _run(cmd, verbose):
     p = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in p.stdout.splitlines() if "packed-fp32-ops" not in l)
     if p.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError(" ".join(cmd) + " failed:\n" + out)
     if verbose and out.strip():
         print(out)
 

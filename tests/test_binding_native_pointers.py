@@ -49,6 +49,11 @@ def test_build_knows_the_torch_it_was_built_for(monkeypatch, tmp_path):
     assert build.pointers_stale() and build.stale()
 
 
+def test_build_names_the_command_that_failed():
+    with pytest.raises(RuntimeError, match="^false --flag failed"):
+        build._run(["false", "--flag"], False)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("make,good", [
     (lambda: torch.zeros(6, 4, device="cuda"), True),
