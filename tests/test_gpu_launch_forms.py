@@ -31,7 +31,8 @@ def _case(name):
         "all_miss": dict(T=6, H=128, E=16, k=2, F=64, C=1, n_shared=1, F_shared=64),
         "k_equals_e": dict(T=3, H=64, E=4, k=4, F=64, C=4),
         "e128": dict(T=9, H=256, E=128, k=8, F=128, C=64, hidden="unit"),
-        # 17-32 tokens: two token groups per pass; the two-launch form ranks two tokens per wavefront
+        # 17-32 tokens: two token groups per pass; the two-launch form ranks four tokens to a wavefront, with more than 64
+        # experts two, one after the other
         "twenty_four": dict(T=24, H=512, E=64, k=6, F=384, C=40, n_shared=1, F_shared=128, hidden="unit"),
         "thirty_two_e128": dict(T=32, H=256, E=128, k=8, F=128, C=96, hidden="unit"),
         "panels_of_2112": dict(T=5, H=2112, E=7, k=2, F=256, C=3, n_shared=3, F_shared=192),
