@@ -534,7 +534,7 @@ __global__ __launch_bounds__(1024) void layer_kernel(LayerArgs a, RouteArgs ra)
             }
         }
         for (int i = tid; i < A; i += kThreads) pos_s[i] = -1;
-        asm volatile("" : : "s"(tag));   // (read by now in every wavefront)
+        asm volatile("" : : "v"(tag));   // (read by now in every wavefront)
         __syncthreads();
         // Workgroup 0 gives the call its number in the control block, at its end, only when every workgroup has read the old
         // one: each says so with a stamped word of its own, behind a barrier, for each wavefront reads the number for itself.

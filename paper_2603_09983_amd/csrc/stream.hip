@@ -458,6 +458,15 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
         }
         first_shared_item();
         R = route_args();
+        // Workgroup 0 gives the call its number in the control block only when every workgroup has read the old one: each says
+        // so with a stamped word of its own, behind a barrier, for each wavefront reads the number for itself, and one without a dot
+        // product of its own that read it late would wait for the next call's logits.  (Here, where the logits are waited for
+        // anyway; behind the ranking workgroup 0 waits for the words: one token 27.4 -> 27.7 us.)
+        asm volatile("" : : "v"(rtag));   // (read by now, also where this wavefront had no use for it)
+        __syncthreads();
+        if (tid == 0)
+            __hip_atomic_store(glob(R->lists_pub) + (size_t)kListReplicas * list_pub_entries(T, a.k, C) + b,
+                               ((unsigned long long)rtag << 32) | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         {
             // a wavefront ranks the logits of one token, or of four; then the per-slot lists out of LDS (which nothing else uses yet:
             // the first tile is still on its way)
@@ -506,14 +515,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
             }
             // (few slots, and the lists' places below not where the ranking keeps its own data)
             short_lists = C <= kWave && (size_t)((unsigned char *)ctl_s - lds) >= post_lds_bytes(E, C, A, true);
-            asm volatile("" : "+s"(rtag));   // (read by now, also where this wavefront had no use for it)
             __syncthreads();
-            // Workgroup 0 gives the call its number in the control block only when every workgroup has read the old one: each
-            // says so with a stamped word of its own, behind a barrier, for each wavefront reads the number for itself, and one
-            // without a dot product of its own that read it late would wait for the next call's logits.
-            if (tid == 0)
-                __hip_atomic_store(glob(R->lists_pub) + (size_t)kListReplicas * list_pub_entries(T, a.k, C) + b,
-                                   ((unsigned long long)rtag << 32) | 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (short_lists) {
                 // Every wavefront that has an assignment works the slots' prefix sums out for itself, from ballots; with up to 64
                 // assignments that is the first one only, and no barrier.  What of this the step outputs and the down kernel

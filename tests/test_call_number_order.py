@@ -10,12 +10,13 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 
 def _said_behind_a_barrier(source, number, said):
-    """number, said: patterns of the read of the call number and of the store of the workgroup's word."""
+    """number, said: patterns of the read of the call number and of the store of the workgroup's word.  What holds the read in
+    front of the barrier takes a vector register: the number may be in one, and a copy to a scalar register does not compile then."""
     source = re.sub(r"//[^\n]*", "", source)
     first, store = re.search(number, source), re.search(said, source)
     assert first and store and first.start() < store.start()
     used, barrier, stack, n = False, [], [], 0
-    for m in re.finditer(r"[{}]|asm volatile\(\"\" : [^)]*\"\+?s\"\(r?tag\)|__syncthreads\(\)", source[:store.start()]):
+    for m in re.finditer(r"[{}]|asm volatile\(\"\" : : \"v\"\(r?tag\)\)|__syncthreads\(\)", source[:store.start()]):
         if m.group() == "{":
             stack.append(n)
             n += 1
@@ -40,8 +41,8 @@ def test_number_read_by_all_before_the_workgroup_says_so(name, number, said):
 
 
 def test_the_check_sees_what_it_looks_for():
-    good = 'n = ctrl[k]; { asm volatile("" : "+s"(rtag)); __syncthreads(); if (x) put(b); }'
+    good = 'n = ctrl[k]; { asm volatile("" : : "v"(rtag)); __syncthreads(); if (x) put(b); }'
     assert _said_behind_a_barrier(good, r"ctrl\[k\]", r"put\(b\)")
     for bad in (good.replace("__syncthreads(); ", ""), good.replace("__syncthreads();", "if (y) { __syncthreads(); }"),
-                good.replace('asm volatile("" : "+s"(rtag)); ', ""), "n = ctrl[k]; put(b); __syncthreads();"):
+                good.replace('asm volatile("" : : "v"(rtag)); ', ""), good.replace('"v"', '"s"'), "n = ctrl[k]; put(b); __syncthreads();"):
         assert not _said_behind_a_barrier(bad, r"ctrl\[k\]", r"put\(b\)")
