@@ -1,4 +1,4 @@
-// Device-side pieces of the routing steps (Top-k and gate of one token per wavefront, histogram, slot
+// Device-side pieces of the routing steps (Top-k and gate of one token or of four per wavefront, histogram, slot
 // lookup, miss list and per-slot lists of a whole batch per workgroup), shared by the routing kernel and
 // by the gate/up kernel that does the routing itself.  Included inside an unnamed namespace of each
 // translation unit.

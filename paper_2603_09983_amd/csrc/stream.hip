@@ -1100,8 +1100,8 @@ bool stream_ragged(const StreamArgs &x, bool gateup)
 
 // Batches of more than 32 tokens (use_stream_large() true: single panels of whole 64s).  An expert with more tokens than
 // the 32 whose B operand the registers hold is several entries of the item list, one for each 32 tokens (a shared expert has
-// all tokens); its weights are streamed once for each (FETCH_SIZE, 128 tokens Zipf-skewed, 55 blocks on 44 experts: gate/up
-// 640 MB for 508 MB of weights).  Nothing but the item list depends on the other experts' tokens.  Against the kernel with both operands in LDS (wide_device.h), 64 experts of
+// all tokens); its weights are streamed once for each (FETCH_SIZE, 128 tokens Zipf-skewed, 54 blocks on 44 experts: gate/up
+// 629 MB for 508 MB of weights).  Nothing but the item list depends on the other experts' tokens.  Against the kernel with both operands in LDS (wide_device.h), 64 experts of
 // 2048 x 1408, us per layer: 128 tokens 155 | 170; 256 tokens (a mean of 24 an expert) 191 | 217; 512 tokens 347 | 367; 1000 tokens
 // 690 | 675; Zipf-skewed 64 tokens 134 | 143, 128 tokens 181 | 189, 256 tokens 263 | 271; one shared expert, 33 tokens 147 | 159.
 static hipError_t launch_large(const StreamArgs &a, bool gateup, int npi, int tile_lds_bytes, size_t lds, hipStream_t s)

@@ -9,7 +9,7 @@
 // 512 columns, every load instruction one row's consecutive kilobyte, and the accumulators stay in registers for the
 // whole contraction.  Bound: HBM for the weights.  An expert's weights are read once for each 32 of its tokens, and the
 // L2s do not keep them in between (FETCH_SIZE, 8 experts of 4096 x 14336: gate/up 1.92 GB for 1.88 GB of weights at 64 tokens,
-// all lists within 32; 2.31 GB at 128 tokens, 10 blocks on 8 experts, where 2.35 GB would be no reuse at all).
+// all lists within 32; 2.77 GB at 128 tokens, 12 blocks on 8 experts, where 2.82 GB would be no reuse at all).
 //
 // One workgroup of sixteen wavefronts per CU takes items b, b + G, .. and keeps three chunks in flight, across items
 // (3 x 64 KB of weights).
