@@ -376,8 +376,9 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
     u32x4 bx[NG][kPieces];
     int bx_key = -1, bx_panel = -1;   // expert (and panel) whose operand the registers hold
 
-    // B operand of this wavefront's column blocks: token 16*gr + n sits on column n of group gr.  Drains every load in flight (rare path), unless
-    // told to leave the wait to the caller.
+    // B operand of this wavefront's column blocks: token 16*gr + n sits on column n of group gr.  Drains every load in flight, unless
+    // told to leave the wait to the caller: once for each expert of a run where the items have one panel, at every step where
+    // they have several (a contraction beyond 2048).
     auto load_bx = [&](bool wait = true) {
         const int nkb = col_blocks(c_rs);
         const int cstart = RAGGED && cpan > 0 && cpan + 1 == cnpan ? cK - c_rs / 2 : cpan * (c_rs / 2);   // the panel's first column
@@ -483,7 +484,7 @@ __device__ __forceinline__ void stream_body(const StreamArgs &a, const int tile_
                 !rows_topk_gate(E, a.k, w * 4, T, R->tagged_logits + (size_t)(b % kLogitReplicas) * TE, rtag, rspin, L.idx_s,
                                 b == 0 ? R->topk_idx : nullptr, R->topk_w) && lane == 0)
                 atomicOr(R->error_flag, 1u);
-            for (int t = by_rows ? T : w; t < T; t += kWaves) {   // (one token per wavefront up to 16 tokens, two up to 32)
+            for (int t = by_rows ? T : w; t < T; t += kWaves) {   // (one token per wavefront up to 16 tokens, else two)
                 const auto src = glob(R->tagged_logits) + (size_t)(b % kLogitReplicas) * TE + (size_t)t * E;
                 for (int e0 = 0; e0 < E; e0 += kWave) {
                     const int e = e0 + lane;
