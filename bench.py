@@ -562,17 +562,18 @@ def main():
                     B.moe_pool_load(*store, *stage, mv_list, mv_slot, mv_n, n_move, shape.H, shape.F)
                 torch.cuda.synchronize()
                 host_load_us = (time.perf_counter() - t0) / 5 * 1e6
-                # the copy takes many verify steps: keep one in flight on the second stream all the time
+                # the copy takes many verify steps: keep one in flight on the second stream all the time.  The host is many
+                # steps ahead of the device, so it cannot go by what has finished: it puts as many copies in the queue as fit
+                every = max(1, int(host_load_us / us_alone))
+
                 def chain_host():
                     torch.cuda.synchronize()
-                    done = torch.cuda.Event()
                     n_loads = 0
                     t0 = time.perf_counter()
                     for i in range(4 * n_ov):
                         step(i)
-                        if n_loads == 0 or done.query():
+                        if i % every == 0:
                             B.moe_pool_load(*store, *stage, mv_list, mv_slot, mv_n, n_move, shape.H, shape.F, stream=side)
-                            done.record(side)
                             n_loads += 1
                     torch.cuda.current_stream().synchronize()
                     us = (time.perf_counter() - t0) / (4 * n_ov) * 1e6

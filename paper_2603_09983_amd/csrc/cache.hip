@@ -244,9 +244,10 @@ extern "C" int moe_pool_load(const void *store_gate, const void *store_up, const
     // A store in host memory is read at the rate of the link to the host, a hundred times below HBM's: a
     // chip-wide launch would hold every wavefront slot for a millisecond and keep the verify steps'
     // workgroups waiting.  Sixteen workgroups with one 16-byte word per thread in flight (64 KB) reach 9/10
-    // of the link's rate (51 of 56 GB/s) and disturb the verify steps least.  Measured per cfg2 layer with a
-    // copy always in flight: +5.7 us; 32 workgroups +7.5, 64 +11.5, a chip-wide launch +15; four words per
-    // thread in flight +8 (4 workgroups) to +12 (16).
+    // of the link's rate (51 of 57 GB/s).  Measured with a copy of 69 MB always in flight, per layer of 9 tokens on 64 experts of
+    // 2048 x 1408 with two shared ones (76.6 us alone), and what a copy takes beside the layers: +33 us, 1.85 ms (0.56 ms of layer time lost per
+    // copy, the least); 8 workgroups +30, 3.5 ms; 32 +40, 1.75 ms; 64 +61, 2.1 ms; a chip-wide launch +79, 2.5 ms; four words per
+    // thread in flight +74, 2.7 ms (4 workgroups) and +67, 2.2 ms (16).
     bool narrow = false;
     {
         hipPointerAttribute_t attr;
